@@ -1,64 +1,45 @@
-// Index build (Eq. 4 and Eq. 5): k_build and its launcher. The segment
-// close of an append runs the same kernel on one segment, so appends and
-// rebuilds agree bit for bit.
+// Index build (Eq. 4 and Eq. 5): k_build_bf16 (bf16 keys) and k_build_f32
+// (fp32 keys) and their launchers. The segment close of an append runs the
+// same kernel on one segment, so appends and rebuilds agree bit for bit.
 #include "radar_impl.h"
 
 namespace radar_impl {
 
 // ---------------------------------------------------------------------------
-// k_build: segment summaries (Eq. 4, Eq. 5)
+// k_build_f32: segment summaries (Eq. 4, Eq. 5) of fp32 keys
 // ---------------------------------------------------------------------------
 // Work item = one (b, kv head, segment) and one slice of 64*FT features.
 // Wave w of the workgroup owns features [w*16*FT, (w+1)*16*FT) of the slice
-// and keeps that slice of Omega (rounded to the MFMA input type) resident in
-// registers as MFMA B operands for the whole kernel. Keys stream through two
-// LDS buffers in tiles of 64 tokens (register-prefetched one tile ahead, one
-// barrier per tile); every wave
+// and keeps that slice of Omega resident in registers as MFMA B operands for
+// the whole kernel. Keys stream through two LDS buffers in tiles of 64 tokens
+// (register-prefetched one tile ahead, one barrier per tile); every wave
 // multiplies each 16-token sub-tile with its Omega slice on the matrix cores,
 // applies exp2(acc * s1 - |k|^2 * s2) and adds the result into per-lane
 // column sums. At the segment's end the sums are reduced across the four
 // row groups of the MFMA output and scaled by 1 / (c sqrt(n)).
 //
-// MFMA operand layout (16x16 output tiles, both instructions):
+// MFMA operand layout (v_mfma_f32_16x16x4_f32; the bf16 16x16x32 one below
+// holds eight k-slots per lane instead of one):
 //   A (keys):    lane l supplies row (l & 15), k-slots of group (l >> 4)
 //   B (Omega^T): lane l supplies column (l & 15), same k-slots
 //   D:           lane l holds rows 4*(l >> 4) + j, j < 4, column (l & 15)
 // The k-slot -> head-dim map is the same for A and B, so the dot products
-// are the same whatever order the hardware sums them in.
-template <typename T> struct MfmaCfg;
-template <> struct MfmaCfg<bf16_t> {     // v_mfma_f32_16x16x32_bf16
-  static constexpr int kK = 32;          // head dims per instruction
-  typedef bf16x8_t frag_t;
-};
-template <> struct MfmaCfg<float> {      // v_mfma_f32_16x16x4_f32
-  static constexpr int kK = 4;
-  typedef float frag_t;
-};
-
-template <typename T, int D, int TL>
-struct BuildTile {
-  static constexpr int kRowBytes = D * (int)sizeof(T);
-  static constexpr int kPitch = kRowBytes + 16;          // LDS row pitch
-  static constexpr int kChunksPerRow = kRowBytes / 16;
-  static constexpr int kChunksPerThread = TL * kChunksPerRow / 256;
-};
-
-// TL: keys per LDS tile (64, or 128 for bf16 keys in segments of >= 128)
-template <typename T, int D, int FT, int TL>
-__global__ __launch_bounds__(256) void k_build(
-    const T* __restrict__ K, const void* __restrict__ omega, bool obf,
-    float* __restrict__ summ, int n, int c, int64_t cap, int64_t s_cap,
-    int seg_first, int seg_count, int64_t n_items, float s1, float s2,
+// are the same whatever order the hardware sums them in. The fp32 matrix
+// rate (1/16 of bf16) bounds this kernel, not its staging.
+template <int D, int FT>
+__global__ __launch_bounds__(256) void k_build_f32(
+    const float* __restrict__ K, const float* __restrict__ omega, float* __restrict__ summ,
+    int n, int c, int64_t cap, int64_t s_cap, int seg_first, int seg_count, int64_t n_items, float s1, float s2,
     float out_scale, int64_t kv_head_stride_rows,
     const int64_t* __restrict__ pos, int Hkv, int n_sink) {
-  using MC = MfmaCfg<T>;
-  using BT = BuildTile<T, D, TL>;
-  constexpr int KB = D / MC::kK;
-  constexpr int CPR = BT::kChunksPerRow;
-  constexpr int CPT = BT::kChunksPerThread;
+  constexpr int TL = kTile;                // keys per LDS tile
+  constexpr int KB = D / 4;                // MFMA steps per product
+  constexpr int kPitch = D * 4 + 16;       // LDS row pitch in bytes
+  constexpr int CPR = D / 4;               // 16-byte chunks per row
+  constexpr int CPT = TL * CPR / 256;      // chunks per thread
   static_assert(CPT >= 1 && (256 % CPR) == 0, "tile shape");
 
-  __shared__ __attribute__((aligned(16))) unsigned char tile_lds[2][TL * BT::kPitch];
+  __shared__ __attribute__((aligned(16))) unsigned char tile_lds[2][TL * kPitch];
   __shared__ float nrm_lds[2][TL];
 
   const int tid = threadIdx.x;
@@ -69,25 +50,13 @@ __global__ __launch_bounds__(256) void k_build(
   const int fbase = blockIdx.y * (64 * FT) + wave * (16 * FT);
 
   // Omega slice -> B fragments (resident for the whole kernel)
-  typename MC::frag_t bfrag[FT][KB];
+  float bfrag[FT][KB];
 #pragma unroll
   for (int f = 0; f < FT; ++f) {
     const int64_t orow = (int64_t)(fbase + f * 16 + col) * D;
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
-      if constexpr (sizeof(T) == 2) {
-        const int64_t i0 = orow + kb * 32 + grp * 8;
-        const float4 a = obf ? load_omega4<true>(omega, i0) : load_omega4<false>(omega, i0);
-        const float4 b = obf ? load_omega4<true>(omega, i0 + 4) : load_omega4<false>(omega, i0 + 4);
-        bf16x8_t v;
-        v[0] = (short)f32_to_bf16(a.x); v[1] = (short)f32_to_bf16(a.y);
-        v[2] = (short)f32_to_bf16(a.z); v[3] = (short)f32_to_bf16(a.w);
-        v[4] = (short)f32_to_bf16(b.x); v[5] = (short)f32_to_bf16(b.y);
-        v[6] = (short)f32_to_bf16(b.z); v[7] = (short)f32_to_bf16(b.w);
-        bfrag[f][kb] = v;
-      } else {
-        bfrag[f][kb] = static_cast<const float*>(omega)[orow + kb * 4 + grp];
-      }
+      bfrag[f][kb] = omega[orow + kb * 4 + grp];
     }
   }
 
@@ -115,7 +84,7 @@ __global__ __launch_bounds__(256) void k_build(
     return it;
   };
   // base row pointer of an item, computed once per segment
-  auto item_base = [&](int64_t it) -> const T* {
+  auto item_base = [&](int64_t it) -> const float* {
     const uint32_t bh = (uint32_t)it / (uint32_t)seg_count;
     return K + ((int64_t)bh * kv_head_stride_rows + (int64_t)seg_of(it) * c) * D;
   };
@@ -123,9 +92,9 @@ __global__ __launch_bounds__(256) void k_build(
   uint4 pre[CPT];
   int pre_valid = 0;
   // tile tl of the item whose rows start at `base`
-  auto fetch = [&](const T* base, int tl_) {
+  auto fetch = [&](const float* base, int tl_) {
     pre_valid = min(TL, c - tl_ * TL);
-    const T* src = base + (int64_t)tl_ * TL * D;
+    const float* src = base + (int64_t)tl_ * TL * D;
 #pragma unroll
     for (int p = 0; p < CPT; ++p) {
       const int ci = p * 256 + tid;
@@ -144,30 +113,14 @@ __global__ __launch_bounds__(256) void k_build(
     for (int p = 0; p < CPT; ++p) {
       const int ci = p * 256 + tid;
       const int row = ci / CPR, ch = ci % CPR;
-      *reinterpret_cast<uint4*>(tb + row * BT::kPitch + ch * 16) = pre[p];
+      *reinterpret_cast<uint4*>(tb + row * kPitch + ch * 16) = pre[p];
       float sq = 0.f;
-      if constexpr (sizeof(T) == 2) {
-        // bf16 pairs: one dot2 per 32-bit word (exact products, fp32 sum)
-        const uint32_t w[4] = {pre[p].x, pre[p].y, pre[p].z, pre[p].w};
+      float e[4];
+      unpack16<float>(pre[p], e);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bf16x2v_t v = __builtin_bit_cast(bf16x2v_t, w[i]);
-          sq = __builtin_amdgcn_fdot2_f32_bf16(v, v, sq, false);
-        }
-      } else {
-        float e[4];
-        unpack16<T>(pre[p], e);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sq = fmaf(e[i], e[i], sq);
-      }
-      if constexpr (CPR == 8) {
-        sq += dpp_f<kDppQuadSwap1>(sq);
-        sq += dpp_f<kDppQuadSwap2>(sq);
-        sq += dpp_f<kDppHalfMirror>(sq);
-      } else {
-        sq = row_sum(sq);
-        if constexpr (CPR == 32) sq = xor_sum<16>(sq);
-      }
+      for (int i = 0; i < 4; ++i) sq = fmaf(e[i], e[i], sq);
+      sq = row_sum(sq);
+      if constexpr (CPR == 32) sq = xor_sum<16>(sq);
       if (ch == 0) nrm_lds[buf][row] = sq * s2;
     }
   };
@@ -179,14 +132,11 @@ __global__ __launch_bounds__(256) void k_build(
 #pragma unroll
     for (int st = 0; st < TL / 16; ++st) {
       if (!FULL && st * 16 >= valid) break;
-      typename MC::frag_t afrag[KB];
-      const unsigned char* arow = tb + (st * 16 + col) * BT::kPitch;
+      float afrag[KB];
+      const unsigned char* arow = tb + (st * 16 + col) * kPitch;
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
-        if constexpr (sizeof(T) == 2)
-          afrag[kb] = *reinterpret_cast<const bf16x8_t*>(arow + (kb * 32 + grp * 8) * 2);
-        else
-          afrag[kb] = *reinterpret_cast<const float*>(arow + (kb * 4 + grp) * 4);
+        afrag[kb] = *reinterpret_cast<const float*>(arow + (kb * 4 + grp) * 4);
       }
       float nb[4];
 #pragma unroll
@@ -200,10 +150,7 @@ __global__ __launch_bounds__(256) void k_build(
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
         for (int f = 0; f < FT; ++f) {
-          if constexpr (sizeof(T) == 2)
-            acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afrag[kb], bfrag[f][kb], acc[f], 0, 0, 0);
-          else
-            acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag[kb], bfrag[f][kb], acc[f], 0, 0, 0);
+          acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag[kb], bfrag[f][kb], acc[f], 0, 0, 0);
         }
 #pragma unroll
       for (int f = 0; f < FT; ++f)
@@ -221,7 +168,7 @@ __global__ __launch_bounds__(256) void k_build(
   // registers go to the other buffer.
   int64_t item = next_active(blockIdx.x);
   int tl = 0, buf = 0;
-  const T* base = nullptr;
+  const float* base = nullptr;
   if (item < n_items) {
     base = item_base(item);
     fetch(base, 0);
@@ -232,7 +179,7 @@ __global__ __launch_bounds__(256) void k_build(
   while (item < n_items) {
     int64_t nitem = item;
     int ntl = tl + 1;
-    const T* nbase = base;
+    const float* nbase = base;
     if (ntl == ntiles) {
       nitem = next_active(nitem + gridDim.x);
       ntl = 0;
@@ -267,15 +214,271 @@ __global__ __launch_bounds__(256) void k_build(
   }
 }
 
-template <typename T, int D, int FT, int TL>
-radar_status launch_build_tl(const Shape& s, const void* K, const void* omega,
-                             float* summ, int seg_first, int seg_count,
-                             const int64_t* pos, hipStream_t st) {
+// ---------------------------------------------------------------------------
+// k_build_bf16: the summaries of bf16 keys, one wave per segment
+// ---------------------------------------------------------------------------
+// Work item = one (b, kv head, segment) for one slice of 16 * NF features,
+// done by one wave from its first key to its last: the slice of Omega sits
+// in LDS as MFMA B fragments (written once per workgroup), the wave's keys
+// come straight from memory into registers as A fragments, 64 at a time, and
+// the waves never meet after the Omega barrier. Feature tile f + 1 is
+// multiplied while the exp2 epilogue of tile f runs (two accumulator sets);
+// B fragments are read one tile ahead.
+//
+// What bounds it is power: at two waves per SIMD the 64 MFMAs, 64 exp2, 64
+// fma and 64 adds of 64 keys x 64 features take the same time whether they
+// are interleaved by hand or left to the compiler to within 3% (the clock
+// falls from 2.2 to 1.7 GHz as the schedule gets denser), so what counts is
+// work per key and feature. For 1024 (key, feature) quads a SIMD takes 195 ns
+// with everything in registers; B fragments from LDS add 15 ns, keys from
+// HBM 50 ns at 256 features per pass and half of that at 512. Keys staged
+// through LDS and shared by four waves, with a barrier per 128 keys (the
+// layout before this one), took 334 ns: 2.71 -> 2.42 ms for the 33.5 M keys
+// of batch 8 x 32 heads x 128K at n = 256, 615 -> 535 us for 4.2 M keys at
+// n = 512 and 94 -> 67 us for 131 K keys at n = 2048. Fetching the next
+// block ahead (n <= 256, where the registers allow it) is worth 2%.
+template <int D, int NF, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
+    const bf16_t* __restrict__ K, const void* __restrict__ omega, bool obf,
+    float* __restrict__ summ, int n, int c, int64_t cap, int64_t s_cap,
+    int seg_first, int seg_count, uint32_t n_items, float s1, float s2,
+    float out_scale, const int64_t* __restrict__ pos, int Hkv, int n_sink) {
+  constexpr int KB = D / 32;               // MFMA steps per product
+  constexpr int NS = 4;                    // 16-key sub-tiles per block
+  constexpr bool kAhead = NF <= 16;        // registers for two blocks of keys
+  __shared__ __attribute__((aligned(16))) uint4 om_lds[NF * KB * 64];
+  __shared__ __attribute__((aligned(16))) float nrm_lds[NW][NS * 16];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15;
+  const int grp = lane >> 4;
+  const int fbase = blockIdx.y * (16 * NF);
+  const uint32_t stride = gridDim.x * NW;
+
+  // the segment of an item: seg_first + item % seg_count, or, with pos (item
+  // = (b, kv head), one per-sequence segment close), the segment that row
+  // pos[b] completes, -1 if it completes none
+  auto seg_of = [&](uint32_t it) -> int {
+    if (!pos) return seg_first + (int)(it % (uint32_t)seg_count);
+    const int64_t p = pos[it / (uint32_t)Hkv];
+    const int64_t r = p - n_sink;
+    if (p >= cap || r < 0 || (r + 1) % c != 0) return -1;
+    return (int)((r + 1) / c - 1);
+  };
+  auto next_active = [&](uint32_t it) -> uint32_t {
+    while (it < n_items && seg_of(it) < 0) it += stride;
+    return it;
+  };
+  auto item_base = [&](uint32_t it) -> const bf16_t* {
+    return K + ((int64_t)(it / (uint32_t)seg_count) * cap + (int64_t)seg_of(it) * c) * D;
+  };
+
+  uint32_t item = next_active(blockIdx.x * NW + wave);
+  // a workgroup without a segment to close leaves before it reads Omega
+  if (pos && !__syncthreads_or(item < n_items)) return;
+
+  // key blocks: lane (row col, k-slot group grp) of sub-tile st holds bytes
+  // kb * 64 + grp * 16 .. + 16 of key st * 16 + col; keys past the segment
+  // re-read its last one and are masked by their norm
+  auto fetch = [&](uint4 (&A)[NS][KB], const bf16_t* base, int off) {
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+      const int row = min(off + st * 16 + col, c - 1);
+      const bf16_t* src = base + (int64_t)row * D + grp * 8;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+        A[st][kb] = *reinterpret_cast<const uint4*>(src + kb * 32);
+    }
+  };
+
+  uint4 keys[NS][KB];
+  const bf16_t* base = nullptr;
+  if (item < n_items) {
+    base = item_base(item);
+    fetch(keys, base, 0);
+  }
+
+  // Omega slice -> B fragments in LDS: fragment (f, kb), lane (col, grp):
+  // dims kb * 32 + grp * 8 .. + 8 of feature f * 16 + col
+  for (int i = tid; i < NF * KB * 64; i += NW * 64) {
+    const int f = i / (KB * 64), kb = (i / 64) % KB, ln = i & 63;
+    const int64_t i0 = (int64_t)(fbase + f * 16 + (ln & 15)) * D + kb * 32 + (ln >> 4) * 8;
+    uint4 u;
+    if (obf) {
+      u = *reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(omega) + i0);
+    } else {
+      const float* src = static_cast<const float*>(omega) + i0;
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        w[e] = f32_to_bf16(src[2 * e]) | (f32_to_bf16(src[2 * e + 1]) << 16);
+      u = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    om_lds[i] = u;
+  }
+  __syncthreads();
+
+  float psum[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) psum[f] = 0.f;
+
+  // ST sub-tiles of 16 keys, the first `valid` of them real
+  auto compute = [&](const uint4 (&A)[NS][KB], int valid, auto st_tag) {
+    constexpr int ST = decltype(st_tag)::value;
+    // |k|^2 s2 of the block's 64 keys: every lane sums its 16-byte chunks of
+    // a key, the four k-slot groups are added, and LDS turns the column
+    // order of the A operand into the row order of the products; a key past
+    // the segment gets +inf, so its exp2 is 0
+    float nrm = 0.f;
+#pragma unroll
+    for (int st = 0; st < ST; ++st) {
+      float sq = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const uint32_t w[4] = {A[st][kb].x, A[st][kb].y, A[st][kb].z, A[st][kb].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bf16x2v_t v = __builtin_bit_cast(bf16x2v_t, w[i]);
+          sq = __builtin_amdgcn_fdot2_f32_bf16(v, v, sq, false);
+        }
+      }
+      sq = xor_sum<16>(sq);
+      sq = xor_sum<32>(sq);
+      nrm = grp == st ? sq : nrm;
+    }
+    nrm_lds[wave][lane] = lane < valid ? nrm * s2 : INFINITY;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    f32x4_t nb[ST];
+#pragma unroll
+    for (int st = 0; st < ST; ++st)
+      nb[st] = *reinterpret_cast<const f32x4_t*>(&nrm_lds[wave][st * 16 + grp * 4]);
+
+    uint4 b[2][KB];
+    f32x4_t acc[2][ST];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) b[0][kb] = om_lds[kb * 64 + lane];
+    // slot q of tile f: product q of the tile's ST * KB, and of tile f - 1's
+    // ST * 4 elements per lane the fma of element q, the exp2 of q - 1 and
+    // the sum of q - 2 (so no instruction waits for the one before it)
+    constexpr int NP = ST * KB, NE = ST * 4;
+    constexpr int SLOTS = (NP > NE + 2 ? NP : NE + 2);
+#pragma unroll
+    for (int f = 0; f <= NF; ++f) {
+      if (f + 1 < NF) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+          b[(f + 1) & 1][kb] = om_lds[((f + 1) * KB + kb) * 64 + lane];
+      }
+      float x[NE];
+#pragma unroll
+      for (int q = 0; q < SLOTS; ++q) {
+        if (f < NF && q < NP) {
+          const int kb = q / ST, st = q % ST;
+          const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+          acc[f & 1][st] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8_t, A[st][kb]),
+              __builtin_bit_cast(bf16x8_t, b[f & 1][kb]), kb ? acc[f & 1][st] : zero, 0, 0, 0);
+        }
+        if (f > 0) {
+          if (q < NE) x[q] = fmaf(acc[(f - 1) & 1][q / 4][q % 4], s1, -nb[q / 4][q % 4]);
+          if (q >= 1 && q - 1 < NE) x[q - 1] = fast_exp2(x[q - 1]);
+          if (q >= 2 && q - 2 < NE) psum[f - 1] += x[q - 2];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
+  // one block of `cur`; the next block's keys go to `nxt` (the same
+  // registers where there is no room for two blocks)
+  int off = 0;
+  auto step = [&](uint4 (&cur)[NS][KB], uint4 (&nxt)[NS][KB]) {
+    const uint32_t it = item;
+    const int o = off;
+    off += NS * 16;
+    const bool last = off >= c;            // the segment's last block
+    if (last) {
+      item = next_active(item + stride);
+      off = 0;
+      if (item < n_items) base = item_base(item);
+    }
+    if (kAhead && item < n_items) fetch(nxt, base, off);
+    // a remainder of at most 32 keys takes half a block's products
+    if (c - o > 32) compute(cur, c - o, std::integral_constant<int, NS>{});
+    else compute(cur, c - o, std::integral_constant<int, 2>{});
+    if (!kAhead && item < n_items) fetch(nxt, base, off);
+    if (last) {
+      float* dst = summ + ((int64_t)(it / (uint32_t)seg_count) * s_cap + seg_of(it)) * n + fbase;
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        float v = psum[f];
+        v = xor_sum<16>(v);
+        v = xor_sum<32>(v);
+        if (lane < 16) dst[f * 16 + col] = v * out_scale;
+        psum[f] = 0.f;
+      }
+    }
+  };
+  if constexpr (kAhead) {
+    uint4 keys2[NS][KB];
+    while (item < n_items) {
+      step(keys, keys2);
+      if (item >= n_items) break;
+      step(keys2, keys);
+    }
+  } else {
+    while (item < n_items) step(keys, keys);
+  }
+}
+
+// Features per workgroup (16 NF): as many as n has, up to 512 (each key is
+// read once per slice), halved while the call has too few (segment, slice)
+// items to give every SIMD two waves. A feature's sum does not depend on the
+// slice, so a segment close and a rebuild agree bit for bit.
+template <int D, int NF>
+radar_status launch_build_bf16(const Shape& s, const void* K, const void* omega,
+                               float* summ, int seg_first, int seg_count,
+                               const int64_t* pos, hipStream_t st) {
+  const int64_t items = (int64_t)s.B * s.Hkv * seg_count;
+  if constexpr (NF > 2) {
+    if (16 * NF > s.n || items * (s.n / (16 * NF)) < 8 * num_cu())
+      return launch_build_bf16<D, NF / 2>(s, K, omega, summ, seg_first, seg_count, pos, st);
+  }
+  if (items == 0) return RADAR_OK;
+  if (items >= ((int64_t)1 << 31)) return RADAR_EUNSUPPORTED;   // 32-bit item ids
+  constexpr int NW = NF >= 16 ? 8 : 4;     // 8 waves share 64 or 128 KB of Omega
+  const int slices = s.n / (16 * NF);
+  const int64_t resident = std::max<int64_t>(1, (8 / NW) * (int64_t)num_cu() / slices);
+  const int64_t gx = std::min<int64_t>(ceil_div(items, NW), resident);
+  const float s1 = kLog2e / std::pow((float)s.d, 0.25f);
+  const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
+  const float out_scale = 1.f / ((float)s.c * std::sqrt((float)s.n));
+  launch(RADAR_K_BUILD, k_build_bf16<D, NF, NW>, dim3((unsigned)gx, (unsigned)slices),
+         dim3(64 * NW), 0, st, reinterpret_cast<const bf16_t*>(K), omega, s.obf, summ, s.n, s.c,
+         s.cap, s.s_cap, seg_first, seg_count, (uint32_t)items, s1, s2, out_scale, pos, s.Hkv,
+         s.n_sink);
+  return launch_status();
+}
+
+template <int D, int FT>
+radar_status launch_build_f32(const Shape& s, const void* K, const void* omega,
+                              float* summ, int seg_first, int seg_count,
+                              const int64_t* pos, hipStream_t st) {
+  // features per workgroup = 64 * FT; FT capped so the resident Omega slice
+  // stays at 128 VGPRs or fewer
+  if constexpr (FT > 1) {
+    if (64 * FT > s.n)
+      return launch_build_f32<D, FT / 2>(s, K, omega, summ, seg_first, seg_count, pos, st);
+  }
   const int slices = s.n / (64 * FT);
   const int64_t items = (int64_t)s.B * s.Hkv * seg_count;
   if (items == 0) return RADAR_OK;
   if (items >= ((int64_t)1 << 31)) return RADAR_EUNSUPPORTED;   // 32-bit item ids
-  auto kern = k_build<T, D, FT, TL>;
+  auto kern = k_build_f32<D, FT>;
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0) != hipSuccess || per_cu < 1)
     per_cu = 1;
@@ -286,45 +489,10 @@ radar_status launch_build_tl(const Shape& s, const void* K, const void* omega,
   const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
   const float out_scale = 1.f / ((float)s.c * std::sqrt((float)s.n));
   launch(RADAR_K_BUILD, kern, dim3((unsigned)gx, (unsigned)slices), dim3(256), 0, st,
-                     reinterpret_cast<const T*>(K), omega, s.obf, summ, s.n, s.c, s.cap,
+                     reinterpret_cast<const float*>(K), static_cast<const float*>(omega), summ, s.n, s.c, s.cap,
                      s.s_cap, seg_first, seg_count, items, s1, s2, out_scale, s.cap,
                      pos, s.Hkv, s.n_sink);
   return launch_status();
-}
-
-// 128-key tiles halve the tile loop's barriers and prefetch rounds per key
-// (same sums in the same order: each lane's column sums run over the same
-// 16-key sub-tiles); for bf16 keys only (fp32 rows at d = 128 would need
-// 136 KB of LDS) and segments of at least 128 keys (shorter ones would run
-// half-empty tiles)
-template <typename T, int D, int FT>
-radar_status launch_build_t(const Shape& s, const void* K, const void* omega,
-                            float* summ, int seg_first, int seg_count,
-                            const int64_t* pos, hipStream_t st) {
-  if constexpr (sizeof(T) == 2) {
-    if (s.c >= 128)
-      return launch_build_tl<T, D, FT, 128>(s, K, omega, summ, seg_first, seg_count, pos, st);
-  }
-  return launch_build_tl<T, D, FT, 64>(s, K, omega, summ, seg_first, seg_count, pos, st);
-}
-
-template <typename T, int D>
-radar_status launch_build_d(const Shape& s, const void* K, const void* omega,
-                            float* summ, int seg_first, int seg_count,
-                            const int64_t* pos, hipStream_t st) {
-  // features per workgroup = 64 * FT; FT capped so the resident Omega slice
-  // stays at 128 VGPRs or fewer
-  constexpr int FTMAX = (D * sizeof(T) <= 256) ? 8 : 4;
-  const int ft = std::min(s.n / 64, FTMAX);
-  switch (ft) {
-    case 1: return launch_build_t<T, D, 1>(s, K, omega, summ, seg_first, seg_count, pos, st);
-    case 2: return launch_build_t<T, D, 2>(s, K, omega, summ, seg_first, seg_count, pos, st);
-    case 4: return launch_build_t<T, D, 4>(s, K, omega, summ, seg_first, seg_count, pos, st);
-    default:
-      if constexpr (FTMAX >= 8)
-        return launch_build_t<T, D, 8>(s, K, omega, summ, seg_first, seg_count, pos, st);
-      return RADAR_EUNSUPPORTED;
-  }
 }
 
 // K: the first row after the sinks (after_sinks); pos: per-sequence segment
@@ -333,9 +501,9 @@ radar_status launch_build(const Shape& s, const void* K, const void* omega,
                           float* summ, int seg_first, int seg_count,
                           const int64_t* pos, hipStream_t st) {
   if (s.dt == RADAR_BF16)
-    return s.d == 64 ? launch_build_d<bf16_t, 64>(s, K, omega, summ, seg_first, seg_count, pos, st)
-                     : launch_build_d<bf16_t, 128>(s, K, omega, summ, seg_first, seg_count, pos, st);
-  return s.d == 64 ? launch_build_d<float, 64>(s, K, omega, summ, seg_first, seg_count, pos, st)
-                   : launch_build_d<float, 128>(s, K, omega, summ, seg_first, seg_count, pos, st);
+    return s.d == 64 ? launch_build_bf16<64, 32>(s, K, omega, summ, seg_first, seg_count, pos, st)
+                     : launch_build_bf16<128, 32>(s, K, omega, summ, seg_first, seg_count, pos, st);
+  return s.d == 64 ? launch_build_f32<64, 8>(s, K, omega, summ, seg_first, seg_count, pos, st)
+                   : launch_build_f32<128, 4>(s, K, omega, summ, seg_first, seg_count, pos, st);
 }
 }  // namespace radar_impl

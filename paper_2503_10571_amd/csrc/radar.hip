@@ -1,7 +1,8 @@
 // Radar decode path on MI355X (gfx950, CDNA4): host logic and the C ABI.
 //
 // Kernels (all on the caller's stream):
-//   k_build        segment summaries, Eq. 4 + Eq. 5: bf16/fp32 matrix-core
+//   k_build_bf16, k_build_f32
+//                  segment summaries, Eq. 4 + Eq. 5: bf16/fp32 matrix-core
 //                  projection of the keys onto Omega, exp2 epilogue, mean
 //                  over the segment's tokens. Also serves the segment close
 //                  of an append, so appends and rebuilds agree bit for bit.
@@ -38,7 +39,7 @@
 // scale factors: exp(x) = exp2(x * log2(e)).
 //
 // Units: this file (host logic, C ABI, k_append, the measurement
-// microkernels and the no-alloc scratch), build.hip (k_build), split.hip
+// microkernels and the no-alloc scratch), build.hip (the index build), split.hip
 // (the split path's kernels and k_combine), fused.hip (k_decode_fused, one
 // unit per feature count), radar_impl.h (what they share).
 

@@ -23,7 +23,7 @@ namespace radar_impl {
 
 constexpr float kLog2e = 1.44269504088896340736f;
 constexpr int kWave = 64;
-constexpr int kTile = 64;          // tokens per wave in k_attend / k_build
+constexpr int kTile = 64;          // tokens per attention tile and per key tile of k_build_f32
 constexpr int kMaxK = 256;         // largest k accepted
 constexpr int kMaxG = 8;           // largest query-head group
 constexpr int kMaxCand = 2048;     // largest number of candidate segments
@@ -183,20 +183,9 @@ __device__ __forceinline__ float4 ld_stream_f4(const float* p) {
 }
 
 // Omega is fp32 [n][d], or bf16 [n][d] for bf16 caches (whose projection
-// rounds Omega to bf16 anyway, so both give the same products); four
-// consecutive entries from element idx, widened to fp32 (exact for bf16).
-// fp32 caches always pass fp32 Omega.
-template <bool BF>
-__device__ __forceinline__ float4 load_omega4(const void* omega, int64_t idx) {
-  if constexpr (BF) {
-    const uint2 u = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(omega) + idx);
-    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                       __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
-  } else {
-    return *reinterpret_cast<const float4*>(static_cast<const float*>(omega) + idx);
-  }
-}
-
+// rounds Omega to bf16 anyway, so both give the same products); fp32 caches
+// always pass fp32 Omega.
+//
 // NR rows of QPL Omega entries (row_idx(p): element index of row p's first
 // entry), stored as bf16 (BF) or fp32, all loads issued together and kept
 // as raw words (fp32: four floats; bf16: four values in .x and .y);
