@@ -291,7 +291,9 @@ radar_status radar_schedule_sqrt(int64_t t, int32_t* seg_len, int32_t* window);
  * chip or a step is small; with R > 1 a merge kernel follows); the select
  * path runs phi(q), scores, top-k and union of each pair in one workgroup
  * and then the split path's attention and merge. All compute the same
- * method; their fp32 summation orders differ. */
+ * method; their fp32 summation orders differ. Left to its own choice the
+ * library runs the split path of a group of eight on a bf16 cache from its
+ * top-k on as the scored path does; a forced split path keeps its kernels. */
 typedef enum {
   RADAR_PATH_AUTO = 0,   /* fused when the shape fits and either B * Hkv >=
                             #CUs, one pair's step reads <= 256 KB, or a

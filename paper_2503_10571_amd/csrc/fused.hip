@@ -60,29 +60,34 @@ __global__ __launch_bounds__(512) void k_decode_fused(
   constexpr int NW = kFusedWaves;
   constexpr int QPL = D / 16;              // q elements per lane (phase 1)
   constexpr int FPL = N / 64;              // features per lane (phase 2)
-  using TA = TileAttn<T, D, G>;
-  constexpr int EPL = TA::EPL, LPR = TA::LPR;
-  constexpr int SEL_FLOATS = SCORED ? 0 : G * N + G * kFusedMaxCand;
-  constexpr int MRG_FLOATS = NW * G * D;
-  constexpr int AREA = SEL_FLOATS > MRG_FLOATS ? SEL_FLOATS : MRG_FLOATS;
-  static_assert(G <= kFusedMaxG, "group");
+  using TA = Tile<T, D, G>;
+  // One LDS area serves the phases in turn: phi(q), the scores and the top-k
+  // lists (dead after the top-k), the K rows of the waves' tiles, and the
+  // waves' accumulators at the end. The waves that attend window tiles
+  // beside the top-k are those >= G: their K rows lie past the first part
+  // (at d = 64 with many features all K rows follow it).
+  constexpr int SEL_BYTES = (SCORED ? 0 : G * (N + kFusedMaxCand) * 4) + G * kMaxK * 8;
+  constexpr int MRG_BYTES = NW * G * D * 4;
+  constexpr int KROWS = SEL ? 0 : NW * TA::kLdsBytes;
+  constexpr int KOFF = SEL_BYTES <= G * TA::kLdsBytes ? 0 : SEL_BYTES;
+  constexpr int AREA = std::max({SEL_BYTES, SEL ? 0 : MRG_BYTES, KOFF + KROWS});
+  static_assert(G <= (SCORED ? kScoredMaxG : kFusedMaxG), "group");
   static_assert(N % (4 * NW) == 0, "features");
 
-  // phi(q) and the scores live only until the top-k; the merge reuses them
-  __shared__ __attribute__((aligned(16))) float area[AREA];
+  __shared__ __attribute__((aligned(16))) unsigned char area[AREA];
   __shared__ int sel_lds[G * kMaxK];
   __shared__ unsigned bits_lds[G * kBitmapWords];
   __shared__ int uni_lds[G * kMaxK];
-  __shared__ u64 list_lds[G][kMaxK];
   __shared__ float wm[NW][G], wl[NW][G];
   __shared__ int ucnt_lds;
-  float* phq = area;                       // [G][N]
-  float* sc = area + G * N;                // [G][kFusedMaxCand]
-  float* wacc = area;                      // [NW][G][D]
+  u64* list_lds = reinterpret_cast<u64*>(area);          // [G][kMaxK]
+  float* phq = reinterpret_cast<float*>(area + G * kMaxK * 8);   // [G][N]
+  float* sc = phq + G * N;                               // [G][kFusedMaxCand]
+  float* wacc = reinterpret_cast<float*>(area);          // [NW][G][D]
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // measurement hook: the first thread stamps the phase boundaries (every
   // stamp starts as the entry time: phases 1-2 when they do not run keep it;
   // later stamps are written on every path)
@@ -100,9 +105,13 @@ __global__ __launch_bounds__(512) void k_decode_fused(
   // multiple of n_pairs, so they share an XCD (and its L2) when n_pairs is a
   // multiple of 8 (dealing a pair's workgroups over all XCDs instead measured
   // 2% slower on the scored path at 512K)
-  const int64_t bh = blockIdx.x % n_pairs;
-  const int rj = (int)(blockIdx.x / n_pairs);
-  const int64_t b = bh / Hkv, hk = bh % Hkv;
+  // (the divisions run on the vector unit: readfirstlane keeps what follows
+  // from them, loop counters and addresses, in scalar registers)
+  const int rj = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)n_pairs));
+  const int pair = (int)blockIdx.x - rj * n_pairs;
+  const int64_t bh = pair;
+  const int64_t b = __builtin_amdgcn_readfirstlane(pair / Hkv);
+  const int64_t hk = pair - b * Hkv;
   const T* q0 = q + (b * Hq + hk * G) * D;
   const Span sp = seq_span(sa, b);
   const int c = sa.c, k = sa.k, n_cand = sp.n_cand, k_eff = sp.k_eff;
@@ -341,10 +350,28 @@ __global__ __launch_bounds__(512) void k_decode_fused(
   }
 
   // ---- 3. top-k (waves < G) | window and sink tiles (the other waves) ----
+  // (a group of eight has no wave to spare: its window tiles come with the
+  // segments' in phase 5)
+  constexpr bool kBeside = G < NW;
   TA ta;
   if constexpr (!SEL) ta.init(q0, qscale, lane);
+  unsigned char* const krows = area + KOFF + wave * TA::kLdsBytes;
   const int win_tiles = (int)((t - ws + kTile - 1) / kTile);
   const int extra_tiles = win_tiles + (sp.sink + kTile - 1) / kTile;
+  auto extra_tile = [&](int i) {
+    TileRef r;
+    r.hmask = kAllHeads;
+    if (i < win_tiles) {
+      const int64_t start = ws + (int64_t)i * kTile;
+      r.row0 = bh * cap + start;
+      r.len = (int)min((int64_t)kTile, t - start);
+    } else {
+      const int off = (i - win_tiles) * kTile;
+      r.row0 = bh * cap + off - sa.n_sink;
+      r.len = min(kTile, sp.sink - off);
+    }
+    return r;
+  };
   if (wave < G) {
     const int64_t hq = hk * G + wave;
     // every workgroup of the pair selects the same segments; the first
@@ -354,7 +381,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     const float* src = SCORED ? gscores + (b * Hq + hq) * (int64_t)nc_cap
                               : sc + wave * kFusedMaxCand;
     int* row = sel_lds + wave * k_eff;
-    u64* list = list_lds[wave];
+    u64* list = list_lds + wave * kMaxK;
     const int npl = (n_cand + 63) / 64;
     if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list);
     else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list);
@@ -365,19 +392,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     else if constexpr (SCORED)             // up to 2048 candidates
       head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list);
   } else if constexpr (!SEL) {
-    for (int i = rj + (wave - G) * R; i < extra_tiles; i += (NW - G) * R) {
-      int64_t start;
-      int len;
-      if (i < win_tiles) {
-        start = ws + (int64_t)i * kTile;
-        len = (int)min((int64_t)kTile, t - start);
-      } else {
-        const int off = (i - win_tiles) * kTile;
-        start = (int64_t)off - sa.n_sink;
-        len = min(kTile, sp.sink - off);
-      }
-      ta.tile(K, V, bh * cap + start, len, lane, kAllHeads);
-    }
+    ta.run(K, V, rj + (wave - G) * R, extra_tiles, (NW - G) * R, krows, extra_tile);
   }
   __syncthreads();
   stamp(3);
@@ -409,31 +424,20 @@ __global__ __launch_bounds__(512) void k_decode_fused(
   // rows instead, cut at segment ends, measured slower: the shares start
   // mid-tile, so waves run more partial tiles, each costing nearly a whole
   // one)
-  for (int i = rj + wave * R; i < seg_tiles; i += NW * R) {
+  ta.run(K, V, rj + wave * R, seg_tiles + (kBeside ? 0 : extra_tiles), NW * R, krows, [&](int i) {
+    if (!kBeside && i >= seg_tiles) return extra_tile(i - seg_tiles);
     const int e = segs[i / tiles_per_seg];
     const int s = e & ((1 << kUniIdBits) - 1);
-    // (the plain selection of a one-head group carries no head mask)
-    const unsigned hm = (G > 1 && per_head) ? (unsigned)e >> kUniIdBits : kAllHeads;
     const int off = (i % tiles_per_seg) * kTile;
-    ta.tile(K, V, bh * cap + (int64_t)s * c + off, min(kTile, c - off), lane, hm);
-  }
+    // (the plain selection of a one-head group carries no head mask)
+    return TileRef{bh * cap + (int64_t)s * c + off, min(kTile, c - off),
+                   (G > 1 && per_head) ? (unsigned)e >> kUniIdBits : kAllHeads};
+  });
 
   // ---- 6. merge -----------------------------------------------------------
-  ta.reduce_rows();
-  __syncthreads();                         // phq / sc are dead from here on
+  __syncthreads();                         // the K rows are dead from here on
   stamp(5);
-  const int jj = lane % LPR;
-  if (lane < LPR) {
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int e = 0; e < EPL; ++e)
-        wacc[(wave * G + g) * D + jj * EPL + e] = ta.acc[g][e];
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) { wm[wave][g] = ta.m[g]; wl[wave][g] = ta.l[g]; }
-  }
+  ta.finish(wacc + wave * G * D, wm[wave], wl[wave]);
   __syncthreads();
   for (int x = tid; x < G * D; x += NW * 64) {
     const int g = x / D, e = x % D;
@@ -493,7 +497,11 @@ radar_status launch_fused_td(const FusedArgs& a) {
   switch (a.s->G) {
     case 1: return launch_fused_tdg<T, D, 1, MODE>(a);
     case 2: return launch_fused_tdg<T, D, 2, MODE>(a);
-    default: return launch_fused_tdg<T, D, 4, MODE>(a);
+    case 4: return launch_fused_tdg<T, D, 4, MODE>(a);
+    default:
+      if constexpr (MODE == kFusedScored && sizeof(T) == 2)
+        return launch_fused_tdg<T, D, 8, MODE>(a);
+      return RADAR_EUNSUPPORTED;
   }
 }
 

@@ -375,6 +375,8 @@ struct DecodePlan {
   int path;
   AttendGrid ag;
   int R;               // fused kernel: workgroups per pair
+  bool tail;           // top-k, union and attention in the fused kernel's
+                       // scored mode (the scored path; see plan_decode)
 };
 
 #ifndef RADAR_FUSED_WAYS_MAX
@@ -397,10 +399,16 @@ radar_status plan_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
   p->path = choose_path(s, sa);
   p->ag = AttendGrid{0, 1};
   p->R = 1;
-  if (p->path == RADAR_PATH_FUSED || p->path == RADAR_PATH_SCORED) {
-    p->R = fused_ways(s, L, sa);
-    return RADAR_OK;
-  }
+  // The split path, chosen by the library for a group of eight on a bf16
+  // cache, runs its last stages as the scored path does: one launch instead
+  // of top-k and attention, and the attention of R workgroups per pair
+  // (measured 110 against 117 us for six ragged sequences of 32K tokens).
+  // Forced, it keeps its own kernels.
+  p->tail = p->path == RADAR_PATH_SCORED ||
+            (p->path == RADAR_PATH_SPLIT && g_path_override == RADAR_PATH_AUTO &&
+             s.dt == RADAR_BF16);
+  if (p->path == RADAR_PATH_FUSED || p->tail) p->R = fused_ways(s, L, sa);
+  if (p->path == RADAR_PATH_FUSED || p->path == RADAR_PATH_SCORED) return RADAR_OK;
   const int u_bound = std::min(s.G * top.k_eff, top.n_cand);
   p->ag = attend_grid(s, L, u_bound, extra_tiles(s, sa));
   return p->ag.grid_x > kMaxWg ? RADAR_EUNSUPPORTED : RADAR_OK;
@@ -432,7 +440,7 @@ radar_status run_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
     launch_phi_q_any(s, q, omega, phiq, stream);
     launch_score(s, phiq, summaries, sc, top.n_cand, sa, stream);
   }
-  if (plan.path == RADAR_PATH_SCORED) {
+  if (plan.tail) {
     float* part = plan.R > 1 ? reinterpret_cast<float*>(w + L.part) : nullptr;
     const FusedArgs a{&s, q, Kp, Vp, omega, summaries, sa, out, selected, scores,
                       nullptr, nullptr, 0, ap, plan.R, part, L.maxwg, stream, sc,

@@ -231,6 +231,7 @@ constexpr int kDppQuadSwap2 = 0x4E;
 constexpr int kDppHalfMirror = 0x141;
 constexpr int kDppMirror = 0x140;
 constexpr int kDppRowBcast0 = 0x150;
+constexpr int kDppRowRor0 = 0x120;         // + n: lane i of a row takes lane i - n mod 16
 
 // compile-time loop: f(std::integral_constant<int, I>) for I = B .. E-1
 template <int B, int E, typename F>
@@ -604,86 +605,64 @@ __device__ inline void group_union(const int* sel, unsigned* bits, int G, int pe
 // exact attention over <= 64-token tiles (shared by k_attend and k_decode_fused)
 // ---------------------------------------------------------------------------
 // The attended tokens of a (b, kv head) are cut into tiles of <= 64 tokens
-// that never cross a segment or the window boundary. A wave processes one
-// tile at a time: lane (r, jj) (r = lane / LPR) reads the 16-byte chunk jj of
-// rows r, r + RPI, ... so every load instruction covers RPI whole rows
-// contiguously (rows past the tile end re-read its last row and are masked).
-// q.k partials (bf16: v_dot2_f32_bf16 on the raw pairs, the scale applied to
-// the sums; fp32: fma of the pre-scaled query) are transpose-reduced so that
-// each lane ends with one token's logit, softmax runs across the wave, and p is broadcast back (DPP row
-// broadcast) to the lanes that hold the matching V chunks. The state carries
-// across tiles as an online softmax: running max m and sum l (log2 units,
-// wave-uniform) and unreduced per-lane accumulators.
-//
-// (q.k on the matrix cores was measured slower here: the MFMA operand layout
-// gives each 16-lane quarter of a load instruction one 16-byte chunk of 16
-// different rows; that made one-head groups slower and groups of four no
-// faster.)
-template <typename T, int D, int G>
-struct TileAttn {
-  static constexpr int EPL = Elem<T>::kPer16;   // elements per 16-byte chunk
+// that never cross a segment or the window boundary; a wave attends one tile
+// after another with an online softmax (running max m and sum l in log2
+// units, unreduced accumulators). TileMfma serves bf16 caches, TileVec fp32
+// ones; run() walks a wave's tiles, finish() leaves its state in LDS.
+struct TileRef {
+  int64_t row0;     // first row of the tile, counted from the base pointers
+  int len;          // 1 .. 64 rows
+  unsigned hmask;   // head g of the group takes part only if bit g is set
+};
+
+// fp32 caches, on the vector ALUs: lane (r, jj) (r = lane / LPR) reads the
+// 16-byte chunk jj of rows r, r + RPI, ... so every load instruction covers
+// RPI whole rows contiguously (rows past the tile end re-read its last row
+// and are masked). q.k partials (fma of the pre-scaled query) are
+// transpose-reduced so that each lane ends with one token's logit, softmax
+// runs across the wave, and p is broadcast back to the lanes that hold the
+// matching V chunks.
+template <int D, int G>
+struct TileVec {
+  static constexpr int kLdsBytes = 0;           // per wave
+  static constexpr int EPL = 4;                 // elements per 16-byte chunk
   static constexpr int LPR = D / EPL;           // lanes per row
   static constexpr int RPI = kWave / LPR;       // rows per load instruction
   static constexpr int ITER = kTile / RPI;      // load instructions per tile
   static_assert(ITER == LPR, "tile shape");
 
-  // bf16: the raw query pairs (dot2 operands) and the scale applied to
-  // the sums; fp32: the queries times the scale
-  static constexpr bool BF = sizeof(T) == 2;
-  float qf[BF ? 1 : G][EPL];
-  uint32_t q2[BF ? G : 1][EPL / 2];
-  float qs;
+  float qf[G][EPL];
   float m[G], l[G], acc[G][EPL];
+  int lane;
 
   // q0: the group's first query head; qscale folds log2(e) / sqrt(d)
-  __device__ __forceinline__ void init(const T* __restrict__ q0, float qscale,
-                                       int lane) {
+  __device__ __forceinline__ void init(const float* __restrict__ q0, float qscale, int ln) {
+    lane = ln;
     const int jj = lane % LPR;
-    qs = qscale;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const uint4 u = *reinterpret_cast<const uint4*>(q0 + g * D + jj * EPL);
-      if constexpr (BF) {
-        q2[g][0] = u.x; q2[g][1] = u.y; q2[g][2] = u.z; q2[g][3] = u.w;
-      } else {
-        unpack16<T>(u, qf[g]);
+      unpack16<float>(*reinterpret_cast<const uint4*>(q0 + g * D + jj * EPL), qf[g]);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) qf[g][e] *= qscale;
-      }
+      for (int e = 0; e < EPL; ++e) { qf[g][e] *= qscale; acc[g][e] = 0.f; }
       m[g] = -INFINITY;
       l[g] = 0.f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
     }
   }
 
-  // rows [row0, row0 + len) of K and V (row0 counts rows from the base
-  // pointers); 1 <= len <= 64; wave-uniform call. Head g of the group takes
-  // part only if bit g of hmask is set (a head that has attended nothing
-  // yet keeps m = -inf, l = 0, acc = 0).
-  __device__ __forceinline__ void tile(const T* __restrict__ K,
-                                       const T* __restrict__ V, int64_t row0,
-                                       int len, int lane, unsigned hmask) {
+  // (a head that has attended nothing yet keeps m = -inf, l = 0, acc = 0)
+  __device__ __forceinline__ void tile(const float* __restrict__ K, const float* __restrict__ V,
+                                       const TileRef& t) {
     const int r = lane / LPR;
     const int jj = lane % LPR;
     uint4 kr[ITER], vr[ITER];
-    if (BF && len == kTile) {              // uniform: no row to clamp
-      const T* kbase = K + (row0 + r) * D + jj * EPL;
-      const T* vbase = V + (row0 + r) * D + jj * EPL;
+    const float* kbase = K + t.row0 * D + jj * EPL;
+    const float* vbase = V + t.row0 * D + jj * EPL;
 #pragma unroll
-      for (int i = 0; i < ITER; ++i) kr[i] = ld_stream(kbase + i * RPI * D);
+    for (int i = 0; i < ITER; ++i)
+      kr[i] = ld_stream(kbase + (int64_t)min(i * RPI + r, t.len - 1) * D);
 #pragma unroll
-      for (int i = 0; i < ITER; ++i) vr[i] = ld_stream(vbase + i * RPI * D);
-    } else {
-      const T* kbase = K + row0 * D + jj * EPL;
-      const T* vbase = V + row0 * D + jj * EPL;
-#pragma unroll
-      for (int i = 0; i < ITER; ++i)
-        kr[i] = ld_stream(kbase + (int64_t)min(i * RPI + r, len - 1) * D);
-#pragma unroll
-      for (int i = 0; i < ITER; ++i)
-        vr[i] = ld_stream(vbase + (int64_t)min(i * RPI + r, len - 1) * D);
-    }
+    for (int i = 0; i < ITER; ++i)
+      vr[i] = ld_stream(vbase + (int64_t)min(i * RPI + r, t.len - 1) * D);
 
     // logits: lane (r, jj) ends with the logit of tile row jj * RPI + r
     float lg[G];
@@ -691,42 +670,27 @@ struct TileAttn {
       float pl[G][ITER];
 #pragma unroll
       for (int i = 0; i < ITER; ++i) {
-        if constexpr (BF) {
-          // bf16 pairs: exact products, fp32 sums
-          const uint32_t kw[4] = {kr[i].x, kr[i].y, kr[i].z, kr[i].w};
+        float kf[EPL];
+        unpack16<float>(kr[i], kf);
 #pragma unroll
-          for (int g = 0; g < G; ++g) {
-            float a = 0.f;
+        for (int g = 0; g < G; ++g) {
+          float a = 0.f;
 #pragma unroll
-            for (int w = 0; w < 4; ++w)
-              a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v_t, q2[g][w]),
-                                                  __builtin_bit_cast(bf16x2v_t, kw[w]), a,
-                                                  false);
-            pl[g][i] = a;
-          }
-        } else {
-          float kf[EPL];
-          unpack16<T>(kr[i], kf);
-#pragma unroll
-          for (int g = 0; g < G; ++g) {
-            float a = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) a = fmaf(qf[g][e], kf[e], a);
-            pl[g][i] = a;
-          }
+          for (int e = 0; e < EPL; ++e) a = fmaf(qf[g][e], kf[e], a);
+          pl[g][i] = a;
         }
       }
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         transpose_reduce<LPR>(pl[g], lane);
-        lg[g] = BF ? pl[g][0] * qs : pl[g][0];
+        lg[g] = pl[g][0];
       }
     }
-    const bool mine_ok = (jj * RPI + r) < len;
+    const bool mine_ok = (jj * RPI + r) < t.len;
     float p[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const bool on = mine_ok && ((hmask >> g) & 1u);
+      const bool on = mine_ok && ((t.hmask >> g) & 1u);
       const float mt = wave_max(on ? lg[g] : -INFINITY);
       const float mn = fmaxf(m[g], mt);
       const float mref = mn == -INFINITY ? 0.f : mn;
@@ -740,7 +704,7 @@ struct TileAttn {
     static_for<0, ITER>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
       float vf[EPL];
-      unpack16<T>(vr[i], vf);
+      unpack16<float>(vr[i], vf);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         // p of row (i, r) lives in lane i of this lane's LPR-lane group
@@ -755,9 +719,16 @@ struct TileAttn {
     });
   }
 
-  // sum the accumulators over the RPI row groups: lanes r = 0 (lane < LPR)
-  // then hold dims jj*EPL .. jj*EPL + EPL - 1 of the wave's total
-  __device__ __forceinline__ void reduce_rows() {
+  // tiles first, first + step, ... < end of at(i); wave-uniform call
+  template <typename At>
+  __device__ __forceinline__ void run(const float* K, const float* V, int first, int end, int step,
+                                      unsigned char*, At&& at) {
+    for (int i = first; i < end; i += step) tile(K, V, at(i));
+  }
+
+  // the wave's totals: acc of head g, dim e to wacc[g * D + e], its maximum
+  // and sum to wm[g] and wl[g]
+  __device__ __forceinline__ void finish(float* wacc, float* wm, float* wl) {
     static_for<0, 6>([&](auto bc) {
       constexpr int msk = 1 << decltype(bc)::value;
       if constexpr (msk >= LPR) {
@@ -770,8 +741,296 @@ struct TileAttn {
           }
       }
     });
+    if (lane < LPR) {
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) wacc[g * D + lane * EPL + e] = acc[g][e];
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) { wm[g] = m[g]; wl[g] = l[g]; }
+    }
   }
 };
+
+// bf16 caches, on the matrix cores. Both products are 16x16x32 MFMAs whose 16
+// columns are query heads, so their cost does not depend on the group:
+//   S[token][head] = K Q^T    A = 16 keys, B = the group's queries
+//   O^T[dim][head] += V^T P^T A = 16 dims, B = p of 32 tokens
+// K goes from memory to the wave's own 16 KB (d = 128) of LDS by direct loads
+// of whole rows, 16-byte chunk c of row x at place c ^ swz(x), which makes the
+// A-operand reads free of bank conflicts. (Loading K straight into A-operand
+// registers instead touches 16 cache lines per quarter wave: 5.9 against 6.9
+// TB/s for whole rows, by registers or by LDS alike.) V goes to registers in
+// whole rows too, lane (r, jj) holding chunk jj of tokens 4 i + r: for each
+// element e of the chunk those are one row (dim EV jj + e) of V^T at the
+// k-slots of lane group r, so two-register byte permutes make the operand
+// and no value crosses lanes. The rows of S are assigned to tokens so that
+// the logits a lane ends up with are exactly its k-slots of P^T: a lane's
+// row 4 grp + j of sub-tile st is token 16 st + 4 j + grp.
+//
+// p stays exact: its 24 bits are cut into three bf16 terms (truncations, the
+// last remainder is exact) and the unused columns take them. Up to four heads
+// the 16 columns hold the head's term 0, 1 and 2 at col, col + G and
+// col + 2 G and one product does all three; with eight heads the columns hold
+// terms 0 and 1 and a second product adds term 2. The terms' sums are added
+// at the end. A term is never 0 where p is not (an infinite V times a zero
+// term would be NaN where p V is infinite).
+//
+// The next tile's K is requested as soon as the logits are out of LDS and its
+// V as soon as this tile's V is used, so a wave has loads in flight while it
+// computes.
+//
+// Against one dot2 and fma chain per head on the vector ALUs (the tile before
+// this one, 1570 vector instructions at four heads and twice that at eight,
+// with K in registers and nothing in flight during them): 167 against 183 us
+// for 16 sequences of 64K tokens with four heads per group, 80 against 90 us
+// at 512K, 104 against 211 us for six sequences of 32K with eight heads
+// (485 MB); 109 us either way at 128K with one head, which streams at the
+// read rate.
+template <int D, int G>
+struct TileMfma {
+  static constexpr int KB = D / 32;             // MFMA steps of q.k
+  static constexpr int EV = D / 16;             // V elements per lane and row
+  static constexpr int CPR = D / 8;             // 16-byte chunks per row
+  static constexpr int RPI = kWave / CPR;       // rows per K load
+  static constexpr int NS = kTile / 16;         // 16-token sub-tiles
+  static constexpr int NV = kTile / 4;          // V loads per tile
+  static constexpr int kLdsBytes = kTile * D * 2;   // per wave
+  static constexpr int kTerms = G <= 4 ? 3 : 2; // terms of p in the columns
+  typedef typename std::conditional<EV == 8, uint4, uint2>::type VRow;
+
+  bf16x8_t qb[KB];
+  f32x4_t acc[EV];
+  float m, l, qs;
+  uint32_t cut0, cut1;      // masks that cut the lane's term out of p
+  int lane;
+
+  __device__ static __forceinline__ int swz(int row) {
+    return D == 128 ? row & 15 : (row >> 1) & 7;
+  }
+
+  __device__ __forceinline__ void init(const bf16_t* __restrict__ q0, float qscale, int ln) {
+    lane = ln;
+    qs = qscale;
+    const int col = lane & 15, grp = lane >> 4;
+    const int term = col / G;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+      qb[kb] = *reinterpret_cast<const bf16x8_t*>(q0 + (col % G) * D + kb * 32 + grp * 8);
+#pragma unroll
+    for (int e = 0; e < EV; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    m = -INFINITY;
+    l = 0.f;
+    cut0 = term >= 1 ? 0xffff0000u : 0u;
+    cut1 = term >= 2 ? 0xffff0000u : 0u;
+  }
+
+  // K rows of a tile -> LDS (rows past the end re-read the last one)
+  __device__ __forceinline__ void load_k(const bf16_t* __restrict__ K, const TileRef& t,
+                                         unsigned char* lds) {
+    const bf16_t* base = K + t.row0 * D;
+    const int r = lane / CPR, jj = lane % CPR;
+#pragma unroll
+    for (int i = 0; i < kTile / RPI; ++i) {
+      const int row = i * RPI + r;
+      const bf16_t* src = base + min(row, t.len - 1) * D + (jj ^ swz(row)) * 8;
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)src,
+          (__attribute__((address_space(3))) void*)(lds + i * 1024), 16, 0, 2 /* nt */);
+    }
+  }
+
+  __device__ __forceinline__ void load_v(const bf16_t* __restrict__ V, const TileRef& t,
+                                         VRow (&vr)[NV]) {
+    const bf16_t* base = V + t.row0 * D + (lane & 15) * EV;
+    const int r = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const bf16_t* src = base + min(4 * i + r, t.len - 1) * D;
+      if constexpr (EV == 8) {
+        vr[i] = ld_stream(src);
+      } else {
+        typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+        const u32x2_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(src));
+        vr[i] = make_uint2(v.x, v.y);
+      }
+    }
+  }
+
+  // logits of the tile in LDS: s[st][j] is token 16 st + 4 j + grp, head col % G
+  __device__ __forceinline__ void logits(const unsigned char* lds, f32x4_t (&s)[NS]) {
+    const int row0 = 4 * (lane & 3) + ((lane & 15) >> 2), grp = lane >> 4;
+#pragma unroll
+    for (int st = 0; st < NS; ++st) s[st] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int st = 0; st < NS; ++st) {
+        const int row = 16 * st + row0;
+        const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(
+            lds + row * (D * 2) + (((kb * 4 + grp) ^ swz(row)) * 16));
+        s[st] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qb[kb], s[st], 0, 0, 0);
+      }
+  }
+
+  // mask, online softmax; s becomes p
+  __device__ __forceinline__ void softmax(const TileRef& t, f32x4_t (&s)[NS]) {
+    const int grp = lane >> 4;
+    if (t.len < kTile) {                   // uniform
+#pragma unroll
+      for (int st = 0; st < NS; ++st)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          s[st][j] = 16 * st + 4 * j + grp < t.len ? s[st][j] : -INFINITY;
+    }
+    if (G > 1 && (t.hmask & ((1u << G) - 1u)) != ((1u << G) - 1u)) {   // uniform
+      const bool on = (t.hmask >> ((lane & 15) % G)) & 1u;
+#pragma unroll
+      for (int st = 0; st < NS; ++st)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[st][j] = on ? s[st][j] : -INFINITY;
+    }
+    float mt = -INFINITY;
+#pragma unroll
+    for (int st = 0; st < NS; ++st)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) mt = fmaxf(mt, s[st][j]);
+    float lo, hi;
+    xor_pair<16>(mt, lo, hi);
+    mt = fmaxf(lo, hi);
+    xor_pair<32>(mt, lo, hi);
+    mt = fmaxf(lo, hi) * qs;
+    const float mn = fmaxf(m, mt);
+    const float mref = mn == -INFINITY ? 0.f : mn;
+    if (__ballot(mn != m)) {               // some head's maximum grew
+      const float scale = fast_exp2(m - mref);   // 0 on the head's first tile
+      l *= scale;
+#pragma unroll
+      for (int e = 0; e < EV; ++e)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[e][j] *= scale;
+      m = mn;
+    }
+    float sum = 0.f;                       // of this lane's 16 tokens
+#pragma unroll
+    for (int st = 0; st < NS; ++st)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        s[st][j] = fast_exp2(fmaf(s[st][j], qs, -mref));
+        sum += s[st][j];
+      }
+    l += sum;
+  }
+
+  // acc += V^T P^T
+  __device__ __forceinline__ void pv(const VRow (&vr)[NV], const f32x4_t (&p)[NS]) {
+    constexpr float kTiny = 1.17549435e-38f;     // smallest normal number
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {          // 32 tokens each
+      uint32_t w[4], w2[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t x[2], y[2];
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+          const float pz = p[2 * h + i / 2][2 * (i & 1) + z];
+          float t = pz - __uint_as_float(__float_as_uint(pz) & cut0);
+          if constexpr (kTerms == 3) t -= __uint_as_float(__float_as_uint(t) & cut1);
+          x[z] = __float_as_uint(__builtin_amdgcn_fmed3f(t, pz, kTiny));
+          if constexpr (kTerms == 2) {     // term 2, in the first G columns
+            float u = pz - __uint_as_float(__float_as_uint(pz) & 0xffff0000u);
+            u -= __uint_as_float(__float_as_uint(u) & 0xffff0000u);
+            y[z] = __float_as_uint(__builtin_amdgcn_fmed3f(cut0 ? 0.f : u, pz, kTiny));
+          }
+        }
+        // upper halves of two words: a truncated bf16 pair
+        w[i] = __builtin_amdgcn_perm(x[1], x[0], 0x07060302u);
+        if constexpr (kTerms == 2) w2[i] = __builtin_amdgcn_perm(y[1], y[0], 0x07060302u);
+      }
+      const uint4 b = make_uint4(w[0], w[1], w[2], w[3]);
+#pragma unroll
+      for (int e = 0; e < EV; ++e) {
+        uint32_t a[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          a[i] = __builtin_amdgcn_perm(word(vr[8 * h + 2 * i + 1], e / 2),
+                                       word(vr[8 * h + 2 * i], e / 2),
+                                       (e & 1) ? 0x07060302u : 0x05040100u);
+        const bf16x8_t av = __builtin_bit_cast(bf16x8_t, make_uint4(a[0], a[1], a[2], a[3]));
+        acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8_t, b),
+                                                         acc[e], 0, 0, 0);
+        if constexpr (kTerms == 2)
+          acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              av, __builtin_bit_cast(bf16x8_t, make_uint4(w2[0], w2[1], w2[2], w2[3])), acc[e], 0,
+              0, 0);
+      }
+    }
+  }
+  __device__ static __forceinline__ uint32_t word(const uint4& v, int i) {
+    return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
+  }
+  __device__ static __forceinline__ uint32_t word(const uint2& v, int i) {
+    return i == 0 ? v.x : v.y;
+  }
+
+  // tiles first, first + step, ... < end of at(i); wave-uniform call; lds:
+  // the wave's own kLdsBytes
+  template <typename At>
+  __device__ __forceinline__ void run(const bf16_t* K, const bf16_t* V, int first, int end,
+                                      int step, unsigned char* lds, At&& at) {
+    if (first >= end) return;
+    VRow vr[NV];
+    TileRef t = at(first);
+    load_k(K, t, lds);
+    load_v(V, t, vr);
+    for (int i = first;; i += step) {
+      const bool more = i + step < end;
+      TileRef nt{};
+      if (more) nt = at(i + step);
+      f32x4_t s[NS];
+      logits(lds, s);
+      // the logits' reads of LDS are over before the next rows may land there
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) load_k(K, nt, lds);
+      softmax(t, s);
+      pv(vr, s);
+      if (!more) break;
+      load_v(V, nt, vr);
+      t = nt;
+    }
+  }
+
+  // the wave's totals (see TileVec::finish)
+  __device__ __forceinline__ void finish(float* wacc, float* wm, float* wl) {
+    const int col = lane & 15, grp = lane >> 4;
+    l = xor_sum<16>(l);
+    l = xor_sum<32>(l);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e0 = 0; e0 < EV; e0 += 4) {
+        float a[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          // the lane of term 1 is G lanes up in the row, of term 2 another G
+          const float v = acc[e0 + e][j];
+          a[e] = v + dpp_f<kDppRowRor0 + 16 - G>(v);
+          if constexpr (kTerms == 3) a[e] += dpp_f<kDppRowRor0 + 16 - 2 * G>(v);
+        }
+        if (col < G)
+          *reinterpret_cast<float4*>(&wacc[col * D + EV * (4 * grp + j) + e0]) =
+              make_float4(a[0], a[1], a[2], a[3]);
+      }
+    if (grp == 0 && col < G) { wm[col] = m; wl[col] = l; }
+  }
+};
+
+template <typename T, int D, int G>
+using Tile = typename std::conditional<sizeof(T) == 2, TileMfma<D, G>, TileVec<D, G>>::type;
 
 // decode path shared by the fused kernel and its select-only instantiation
 // k_decode_fused modes: the whole step; the selection only (select path);
@@ -781,6 +1040,7 @@ constexpr int kFusedSelect = 1;
 constexpr int kFusedScored = 2;
 constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxG = 4;
+constexpr int kScoredMaxG = 8;     // bf16 caches (4 for fp32 ones)
 constexpr int kFusedMaxCand = 1024;
 
 // ---------------------------------------------------------------------------

@@ -406,16 +406,19 @@ __global__ __launch_bounds__(256) void k_attend(
     float* __restrict__ part, int Hq, int Hkv, int64_t cap,
     int tiles_per_seg, SeqArgs sa, int per_head, int umax, int maxwg, int tpw,
     float qscale) {
-  using TA = TileAttn<T, D, G>;
-  constexpr int EPL = TA::EPL, LPR = TA::LPR;
+  using TA = Tile<T, D, G>;
   constexpr int PSTRIDE = D + 4;
+  constexpr int kMerge = 4 * G * D * 4;
+  constexpr int kLds = 4 * TA::kLdsBytes > kMerge ? 4 * TA::kLdsBytes : kMerge;
 
   __shared__ float wm[4][G], wl[4][G];
-  __shared__ __attribute__((aligned(16))) float wacc[4][G][D];
+  // the waves' K rows, then (when every wave is done) their accumulators
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  float (*wacc)[G][D] = reinterpret_cast<float (*)[G][D]>(lds);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t bh = blockIdx.y;
   const int64_t b = bh / Hkv, hk = bh % Hkv;
   const int j = blockIdx.x;
@@ -432,40 +435,29 @@ __global__ __launch_bounds__(256) void k_attend(
   TA ta;
   ta.init(q + (b * Hq + hk * G) * D, qscale, lane);
   const int t_end = min(total, (j + 1) * 4 * tpw);
-  for (int ti = j * 4 * tpw + wave; ti < t_end; ti += 4) {   // wave-uniform
-    int64_t start;
-    int len;
-    unsigned hm = kAllHeads;
+  ta.run(K, V, j * 4 * tpw + wave, t_end, 4, lds + wave * TA::kLdsBytes, [&](int ti) {
+    TileRef r;
+    r.hmask = kAllHeads;
     if (ti < seg_tiles) {
       const int e = uni[bh * umax + ti / tiles_per_seg];
       const int s = e & ((1 << kUniIdBits) - 1);
-      if (per_head) hm = (unsigned)e >> kUniIdBits;
+      if (per_head) r.hmask = (unsigned)e >> kUniIdBits;
       const int off = (ti % tiles_per_seg) * kTile;
-      start = (int64_t)s * c + off;
-      len = min(kTile, c - off);
+      r.row0 = bh * cap + (int64_t)s * c + off;
+      r.len = min(kTile, c - off);
     } else if (ti < seg_tiles + win_tiles) {
-      start = sp.ws + (int64_t)(ti - seg_tiles) * kTile;
-      len = (int)min((int64_t)kTile, sp.t - start);
+      const int64_t start = sp.ws + (int64_t)(ti - seg_tiles) * kTile;
+      r.row0 = bh * cap + start;
+      r.len = (int)min((int64_t)kTile, sp.t - start);
     } else {
       const int off = (ti - seg_tiles - win_tiles) * kTile;
-      start = (int64_t)off - sa.n_sink;
-      len = min(kTile, sp.sink - off);
+      r.row0 = bh * cap + off - sa.n_sink;
+      r.len = min(kTile, sp.sink - off);
     }
-    ta.tile(K, V, bh * cap + start, len, lane, hm);
-  }
-  ta.reduce_rows();
-
-  const int jj = lane % LPR;
-  if (lane < LPR) {
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) wacc[wave][g][jj * EPL + e] = ta.acc[g][e];
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) { wm[wave][g] = ta.m[g]; wl[wave][g] = ta.l[g]; }
-  }
+    return r;
+  });
+  __syncthreads();                         // no wave reads its K rows any more
+  ta.finish(&wacc[wave][0][0], wm[wave], wl[wave]);
   __syncthreads();
 
   float* pj = part + ((bh * maxwg + j) * G) * (int64_t)PSTRIDE;

@@ -1,0 +1,126 @@
+"""The attention tiles at their edges: segments and windows that leave tiles of
+1, 15, 16, 17, 63, 64 rows, every group size, both head dims, per-head masks,
+and the library's own choice for a group of eight against the split kernels.
+
+Tolerance of the outputs against fp64: the cut of p into three bf16 terms is
+exact and the sums are fp32, so only the rounding of the bf16 output (half an
+ulp: seven stored bits, so up to 2^-8 of the value) and fp32 sums of up to 400
+products (400 * 2^-24 of the largest |V|, 4e-5 for |V| <= 1.7) remain."""
+import numpy as np
+import pytest
+import torch
+
+import _harness as H
+import paper_2503_10571_amd as radar
+from oracle import radar_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(cfg, seed, vmax=1.7):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    shape = (cfg.batch, cfg.n_kv_heads, cfg.capacity, cfg.head_dim)
+    K = torch.randn(shape, generator=g, device="cuda").to(cfg.dtype)
+    V = torch.randn(shape, generator=g, device="cuda").clamp(-vmax, vmax).to(cfg.dtype)
+    q = torch.randn(cfg.batch, cfg.n_q_heads, cfg.head_dim, generator=g,
+                    device="cuda").to(cfg.dtype)
+    omega = torch.randn(cfg.n_features, cfg.head_dim, generator=g,
+                        device="cuda").to(torch.bfloat16).float()
+    return K, V, q, omega
+
+
+def _close(out, ref, dtype):
+    half_ulp = 2.0 ** -8 if dtype == torch.bfloat16 else 0.0
+    bad = np.abs(out - ref) > half_ulp * np.abs(ref) * 1.01 + 4e-5
+    assert not bad.any(), (np.argwhere(bad)[:4], out[bad][:4], ref[bad][:4])
+
+
+@pytest.mark.parametrize("c,w", [(1, 1), (15, 17), (16, 63), (17, 64), (63, 65), (64, 16),
+                                 (65, 130), (100, 3)])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("d,dtype", [(64, torch.bfloat16), (128, torch.bfloat16),
+                                     (64, torch.float32), (128, torch.float32)])
+def test_partial_tiles(c, w, G, d, dtype):
+    t, n_sink = 3 + 6 * c + w, 3
+    for per_head in (radar.GQA_UNION, radar.GQA_PER_HEAD):
+        print(f"[case] attend c={c} w={w} G={G} d={d} {dtype} per_head={per_head}", flush=True)
+        cfg = radar.Config(1, G, 1, d, 64, c, w, t + 70, dtype, n_sink, per_head)
+        K, V, q, _ = _inputs(cfg, 7 * c + w)
+        ws, n_cand = orc.window_split(t, c, w, n_sink)
+        sel = torch.full((1, G, 3), -1, dtype=torch.int32, device="cuda")
+        for h in range(G):
+            ids = [(h * 5 + 1) % n_cand, (h * 3) % n_cand]
+            sel[0, h, :2] = torch.tensor(ids, dtype=torch.int32)
+        out = H.f64(radar.attend_selected(cfg, q, K, V, sel, t))
+        own = [[int(s) for s in sel[0, h] if s >= 0] for h in range(G)]
+        for h in range(G):
+            ids = own[h] if per_head else [s for o in own for s in o]
+            toks = orc.attended_tokens(ids, c, ws, t, n_sink)
+            ref = orc.attend(H.f64(q[0, h]), H.f64(K[0, 0]), H.f64(V[0, 0]), toks)
+            _close(out[0, h], ref, dtype)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_infinite_value(G, d):
+    """An infinite V element in a tile without masked rows makes its output
+    infinite, not NaN, although p has a single significant bit (all logits
+    are equal: p = 1), so that its second and third term are 0."""
+    cfg = radar.Config(1, G, 1, d, 64, 16, 128, 128, torch.bfloat16)
+    K, V, q, _ = _inputs(cfg, 3)
+    K.zero_()
+    for t in (64, 128):
+        print(f"[case] inf V G={G} d={d} t={t}", flush=True)
+        v = V.clone()
+        v[0, 0, 0, 5] = float("inf")
+        v[0, 0, t - 1, 9] = float("-inf")
+        sel = torch.full((1, G, 1), -1, dtype=torch.int32, device="cuda")
+        out = radar.attend_selected(cfg, q, K, v, sel, t).float()
+        assert bool((out[0, :, 5] == float("inf")).all())
+        assert bool((out[0, :, 9] == float("-inf")).all())
+        rest = [i for i in range(d) if i not in (5, 9)]
+        ref = H.f64(v[0, 0, :t, rest]).mean(0)
+        for h in range(G):
+            _close(H.f64(out[0, h, rest]), ref, torch.bfloat16)
+
+
+@pytest.mark.parametrize("opt", ["plain", "sinks", "per_head", "ragged", "no_candidates", "w0"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_group_of_eight_route(opt, d):
+    """The library's choice for a group of eight (its last stages in one
+    kernel) against the forced split path: the same selection, outputs
+    within their rounding, for both call forms."""
+    print(f"[case] g8 route {opt} d={d}", flush=True)
+    t = 1500 if opt != "no_candidates" else 60
+    cfg = radar.Config(3, 16, 2, d, 128, 37, 0 if opt == "w0" else 90, t + 4, torch.bfloat16,
+                       5 if opt == "sinks" else 0,
+                       radar.GQA_PER_HEAD if opt == "per_head" else radar.GQA_UNION)
+    K, V, q, omega = _inputs(cfg, 11)
+    summ = radar.new_summaries(cfg, "cuda")
+    radar.build_index(cfg, K, omega, t, summ)
+    lens = torch.tensor([t, t // 2, 0], device="cuda") if opt == "ragged" else None
+    k = 7
+    res = {}
+    for path in (radar.PATH_AUTO, radar.PATH_SPLIT):
+        radar.set_decode_path(path)
+        try:
+            assert radar.decode_path(cfg, t, k) == radar.PATH_SPLIT
+            sel = torch.empty(3, 16, k, dtype=torch.int32, device="cuda")
+            sc = torch.empty(3, 16, k, device="cuda")
+            out = radar.decode(cfg, q, K, V, omega, summ, t, k, selected=sel, scores=sc, lens=lens)
+            K2, V2, summ2 = K.clone(), V.clone(), summ.clone()
+            step = radar.append_decode(cfg, q, K2, V2, K[:, :, t].clone(), V[:, :, t].clone(),
+                                       omega, summ2, t + 1, k, pos=lens)
+            res[path] = (out, sel, sc, step, K2, V2, summ2)
+        finally:
+            radar.set_decode_path(radar.PATH_AUTO)
+    a, b = res[radar.PATH_AUTO], res[radar.PATH_SPLIT]
+    for i in (1, 4, 5, 6):
+        assert torch.equal(a[i], b[i]), i
+    assert torch.equal(a[2].nan_to_num(-1.0), b[2].nan_to_num(-1.0))
+    for i in (0, 3):
+        x, y = H.f64(a[i]), H.f64(b[i])
+        assert np.array_equal(np.isnan(x), np.isnan(y))
+        bad = np.abs(x - y) > 2.0 ** -7 * np.abs(y) + 8e-5
+        assert not bad.any()
