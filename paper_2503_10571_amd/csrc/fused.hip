@@ -41,7 +41,7 @@ namespace radar_impl {
 // ucnt_out for the split path's attention (the select path: one workgroup
 // per pair replaces the phi(q), score and top-k kernels). MODE kFusedScored
 // starts at phase 3: the scores of phases 1-2 come from the split path's
-// chip-wide phi(q) and score kernels (gscores [B][Hq][nc_cap]), for pairs
+// chip-wide phi(q) and score kernels (gscores [nsl][B][Hq][nc_cap]), for pairs
 // whose summary rows are too many to read R times (the scored path).
 
 template <typename T, int D, int G, int N, int MODE>
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     float s2, float inv_sqrt_n, float qscale, int* __restrict__ uni_out,
     int* __restrict__ ucnt_out, int umax, AppendArgs ap, int R, int n_pairs,
     float* __restrict__ part, int maxwg, const float* __restrict__ gscores,
-    int nc_cap, uint64_t* __restrict__ clk, int clk_max) {
+    int nc_cap, int nsl, int64_t sl_stride, uint64_t* __restrict__ clk, int clk_max) {
   constexpr bool SEL = MODE == kFusedSelect;
   constexpr bool SCORED = MODE == kFusedScored;
   constexpr int NW = kFusedWaves;
@@ -159,14 +159,40 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     };
 
     // ---- 1. phi(q) -----------------------------------------------------
-    // 16 lanes per Omega row, 4 rows per wave and pass, NP passes. All of a
-    // chunk's Omega loads are issued before any is used, then the summary
-    // rows (when they fit in registers next to them), then the dots. The
-    // phase is compiled once per Omega storage type (BF: bf16) and one copy
-    // runs, so both kinds of load stay in flight together.
+    // 16 lanes per Omega row, 4 rows per wave and pass, NP passes in chunks
+    // of at most 8 (PhiBf16; one fma chain per feature and head for fp32
+    // caches). The first chunk's Omega loads go out first, then q, then the
+    // summary rows (when they fit in registers next to them). For bf16 caches
+    // the phase is compiled once per Omega storage type and one copy runs, so
+    // all those loads stay in flight together.
     const int rb0 = wave * 16 * RB;
-    auto phase1 = [&](auto bf_tag) {
-      constexpr bool BF = decltype(bf_tag)::value;
+    if constexpr (sizeof(T) == 2) {
+      auto phase1 = [&](auto bf_tag) {
+        constexpr bool BF = decltype(bf_tag)::value;
+        constexpr int NP = N / (4 * NW);
+        constexpr int PC = NP < 8 ? NP : 8;
+        using PM = PhiBf16<D, G, PC>;
+        PM pm;
+#pragma unroll
+        for (int c0 = 0; c0 < NP; c0 += PC) {
+          typename PM::template Om<BF> om;
+          PM::template load<BF>(om, omega, c0 * 4 * NW + wave * 4 + (lane >> 4), 4 * NW, lane);
+          if (c0 == 0) {
+            pm.load_q(q0, lane);
+            // rows clamp to the last candidate; a wave whose first row is
+            // past it has no rows (the candidate count is uniform)
+            if (N <= 256 && rb0 < n_cand) load_rows(rb0);
+            pm.norm(s2, lane);
+          }
+          pm.template features<BF>(om, s1, inv_sqrt_n, lane, [&](int g, int p, float v) {
+            phq[g * N + (c0 + p) * 4 * NW + wave * 4 + (lane >> 4)] = v;
+          });
+        }
+        if (N == 512 && rb0 < n_cand) load_rows(rb0);
+      };
+      if (obf) phase1(std::true_type{});
+      else phase1(std::false_type{});
+    } else {
       constexpr int NP = N / (4 * NW);       // passes
       constexpr int PC = NP < 8 ? NP : 8;    // passes per load chunk
       constexpr bool kPrefetch = NP <= 8;
@@ -178,19 +204,15 @@ __global__ __launch_bounds__(512) void k_decode_fused(
       float ph[kChunkOut ? PC : NP][G];
 #pragma unroll
       for (int c0 = 0; c0 < NP; c0 += PC) {
-        // the Omega loads come first in each copy of the phase, so the
-        // compiler cannot hoist the q loads and their conversion (code the
-        // two copies share) above the choice of copy, where they would
-        // have to be waited for
         uint4 om[PC][QPL / 4];
-        load_omega_rows<BF, PC, QPL>(om, omega, [&](int p) {
+        load_omega_rows<PC, QPL>(om, static_cast<const float*>(omega), [&](int p) {
           return (int64_t)((c0 + p) * 4 * NW + wave * 4 + r) * D + jj * QPL;
         });
         if (c0 == 0) {
 #pragma unroll
           for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int e = 0; e < QPL; ++e) qv[g][e] = to_f32<T>(q0[g * D + jj * QPL + e]);
+            for (int e = 0; e < QPL; ++e) qv[g][e] = q0[g * D + jj * QPL + e];
         }
         // rows clamp to the last candidate; a wave whose first row is past
         // it has no rows (the candidate count is uniform)
@@ -211,11 +233,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
           for (int g = 0; g < G; ++g) a[g] = 0.f;
 #pragma unroll
           for (int e4 = 0; e4 < QPL / 4; ++e4) {
-            float4 o = omega_f4<BF>(om[p][e4]);
-            if constexpr (sizeof(T) == 2 && !BF) {
-              o.x = round_bf16(o.x); o.y = round_bf16(o.y);
-              o.z = round_bf16(o.z); o.w = round_bf16(o.w);
-            }
+            const float4 o = omega_f4(om[p][e4]);
 #pragma unroll
             for (int g = 0; g < G; ++g) {
               a[g] = fmaf(o.x, qv[g][4 * e4], a[g]);
@@ -248,12 +266,6 @@ __global__ __launch_bounds__(512) void k_decode_fused(
             for (int g = 0; g < G; ++g) phq[g * N + p * 4 * NW + wave * 4 + r] = ph[p][g];
         }
       }
-    };
-    if constexpr (sizeof(T) == 2) {
-      if (obf) phase1(std::true_type{});
-      else phase1(std::false_type{});
-    } else {
-      phase1(std::false_type{});
     }
     __syncthreads();
     stamp(1);
@@ -383,14 +395,15 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     int* row = sel_lds + wave * k_eff;
     u64* list = list_lds + wave * kMaxK;
     const int npl = (n_cand + 63) / 64;
-    if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list);
-    else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list);
-    else if (npl <= 4) head_topk<4>(src, n_cand, k, k_eff, row, so, sco, lane, list);
-    else if (npl <= 8) head_topk<8>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    const int nsl_ = SCORED ? nsl : 1;
+    if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
+    else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
+    else if (npl <= 4) head_topk<4>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
+    else if (npl <= 8) head_topk<8>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
     else if (!SCORED || npl <= 16)
-      head_topk<16>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+      head_topk<16>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
     else if constexpr (SCORED)             // up to 2048 candidates
-      head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+      head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
   } else if constexpr (!SEL) {
     ta.run(K, V, rj + (wave - G) * R, extra_tiles, (NW - G) * R, krows, extra_tile);
   }
@@ -488,7 +501,7 @@ radar_status launch_fused_tdg(const FusedArgs& a) {
          s.s_cap, (int)ceil_div(s.c, kTile), a.sa, s.per_head, s1, s2,
          1.f / std::sqrt((float)s.n), kLog2e / std::sqrt((float)s.d), a.uni_out,
          a.ucnt_out, a.umax, a.ap, a.R, n_pairs, a.part, a.maxwg, a.gscores, a.nc_cap,
-         g_clock, g_clock_max);
+         a.sp.nsl, a.sp.stride, g_clock, g_clock_max);
   return launch_status();
 }
 

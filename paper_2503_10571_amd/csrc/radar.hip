@@ -13,10 +13,11 @@
 //                  workgroup: phi(q), Eq. 6 scores, top-k, union, attention
 //                  and merge. Its select-only instantiation (phases up to the
 //                  union) is the first kernel of the select path.
-//   k_phi_q        phi(q), Eq. 4, per block of 64 features of a kv head's
-//                  query group (split path).
-//   k_score        Eq. 6 scores of every candidate segment: HBM-bound GEMV
-//                  over the fp32 summaries, DPP transpose-reduce.
+//   k_phi_score    phi(q), Eq. 4, and the Eq. 6 scores of every candidate
+//                  segment for bf16 caches (split and scored paths): phi(q) of
+//                  a feature slice in LDS, HBM-bound GEMV over the fp32
+//                  summaries, DPP transpose-reduce.
+//   k_phi_q, k_score  the same as two kernels for fp32 caches.
 //   k_topk_union   per query head top-k (score desc, index asc) by radix
 //                  selection; per kv head sorted union of the group.
 //   k_segment_mass ln(beta_s), the exact attention mass of every candidate
@@ -244,7 +245,7 @@ radar_status launch_fused(const Shape& s, const void* q, const void* K, const vo
   // registers than the fused kernel has to spare
   if (s.dt == RADAR_F32 && s.d == 128) return RADAR_EUNSUPPORTED;
   const FusedArgs a{&s, q, K, V, omega, summ, sa, out, selected, sel_scores, nullptr,
-                    nullptr, 0, ap, R, part, L.maxwg, st, nullptr, 0};
+                    nullptr, 0, ap, R, part, L.maxwg, st, nullptr, 0, {1, 0}};
   const radar_status r = launch_fused_any(a, false);
   if (r != RADAR_OK || R == 1) return r;
   launch_combine_any(s, part, nullptr, out, sa, L, 1, R, R, st);
@@ -260,7 +261,7 @@ radar_status launch_select(const Shape& s, const void* q, const void* omega,
   const FusedArgs a{&s, q, nullptr, nullptr, omega, summ, sa, nullptr, selected,
                     sel_scores, reinterpret_cast<int*>(w + L.uni),
                     reinterpret_cast<int*>(w + L.ucnt), L.umax, ap, 1, nullptr, 0, st,
-                    nullptr, 0};
+                    nullptr, 0, {1, 0}};
   return launch_fused_any(a, true);
 }
 
@@ -434,23 +435,23 @@ radar_status run_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
     if (r != RADAR_OK) return r;
     return launch_attend(s, q, Kp, Vp, plan.ag, sa, out, w, L, stream);
   }
+  // (bf16 caches: the slices' scores fill both arrays)
   float* phiq = reinterpret_cast<float*>(w + L.phiq);
-  float* sc = reinterpret_cast<float*>(w + L.scores);
-  if (top.n_cand > 0) {
-    launch_phi_q_any(s, q, omega, phiq, stream);
-    launch_score(s, phiq, summaries, sc, top.n_cand, sa, stream);
-  }
+  float* sc = reinterpret_cast<float*>(w + (s.dt == RADAR_BF16 ? L.phiq : L.scores));
+  const ScorePlan sp = score_plan(s, top.n_cand);
+  if (top.n_cand > 0)
+    launch_scores(s, q, omega, summaries, phiq, sc, top.n_cand, sp, sa, stream);
   if (plan.tail) {
     float* part = plan.R > 1 ? reinterpret_cast<float*>(w + L.part) : nullptr;
     const FusedArgs a{&s, q, Kp, Vp, omega, summaries, sa, out, selected, scores,
                       nullptr, nullptr, 0, ap, plan.R, part, L.maxwg, stream, sc,
-                      (int)std::max<int64_t>(1, s.s_cap)};
+                      (int)std::max<int64_t>(1, s.s_cap), sp};
     const radar_status r = launch_fused_scored(a);
     if (r != RADAR_OK || plan.R == 1) return r;
     launch_combine_any(s, part, nullptr, out, sa, L, 1, plan.R, plan.R, stream);
     return launch_status();
   }
-  launch_topk_union(s, sc, sa, reinterpret_cast<int*>(w + L.uni),
+  launch_topk_union(s, sc, sp, sa, reinterpret_cast<int*>(w + L.uni),
                     reinterpret_cast<int*>(w + L.ucnt), L.umax, selected, scores, ap,
                     stream);
   const radar_status r = launch_status();
@@ -787,7 +788,7 @@ radar_status radar_decode_exact(const radar_config* cfg, const void* q,
   if (top.n_cand > 0)
     launch_segment_mass(s, q, Kp, sc, top.n_cand, sa, (int)std::max<int64_t>(1, s.s_cap),
                         false, stream);
-  launch_topk_union(s, sc, sa, reinterpret_cast<int*>(w + L.uni),
+  launch_topk_union(s, sc, {1, 0}, sa, reinterpret_cast<int*>(w + L.uni),
                     reinterpret_cast<int*>(w + L.ucnt), L.umax, selected, scores,
                     AppendArgs{}, stream);
   r = launch_status();

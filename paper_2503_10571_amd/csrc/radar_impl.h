@@ -182,41 +182,21 @@ __device__ __forceinline__ float4 ld_stream_f4(const float* p) {
   return make_float4(t.x, t.y, t.z, t.w);
 }
 
-// Omega is fp32 [n][d], or bf16 [n][d] for bf16 caches (whose projection
-// rounds Omega to bf16 anyway, so both give the same products); fp32 caches
-// always pass fp32 Omega.
-//
-// NR rows of QPL Omega entries (row_idx(p): element index of row p's first
-// entry), stored as bf16 (BF) or fp32, all loads issued together and kept
-// as raw words (fp32: four floats; bf16: four values in .x and .y);
-// omega_f4 widens a word where it is used. Callers choose BF at compile
-// time, so no branch or conversion sits between these loads and the loads
-// issued after them.
-template <bool BF, int NR, int QPL, typename F>
-__device__ __forceinline__ void load_omega_rows(uint4 (&raw)[NR][QPL / 4], const void* omega,
+// NR rows of QPL entries of an fp32 Omega (row_idx(p): element index of row
+// p's first entry), all loads issued together and kept as raw words (fp32
+// caches; bf16 ones read Omega, fp32 or bf16, into matrix operands)
+template <int NR, int QPL, typename F>
+__device__ __forceinline__ void load_omega_rows(uint4 (&raw)[NR][QPL / 4], const float* omega,
                                                 F&& row_idx) {
 #pragma unroll
   for (int p = 0; p < NR; ++p)
 #pragma unroll
-    for (int e4 = 0; e4 < QPL / 4; ++e4) {
-      if constexpr (BF) {
-        const uint2 u = *reinterpret_cast<const uint2*>(
-            static_cast<const uint16_t*>(omega) + row_idx(p) + 4 * e4);
-        raw[p][e4] = make_uint4(u.x, u.y, 0u, 0u);
-      } else {
-        raw[p][e4] = *reinterpret_cast<const uint4*>(
-            static_cast<const float*>(omega) + row_idx(p) + 4 * e4);
-      }
-    }
+    for (int e4 = 0; e4 < QPL / 4; ++e4)
+      raw[p][e4] = *reinterpret_cast<const uint4*>(omega + row_idx(p) + 4 * e4);
 }
-template <bool BF>
 __device__ __forceinline__ float4 omega_f4(uint4 w) {
-  if constexpr (BF)
-    return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
-                       __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u));
-  else
-    return make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z),
-                       __uint_as_float(w.w));
+  return make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z),
+                     __uint_as_float(w.w));
 }
 
 // ---------------------------------------------------------------------------
@@ -436,15 +416,34 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
   return x + (row > 0 ? r0 : 0) + (row > 1 ? r1 : 0) + (row > 2 ? r2 : 0);
 }
 
+//
+// The scores may come in nsl slices of the features, `stride` floats apart,
+// that are added in slice order (several slices' loads in flight at once).
 template <int NPL>
 __device__ void head_topk(const float* __restrict__ src, int n_cand, int k,
                           int k_eff, int* sel_row, int32_t* sel_out,
-                          float* sc_out, int lane, u64* list) {
+                          float* sc_out, int lane, u64* list, int nsl = 1,
+                          int64_t stride = 0) {
   uint32_t u[NPL];                         // ordered score keys, 0 = absent
   if (n_cand > 0) {
     float v[NPL];
 #pragma unroll
     for (int m = 0; m < NPL; ++m) v[m] = src[min(m * 64 + lane, n_cand - 1)];
+    if (nsl > 1) {                         // uniform
+      constexpr int SG = NPL <= 2 ? 7 : NPL <= 8 ? 3 : 1;
+      for (int s0 = 1; s0 < nsl; s0 += SG) {
+        float x[SG][NPL];
+#pragma unroll
+        for (int z = 0; z < SG; ++z)
+#pragma unroll
+          for (int m = 0; m < NPL; ++m)
+            x[z][m] = src[min(s0 + z, nsl - 1) * stride + min(m * 64 + lane, n_cand - 1)];
+#pragma unroll
+        for (int z = 0; z < SG; ++z)
+#pragma unroll
+          for (int m = 0; m < NPL; ++m) v[m] += s0 + z < nsl ? x[z][m] : 0.f;
+      }
+    }
 #pragma unroll
     for (int m = 0; m < NPL; ++m)
       u[m] = (m * 64 + lane < n_cand) ? (uint32_t)(order_key(v[m], 0) >> 32) : 0u;
@@ -1032,6 +1031,119 @@ struct TileMfma {
 template <typename T, int D, int G>
 using Tile = typename std::conditional<sizeof(T) == 2, TileMfma<D, G>, TileVec<D, G>>::type;
 
+// ---------------------------------------------------------------------------
+// phi(q) of a group's heads (Eq. 4) for bf16 caches
+// ---------------------------------------------------------------------------
+// 16 lanes per Omega row, 4 rows per wave and pass: a lane multiplies its
+// D / 16 dims (v_dot2_f32_bf16 on the raw pairs; an fp32 Omega is rounded to
+// bf16 first), and the NP * G sums of a lane's passes and heads are
+// transpose-reduced over the 16 lanes, so each lane ends with one sum per 16
+// and the exponent, exp2 and store run once per feature and head. (One fma
+// chain, one 16-lane reduction and one exp2 in every lane per feature and
+// head, the form fp32 caches keep, is three times the instructions. The matrix
+// cores take fewer still, but their sums put the scores of a 512K context off
+// by 1e-6 where these are off by 2e-7, and reading Omega in operand layout, 16
+// rows per load, was 1 us slower.)
+template <int D, int G, int NP>
+struct PhiBf16 {
+  static constexpr int QPL = D / 16;       // dims per lane
+  static constexpr int W = QPL / 2;        // bf16 pairs per lane
+  static constexpr int NVAL = NP * G;      // sums per lane
+  // NP passes of Omega rows in flight: raw words, as stored
+  template <bool BF> struct Om { uint32_t w[NP][BF ? W : QPL]; };
+  uint32_t qw[G][W];
+  float nrm;                               // |q|^2 s2 of head lane % G
+
+  template <int NWORD>
+  __device__ static __forceinline__ void load_words(uint32_t (&w)[NWORD], const void* src) {
+    if constexpr (NWORD == 2) {
+      const uint2 u = *static_cast<const uint2*>(src);
+      w[0] = u.x; w[1] = u.y;
+    } else {
+#pragma unroll
+      for (int i = 0; i < NWORD / 4; ++i) {
+        const uint4 u = static_cast<const uint4*>(src)[i];
+        w[4 * i] = u.x; w[4 * i + 1] = u.y; w[4 * i + 2] = u.z; w[4 * i + 3] = u.w;
+      }
+    }
+  }
+  // pass p reads row `row` + p * step (row: this lane's row of pass 0)
+  template <bool BF>
+  __device__ static __forceinline__ void load(Om<BF>& om, const void* omega, int row, int step,
+                                              int lane) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int at = (row + p * step) * D + (lane & 15) * QPL;
+      if constexpr (BF) load_words(om.w[p], static_cast<const bf16_t*>(omega) + at);
+      else load_words(om.w[p], static_cast<const float*>(omega) + at);
+    }
+  }
+  __device__ __forceinline__ void load_q(const bf16_t* q0, int lane) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) load_words(qw[g], q0 + g * D + (lane & 15) * QPL);
+  }
+  __device__ static __forceinline__ float dot(uint32_t a, uint32_t b, float c) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v_t, a),
+                                           __builtin_bit_cast(bf16x2v_t, b), c, false);
+  }
+  __device__ __forceinline__ void norm(float s2, int lane) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      float sq = 0.f;
+#pragma unroll
+      for (int i = 0; i < W; ++i) sq = dot(qw[g][i], qw[g][i], sq);
+      sq = row_sum(sq) * s2;
+      nrm = g == 0 || lane % G == g ? sq : nrm;
+    }
+  }
+  // phi of the loaded rows: put(head, pass, value)
+  template <bool BF, typename Put>
+  __device__ __forceinline__ void features(const Om<BF>& om, float s1, float inv_sqrt_n, int lane,
+                                           Put&& put) {
+    constexpr int GRP = NVAL < 16 ? NVAL : 16;     // sums per transpose
+    const int jj = lane & 15;
+    float v[NVAL];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      uint32_t w[W];
+#pragma unroll
+      for (int i = 0; i < W; ++i) {
+        if constexpr (BF) w[i] = om.w[p][i];
+        else w[i] = f32_to_bf16(__uint_as_float(om.w[p][2 * i])) |
+                    (f32_to_bf16(__uint_as_float(om.w[p][2 * i + 1])) << 16);
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        float a = 0.f;
+#pragma unroll
+        for (int i = 0; i < W; ++i) a = dot(w[i], qw[g][i], a);
+        v[p * G + g] = a;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NVAL / GRP; ++q) {
+      float* x = v + q * GRP;
+      // fewer than 16 sums: first add the lanes that share a place
+      if constexpr (GRP <= 8) {
+#pragma unroll
+        for (int i = 0; i < GRP; ++i) x[i] += partner<8>(x[i], lane);
+      }
+      if constexpr (GRP <= 4) {
+#pragma unroll
+        for (int i = 0; i < GRP; ++i) x[i] += partner<4>(x[i], lane);
+      }
+      if constexpr (GRP <= 2) {
+#pragma unroll
+        for (int i = 0; i < GRP; ++i) x[i] += partner<2>(x[i], lane);
+      }
+      transpose_reduce<GRP>(x, lane);
+      const int at = q * GRP + jj % GRP;
+      const float ph = fast_exp2(fmaf(x[0], s1, -nrm)) * inv_sqrt_n;
+      if (jj < GRP) put(at % G, at / G, ph);
+    }
+  }
+};
+
 // decode path shared by the fused kernel and its select-only instantiation
 // k_decode_fused modes: the whole step; the selection only (select path);
 // the step from scores the split path's kernels computed (scored path)
@@ -1138,17 +1250,24 @@ radar_status launch_build(const Shape& s, const void* K, const void* omega,
                           const int64_t* pos, hipStream_t st);
 
 // split.hip: the split path's stages
-void launch_phi_q_any(const Shape& s, const void* q, const void* omega, float* phiq,
-                      hipStream_t st);
-void launch_score(const Shape& s, const float* phiq, const float* summ,
-                  float* scores, int n_cand, const SeqArgs& sa, hipStream_t st);
+// Eq. 6 scores of up to n_cand candidates of every query head into `sc`, in
+// ScorePlan's slices; bf16 caches in one kernel, fp32 ones in two (phi(q) to
+// `phiq` first)
+struct ScorePlan {
+  int nsl;             // slices of the features
+  int64_t stride;      // floats between them
+};
+ScorePlan score_plan(const Shape& s, int n_cand);
+void launch_scores(const Shape& s, const void* q, const void* omega, const float* summ,
+                   float* phiq, float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
+                   hipStream_t st);
 // ln(beta) of candidates [0, n_cand) into rows of nc_cap scores; with_rest
 // also the mass of the window and sinks at index n_cand
 void launch_segment_mass(const Shape& s, const void* q, const void* K, float* scores,
                          int n_cand, const SeqArgs& sa, int nc_cap, bool with_rest,
                          hipStream_t st);
-void launch_topk_union(const Shape& s, const float* scores, const SeqArgs& sa,
-                       int* uni, int* ucnt, int umax, int32_t* selected,
+void launch_topk_union(const Shape& s, const float* scores, const ScorePlan& sp,
+                       const SeqArgs& sa, int* uni, int* ucnt, int umax, int32_t* selected,
                        float* sel_scores, const AppendArgs& ap, hipStream_t st);
 void launch_union_given(const Shape& s, const int32_t* given, int given_k,
                         const SeqArgs& sa, int* uni, int* ucnt, int umax,
@@ -1182,6 +1301,7 @@ struct FusedArgs {
   hipStream_t st;
   const float* gscores;    // scored path: [B][Hq][nc_cap] Eq. 6 scores
   int nc_cap;
+  ScorePlan sp;
 };
 radar_status launch_fused_n64(const FusedArgs& a, bool sel);
 radar_status launch_fused_n128(const FusedArgs& a, bool sel);

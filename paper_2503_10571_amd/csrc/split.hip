@@ -1,5 +1,5 @@
-// The split decode path's stages, each spread over the whole chip: phi(q),
-// Eq. 6 scores, the exact segment mass, top-k and union, the given-selection
+// The split decode path's stages, each spread over the whole chip: phi(q) and
+// Eq. 6 scores (one kernel for bf16 caches, two for fp32 ones), the exact segment mass, top-k and union, the given-selection
 // union, the gather attention and the merge of its partials (also used by
 // the fused path when several workgroups share a pair).
 #include "radar_impl.h"
@@ -8,7 +8,7 @@ namespace radar_impl {
 
 // ---------------------------------------------------------------------------
 // k_phi_q: phi(q) (Eq. 4) of the G query heads of one (b, kv head), one
-// block of 64 features per workgroup
+// block of 64 features per workgroup (fp32 caches)
 // ---------------------------------------------------------------------------
 // Grid (n / 64, B * Hkv): each workgroup reads only its 64 rows of Omega.
 // 16 lanes share one Omega row (D/16 floats each); wave w covers rows
@@ -16,9 +16,9 @@ namespace radar_impl {
 // lane are reduced across its 16 lanes (transpose-reduce over 4 lanes, then
 // two butterflies), so lane jj < 4 of row group r ends with feature
 // 16 w + 4 jj + r.
-template <typename T, int D, int G, bool BF>
-__global__ __launch_bounds__(256) void k_phi_q(const T* __restrict__ q,
-                                               const void* __restrict__ omega,
+template <int D, int G>
+__global__ __launch_bounds__(256) void k_phi_q(const float* __restrict__ q,
+                                               const float* __restrict__ omega,
                                                float* __restrict__ phiq,
                                                int n, int Hq, int Hkv, float s1,
                                                float s2, float inv_sqrt_n) {
@@ -32,14 +32,14 @@ __global__ __launch_bounds__(256) void k_phi_q(const T* __restrict__ q,
   const int f0 = blockIdx.x * 64 + wave * 16;
 
   uint4 om[4][QPL / 4];
-  load_omega_rows<BF, 4, QPL>(om, omega, [&](int p) {
+  load_omega_rows<4, QPL>(om, omega, [&](int p) {
     return (int64_t)(f0 + p * 4 + r) * D + jj * QPL;
   });
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     float qv[QPL];
 #pragma unroll
-    for (int e = 0; e < QPL; ++e) qv[e] = to_f32<T>(q[(hq0 + g) * D + jj * QPL + e]);
+    for (int e = 0; e < QPL; ++e) qv[e] = q[(hq0 + g) * D + jj * QPL + e];
     float nrm = 0.f;
 #pragma unroll
     for (int e = 0; e < QPL; ++e) nrm = fmaf(qv[e], qv[e], nrm);
@@ -50,11 +50,7 @@ __global__ __launch_bounds__(256) void k_phi_q(const T* __restrict__ q,
       float a = 0.f;
 #pragma unroll
       for (int e4 = 0; e4 < QPL / 4; ++e4) {
-        float4 o = omega_f4<BF>(om[p][e4]);
-        if constexpr (sizeof(T) == 2 && !BF) {
-          o.x = round_bf16(o.x); o.y = round_bf16(o.y);
-          o.z = round_bf16(o.z); o.w = round_bf16(o.w);
-        }
+        const float4 o = omega_f4(om[p][e4]);
         a = fmaf(o.x, qv[4 * e4], a);
         a = fmaf(o.y, qv[4 * e4 + 1], a);
         a = fmaf(o.z, qv[4 * e4 + 2], a);
@@ -73,7 +69,7 @@ __global__ __launch_bounds__(256) void k_phi_q(const T* __restrict__ q,
 }
 
 // ---------------------------------------------------------------------------
-// k_score: a[h][s] = phi(q_h) . summ[s], Eq. 6
+// k_score: a[h][s] = phi(q_h) . summ[s], Eq. 6 (fp32 caches)
 // ---------------------------------------------------------------------------
 // Workgroup = 1, 2 or 4 waves x (16 * RB) summary rows of one (b, kv head)
 // (fewer waves per workgroup when that spreads a small call over more CUs;
@@ -229,14 +225,129 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ phiq,
 
 
 // ---------------------------------------------------------------------------
+// k_phi_score: phi(q) and the Eq. 6 scores in one kernel (bf16 caches)
+// ---------------------------------------------------------------------------
+// Grid (row groups, pairs, feature slices). A workgroup computes phi(q) of its
+// slice of fs features into LDS, with its first summary rows already in
+// flight, and then scores blocks of 16 * NW rows of the slice, 16 per wave, in
+// chunks of 64 * FPL features (each chunk of a row one contiguous
+// wave load). A slice's scores go to their own array; the top-k adds the
+// slices in order.
+// Small calls are bound by latency: two kernels, with phi(q) through memory
+// between them, took 11.5 us for the paper's 16K settings (8 pairs, 120 rows
+// of 2048 features) where this one takes 7.5, and the step went from 32.9 to
+// 30.2 us (80.0 to 78.7 us at 512K, 104 to 101 us for six ragged sequences with
+// eight heads per group). Slices are what spreads few rows with many features
+// over the chip without every workgroup reading all of Omega.
+template <int D, int G, int FPL, int NW>
+__global__ __launch_bounds__(64 * NW) void k_phi_score(
+    const bf16_t* __restrict__ q, const void* __restrict__ omega, bool obf,
+    const float* __restrict__ summ, float* __restrict__ scores, int Hq, int Hkv, int n, int fs,
+    SeqArgs sa, int64_t s_cap, int nc_cap, int64_t sl_stride, float s1, float s2,
+    float inv_sqrt_n) {
+  constexpr int FC = 64 * FPL;             // features per chunk
+  extern __shared__ __attribute__((aligned(16))) float phq[];   // [G][fs]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t bh = blockIdx.y;
+  const int64_t b = __builtin_amdgcn_readfirstlane((int)blockIdx.y / Hkv);
+  const int64_t hk = bh - b * Hkv;
+  const int n_cand = seq_span(sa, b).n_cand;
+  if ((int)blockIdx.x * 16 * NW >= n_cand) return;     // workgroup-uniform
+  const int f0 = blockIdx.z * fs;
+  const bf16_t* q0 = q + (b * Hq + hk * G) * D;
+  const float* base = summ + bh * s_cap * n + f0 + lane * FPL;
+
+  float x[16][FPL];
+  auto load_rows = [&](int row0, int ch) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float* src = base + (int64_t)min(row0 + r, n_cand - 1) * n + ch * FC;
+      if constexpr (FPL == 4) {
+        const float4 v = ld_stream_f4(src);
+        x[r][0] = v.x; x[r][1] = v.y; x[r][2] = v.z; x[r][3] = v.w;
+      } else if constexpr (FPL == 2) {
+        const float2 v = *reinterpret_cast<const float2*>(src);
+        x[r][0] = v.x; x[r][1] = v.y;
+      } else {
+        x[r][0] = src[0];
+      }
+    }
+  };
+
+  int row0 = (int)blockIdx.x * 16 * NW + wave * 16;
+  // compiled once per Omega storage type, so that all loads before the first
+  // product stay in flight together
+  auto phi = [&](auto bf_tag) {
+    constexpr bool BF = decltype(bf_tag)::value;
+    constexpr int NP = FC / (4 * NW) < 8 ? FC / (4 * NW) : 8;
+    using PM = PhiBf16<D, G, NP>;
+    PM pm;
+    for (int c0 = 0; c0 < fs; c0 += NP * 4 * NW) {
+      typename PM::template Om<BF> om;
+      const int mine = c0 + wave * 4 + (lane >> 4);
+      PM::template load<BF>(om, omega, f0 + mine, 4 * NW, lane);
+      if (c0 == 0) {
+        pm.load_q(q0, lane);
+        if (row0 < n_cand) load_rows(row0, 0);
+        pm.norm(s2, lane);
+      }
+      pm.template features<BF>(om, s1, inv_sqrt_n, lane, [&](int g, int p, float v) {
+        phq[g * fs + mine + p * 4 * NW] = v;
+      });
+    }
+  };
+  if (obf) phi(std::true_type{});
+  else phi(std::false_type{});
+  __syncthreads();
+
+  float* out = scores + blockIdx.z * sl_stride + (b * Hq + hk * G) * (int64_t)nc_cap;
+  const int nch = fs / FC;
+  const int step = (int)gridDim.x * 16 * NW;
+  for (bool first = true; row0 < n_cand; row0 += step, first = false) {
+    float part[G][16];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[g][r] = 0.f;
+#pragma unroll 1
+    for (int ch = 0; ch < nch; ++ch) {
+      if (!first || ch > 0) load_rows(row0, ch);
+      float pq[G][FPL];
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * fs + ch * FC + lane * FPL + e];
+      // keep the chunk's loads together (the compiler would otherwise sink
+      // each to its first use and wait on one at a time)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int e = 0; e < FPL; ++e) part[g][r] = fmaf(x[r][e], pq[g][e], part[g][r]);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      transpose_reduce<16>(part[g], lane);
+      float v = part[g][0];
+      v = xor_sum<16>(v);
+      v = xor_sum<32>(v);
+      if (lane < 16 && row0 + lane < n_cand) out[g * (int64_t)nc_cap + row0 + lane] = v;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // k_topk_union: top-k of every query head, union per kv head
 // ---------------------------------------------------------------------------
 // One workgroup per (b, kv head); wave w takes heads w, w + 4, ... of the
 // group. The heads' sorted selections go to LDS and the union of the group
 // (ascending ids) to the workspace for the attention stage.
 __global__ __launch_bounds__(256) void k_topk_union(
-    const float* __restrict__ scores, int Hq, int Hkv, int G, SeqArgs sa,
-    int nc_cap, int per_head, int* __restrict__ uni, int* __restrict__ ucnt,
+    const float* __restrict__ scores, int nsl, int64_t sl_stride, int Hq, int Hkv, int G,
+    SeqArgs sa, int nc_cap, int per_head, int* __restrict__ uni, int* __restrict__ ucnt,
     int umax, int32_t* __restrict__ selected, float* __restrict__ sel_scores,
     AppendArgs ap, int64_t cap) {
   __shared__ int sel_lds[kMaxG * kMaxK];
@@ -259,12 +370,12 @@ __global__ __launch_bounds__(256) void k_topk_union(
     int32_t* so = selected ? selected + (b * Hq + hq) * (int64_t)k : nullptr;
     float* sco = sel_scores ? sel_scores + (b * Hq + hq) * (int64_t)k : nullptr;
     int* row = sel_lds + hl * k_eff;
-    if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list);
-    else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list);
-    else if (npl <= 4) head_topk<4>(src, n_cand, k, k_eff, row, so, sco, lane, list);
-    else if (npl <= 8) head_topk<8>(src, n_cand, k, k_eff, row, so, sco, lane, list);
-    else if (npl <= 16) head_topk<16>(src, n_cand, k, k_eff, row, so, sco, lane, list);
-    else head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
+    else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
+    else if (npl <= 4) head_topk<4>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
+    else if (npl <= 8) head_topk<8>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
+    else if (npl <= 16) head_topk<16>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
+    else head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
   }
   __syncthreads();
   group_union(sel_lds, bits_lds, G, k_eff, per_head != 0, uni + bh * umax,
@@ -595,33 +706,22 @@ __global__ __launch_bounds__(NT) void k_combine(
 }
 
 // ---- decode pieces -------------------------------------------------------
-template <typename T, int D, int G>
-void launch_phi_q_g(const Shape& s, const void* q, const void* omega, float* phiq,
-                    hipStream_t st) {
+template <int D>
+void launch_phi_q(const Shape& s, const void* q, const void* omega, float* phiq,
+                  hipStream_t st) {
   const float s1 = kLog2e / std::pow((float)s.d, 0.25f);
   const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
   const dim3 grid((unsigned)(s.n / 64), (unsigned)(s.B * s.Hkv));
-  if constexpr (sizeof(T) == 2) {
-    if (s.obf) {
-      launch(RADAR_K_PHI_Q, k_phi_q<T, D, G, true>, grid, dim3(256), 0, st,
-             reinterpret_cast<const T*>(q), omega, phiq, s.n, s.Hq, s.Hkv, s1, s2,
-             1.f / std::sqrt((float)s.n));
-      return;
-    }
-  }
-  launch(RADAR_K_PHI_Q, k_phi_q<T, D, G, false>, grid, dim3(256), 0, st,
-         reinterpret_cast<const T*>(q), omega, phiq, s.n, s.Hq, s.Hkv, s1, s2,
-         1.f / std::sqrt((float)s.n));
-}
-
-template <typename T, int D>
-void launch_phi_q(const Shape& s, const void* q, const void* omega, float* phiq,
-                  hipStream_t st) {
+  auto go = [&](auto g) {
+    launch(RADAR_K_PHI_Q, k_phi_q<D, decltype(g)::value>, grid, dim3(256), 0, st,
+           static_cast<const float*>(q), static_cast<const float*>(omega), phiq, s.n, s.Hq, s.Hkv,
+           s1, s2, 1.f / std::sqrt((float)s.n));
+  };
   switch (s.G) {
-    case 1: launch_phi_q_g<T, D, 1>(s, q, omega, phiq, st); break;
-    case 2: launch_phi_q_g<T, D, 2>(s, q, omega, phiq, st); break;
-    case 4: launch_phi_q_g<T, D, 4>(s, q, omega, phiq, st); break;
-    default: launch_phi_q_g<T, D, 8>(s, q, omega, phiq, st); break;
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    default: go(std::integral_constant<int, 8>{}); break;
   }
 }
 
@@ -674,6 +774,72 @@ void launch_score(const Shape& s, const float* phiq, const float* summ,
     case 512: launch_score_n<512>(s, phiq, summ, scores, n_cand, sa, st); break;
     case 1024: launch_score_n<1024>(s, phiq, summ, scores, n_cand, sa, st); break;
     default: launch_score_n<2048>(s, phiq, summ, scores, n_cand, sa, st); break;
+  }
+}
+
+// Feature slices of k_phi_score: one, doubled (down to 256 features each)
+// while the call has fewer workgroups than CUs and the slices' scores fit in
+// the workspace's phi(q) and score arrays, which lie next to each other.
+ScorePlan score_plan(const Shape& s, int n_cand) {
+  const int64_t cap = std::max<int64_t>(1, s.s_cap);
+  const int64_t stride = (int64_t)s.B * s.Hq * cap;
+  if (s.dt != RADAR_BF16) return {1, 0};
+  const int64_t rows = std::max<int64_t>(1, ceil_div(n_cand, 128)) * s.B * s.Hkv;
+  int nsl = 1;
+  while (s.n / nsl > 256 && rows * nsl < num_cu() && 2 * nsl * cap <= s.n + cap) nsl *= 2;
+  return {nsl, stride};
+}
+
+template <int D, int G>
+void launch_phi_score(const Shape& s, const void* q, const void* omega, const float* summ,
+                      float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
+                      hipStream_t st) {
+  const float s1 = kLog2e / std::pow((float)s.d, 0.25f);
+  const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
+  const int fs = s.n / sp.nsl, P = s.B * s.Hkv;
+  // four waves per workgroup where eight would leave CUs idle
+  const bool narrow = ceil_div(n_cand, 128) * P * sp.nsl < num_cu();
+  const int rows = narrow ? 64 : 128;
+  // row groups: one block of rows each while the workgroups do not outnumber
+  // two per CU (a workgroup's phi(q) serves all its blocks)
+  const int64_t most = std::max<int64_t>(1, 2 * (int64_t)num_cu() / ((int64_t)P * sp.nsl));
+  const int64_t groups = std::min<int64_t>(ceil_div(n_cand, rows), most);
+  const dim3 grid((unsigned)groups, (unsigned)P, (unsigned)sp.nsl);
+  auto go = [&](auto fpl, auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    launch(RADAR_K_SCORE, k_phi_score<D, G, decltype(fpl)::value, NW>, grid, dim3(64 * NW),
+           (size_t)G * fs * 4, st, static_cast<const bf16_t*>(q), omega, s.obf, summ, sc, s.Hq,
+           s.Hkv, s.n, fs, sa, s.s_cap, (int)std::max<int64_t>(1, s.s_cap), sp.stride, s1, s2,
+           1.f / std::sqrt((float)s.n));
+  };
+  auto go_nw = [&](auto fpl) {
+    if (narrow) go(fpl, std::integral_constant<int, 4>{});
+    else go(fpl, std::integral_constant<int, 8>{});
+  };
+  if (fs >= 256) go_nw(std::integral_constant<int, 4>{});
+  else if (fs == 128) go_nw(std::integral_constant<int, 2>{});
+  else go_nw(std::integral_constant<int, 1>{});
+}
+
+void launch_scores(const Shape& s, const void* q, const void* omega, const float* summ,
+                   float* phiq, float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
+                   hipStream_t st) {
+  if (s.dt != RADAR_BF16) {
+    if (s.d == 64) launch_phi_q<64>(s, q, omega, phiq, st);
+    else launch_phi_q<128>(s, q, omega, phiq, st);
+    launch_score(s, phiq, summ, sc, n_cand, sa, st);
+    return;
+  }
+  auto go = [&](auto g) {
+    constexpr int G = decltype(g)::value;
+    if (s.d == 64) launch_phi_score<64, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
+    else launch_phi_score<128, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
+  };
+  switch (s.G) {
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    default: go(std::integral_constant<int, 8>{}); break;
   }
 }
 
@@ -785,17 +951,6 @@ void launch_segment_mass_d(const Shape& s, const void* q, const void* K, float* 
   }
 }
 // ---- entry points for the other units ---------------------------------------
-void launch_phi_q_any(const Shape& s, const void* q, const void* omega, float* phiq,
-                      hipStream_t st) {
-  if (s.dt == RADAR_BF16) {
-    if (s.d == 64) launch_phi_q<bf16_t, 64>(s, q, omega, phiq, st);
-    else launch_phi_q<bf16_t, 128>(s, q, omega, phiq, st);
-  } else {
-    if (s.d == 64) launch_phi_q<float, 64>(s, q, omega, phiq, st);
-    else launch_phi_q<float, 128>(s, q, omega, phiq, st);
-  }
-}
-
 void launch_segment_mass(const Shape& s, const void* q, const void* K, float* scores,
                          int n_cand, const SeqArgs& sa, int nc_cap, bool with_rest,
                          hipStream_t st) {
@@ -808,11 +963,12 @@ void launch_segment_mass(const Shape& s, const void* q, const void* K, float* sc
   }
 }
 
-void launch_topk_union(const Shape& s, const float* scores, const SeqArgs& sa,
-                       int* uni, int* ucnt, int umax, int32_t* selected,
+void launch_topk_union(const Shape& s, const float* scores, const ScorePlan& sp,
+                       const SeqArgs& sa, int* uni, int* ucnt, int umax, int32_t* selected,
                        float* sel_scores, const AppendArgs& ap, hipStream_t st) {
   launch(RADAR_K_TOPK, k_topk_union, dim3((unsigned)(s.B * s.Hkv)), dim3(256), 0, st,
-         scores, s.Hq, s.Hkv, s.G, sa, (int)std::max<int64_t>(1, s.s_cap), s.per_head,
+         scores, sp.nsl, sp.stride, s.Hq, s.Hkv, s.G, sa, (int)std::max<int64_t>(1, s.s_cap),
+         s.per_head,
          uni, ucnt, umax, selected, sel_scores, ap, s.cap);
 }
 

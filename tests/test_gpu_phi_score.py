@@ -1,0 +1,63 @@
+"""phi(q) and the segment scores at the edges of their tiles and slices: every
+feature count, candidate counts around the row blocks of a wave and of a
+workgroup, every group size, both head dims, few and many pairs (few take
+feature slices and narrow workgroups), on the paths whose scores run as a
+kernel of their own and on the fused one. All candidates are selected (k =
+256), so every score comes back; they are held to the suite's 1e-5 of the fp64
+oracle, and a bf16 Omega has to give the bits of its fp32 copy."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import _harness as H
+import paper_2503_10571_amd as radar
+from oracle import radar_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(path, cfg, q, K, omega, summ, t, k):
+    radar.set_decode_path(path)
+    try:
+        sel = torch.empty(cfg.batch, cfg.n_q_heads, k, dtype=torch.int32, device="cuda")
+        sc = torch.empty(cfg.batch, cfg.n_q_heads, k, device="cuda")
+        out = radar.decode(cfg, q, K, K, omega, summ, t, k, selected=sel, scores=sc)
+    finally:
+        radar.set_decode_path(radar.PATH_AUTO)
+    return out, sel, sc
+
+
+@pytest.mark.parametrize("n", [64, 128, 256, 512, 1024, 2048])
+@pytest.mark.parametrize("n_cand,G,d,pairs", [
+    (1, 1, 64, 1), (15, 2, 128, 2), (16, 4, 128, 1), (17, 8, 64, 1), (63, 4, 64, 3),
+    (64, 1, 128, 40), (65, 8, 128, 2), (127, 2, 64, 1), (128, 4, 128, 2), (129, 1, 64, 2),
+    (255, 4, 128, 1), (256, 8, 128, 1), (129, 4, 64, 300)])
+def test_scores(n, n_cand, G, d, pairs):
+    c, w = 3, 2
+    t = n_cand * c + w
+    cfg = radar.Config(1, G * pairs, pairs, d, n, c, w, t + 3, torch.bfloat16)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + n_cand)
+    K = torch.randn(1, pairs, t + 3, d, generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn(1, G * pairs, d, generator=g, device="cuda").to(torch.bfloat16)
+    omega = torch.randn(n, d, generator=g, device="cuda").to(torch.bfloat16).float()
+    summ = radar.new_summaries(cfg, "cuda")
+    radar.build_index(cfg, K, omega, t, summ)
+    half = dataclasses.replace(cfg, omega_dtype=torch.bfloat16)
+    heads = sorted({0, G * pairs - 1})
+    for path in (radar.PATH_SCORED, radar.PATH_SPLIT, radar.PATH_FUSED, radar.PATH_AUTO):
+        print(f"[case] scores n={n} n_cand={n_cand} G={G} d={d} pairs={pairs} path={path}",
+              flush=True)
+        out, sel, sc = _run(path, cfg, q, K, omega, summ, t, 256)
+        out2, sel2, sc2 = _run(path, half, q, K, omega.to(torch.bfloat16), summ, t, 256)
+        assert torch.equal(sel, sel2) and torch.equal(out, out2)
+        assert torch.equal(sc[..., :n_cand], sc2[..., :n_cand])
+        for h in heads:
+            s64 = H.f64(summ[0, h // G, :n_cand])
+            ref = orc.segment_scores(orc.random_features(H.f64(q[0, h]), H.f64(omega)), s64)
+            ids = sel[0, h, :n_cand].cpu().numpy()
+            assert sorted(ids) == list(range(n_cand))
+            err = np.max(np.abs(H.f64(sc[0, h, :n_cand]) - ref[ids]) / ref[ids])
+            assert err <= H.SCORE_TOL, (path, h, err)
