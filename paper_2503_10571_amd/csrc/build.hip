@@ -224,6 +224,10 @@ __global__ __launch_bounds__(256) void k_build_f32(
 // the waves never meet after the Omega barrier. Feature tile f + 1 is
 // multiplied while the exp2 epilogue of tile f runs (two accumulator sets);
 // B fragments are read one tile ahead.
+// With SPLIT (few long segments, where one wave's chain of blocks would be the
+// whole call) a workgroup takes an item: its waves take the 64-key blocks in
+// turn, and a segment's total adds the block sums in block order, as a wave
+// that walks the segment alone does, so both forms give the same bits.
 //
 // What bounds it is power: at two waves per SIMD the 64 MFMAs, 64 exp2, 64
 // fma and 64 adds of 64 keys x 64 features take the same time whether they
@@ -237,17 +241,19 @@ __global__ __launch_bounds__(256) void k_build_f32(
 // of batch 8 x 32 heads x 128K at n = 256, 615 -> 535 us for 4.2 M keys at
 // n = 512 and 94 -> 67 us for 131 K keys at n = 2048. Fetching the next
 // block ahead (n <= 256, where the registers allow it) is worth 2%.
-template <int D, int NF, int NW>
+template <int D, int NF, int NW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
     const bf16_t* __restrict__ K, const void* __restrict__ omega, bool obf,
     float* __restrict__ summ, int n, int c, int64_t cap, int64_t s_cap,
-    int seg_first, int seg_count, uint32_t n_items, float s1, float s2,
+    int seg_first, int seg_count, uint32_t item0, uint32_t n_items, float s1, float s2,
     float out_scale, const int64_t* __restrict__ pos, int Hkv, int n_sink) {
   constexpr int KB = D / 32;               // MFMA steps per product
   constexpr int NS = 4;                    // 16-key sub-tiles per block
   constexpr bool kAhead = NF <= 16;        // registers for two blocks of keys
   __shared__ __attribute__((aligned(16))) uint4 om_lds[NF * KB * 64];
   __shared__ __attribute__((aligned(16))) float nrm_lds[NW][NS * 16];
+  // SPLIT: a round's block sums, two rounds' worth
+  __shared__ float bsum[SPLIT ? 2 : 1][SPLIT ? NW : 1][SPLIT ? NF : 1][64];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -255,7 +261,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
   const int col = lane & 15;
   const int grp = lane >> 4;
   const int fbase = blockIdx.y * (16 * NF);
-  const uint32_t stride = gridDim.x * NW;
+  const uint32_t stride = SPLIT ? gridDim.x : gridDim.x * NW;
 
   // the segment of an item: seg_first + item % seg_count, or, with pos (item
   // = (b, kv head), one per-sequence segment close), the segment that row
@@ -275,7 +281,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
     return K + ((int64_t)(it / (uint32_t)seg_count) * cap + (int64_t)seg_of(it) * c) * D;
   };
 
-  uint32_t item = next_active(blockIdx.x * NW + wave);
+  // items [item0, n_items) of the call
+  uint32_t item = next_active(item0 + (SPLIT ? blockIdx.x : blockIdx.x * NW + wave));
   // a workgroup without a segment to close leaves before it reads Omega
   if (pos && !__syncthreads_or(item < n_items)) return;
 
@@ -297,7 +304,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
   const bf16_t* base = nullptr;
   if (item < n_items) {
     base = item_base(item);
-    fetch(keys, base, 0);
+    const int first = SPLIT ? wave * NS * 16 : 0;
+    if (first < c) fetch(keys, base, first);
   }
 
   // Omega slice -> B fragments in LDS: fragment (f, kb), lane (col, grp):
@@ -320,12 +328,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
   }
   __syncthreads();
 
-  float psum[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) psum[f] = 0.f;
-
-  // ST sub-tiles of 16 keys, the first `valid` of them real
-  auto compute = [&](const uint4 (&A)[NS][KB], int valid, auto st_tag) {
+  // ST sub-tiles of 16 keys, the first `valid` of them real; put(f, sum of
+  // this lane's elements of feature tile f)
+  auto block = [&](const uint4 (&A)[NS][KB], int valid, auto st_tag, auto&& put) {
     constexpr int ST = decltype(st_tag)::value;
     // |k|^2 s2 of the block's 64 keys: every lane sums its 16-byte chunks of
     // a key, the four k-slot groups are added, and LDS turns the column
@@ -373,7 +378,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
         for (int kb = 0; kb < KB; ++kb)
           b[(f + 1) & 1][kb] = om_lds[((f + 1) * KB + kb) * 64 + lane];
       }
-      float x[NE];
+      float x[NE], sum = 0.f;
 #pragma unroll
       for (int q = 0; q < SLOTS; ++q) {
         if (f < NF && q < NP) {
@@ -386,12 +391,73 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
         if (f > 0) {
           if (q < NE) x[q] = fmaf(acc[(f - 1) & 1][q / 4][q % 4], s1, -nb[q / 4][q % 4]);
           if (q >= 1 && q - 1 < NE) x[q - 1] = fast_exp2(x[q - 1]);
-          if (q >= 2 && q - 2 < NE) psum[f - 1] += x[q - 2];
+          if (q == 2) sum = x[0];
+          if (q > 2 && q - 2 < NE) sum += x[q - 2];
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+      if (f > 0) put(f - 1, sum);
     }
   };
+  // a remainder of at most 32 keys takes half a block's products
+  auto compute = [&](const uint4 (&A)[NS][KB], int valid, auto&& put) {
+    if (valid > 32) block(A, valid, std::integral_constant<int, NS>{}, put);
+    else block(A, valid, std::integral_constant<int, 2>{}, put);
+  };
+
+  if constexpr (SPLIT) {
+    constexpr int OWN = (NF + NW - 1) / NW;      // feature tiles a wave adds up
+    const int nblk = (c + NS * 16 - 1) / (NS * 16);
+    int buf = 0;
+    while (item < n_items) {               // workgroup-uniform
+      const uint32_t nitem = next_active(item + stride);
+      const bf16_t* nbase = nitem < n_items ? item_base(nitem) : nullptr;
+      float tot[OWN];
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) tot[i] = 0.f;
+      for (int b0 = 0; b0 < nblk; b0 += NW, buf ^= 1) {
+        const int blk = b0 + wave;
+        uint4 next[NS][KB];
+        const bool more = blk + NW < nblk;
+        if (more) fetch(next, base, (blk + NW) * NS * 16);
+        if (blk < nblk)
+          compute(keys, c - blk * NS * 16, [&](int f, float v) { bsum[buf][wave][f][lane] = v; });
+        if (more) {
+#pragma unroll
+          for (int st = 0; st < NS; ++st)
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) keys[st][kb] = next[st][kb];
+        }
+        // (the buffer's readers of two rounds ago passed the last barrier)
+        __syncthreads();
+        const int here = min(NW, nblk - b0);
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+          const int f = wave + i * NW;
+          if (f < NF)
+            for (int w = 0; w < here; ++w) tot[i] += bsum[buf][w][f][lane];
+        }
+      }
+      if (nbase && wave < nblk) fetch(keys, nbase, wave * NS * 16);
+      float* dst = summ + ((int64_t)(item / (uint32_t)seg_count) * s_cap + seg_of(item)) * n + fbase;
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) {
+        const int f = wave + i * NW;
+        float v = tot[i];
+        v = xor_sum<16>(v);
+        v = xor_sum<32>(v);
+        if (f < NF && lane < 16) dst[f * 16 + col] = v * out_scale;
+      }
+      item = nitem;
+      base = nbase;
+    }
+    return;
+  }
+
+  float psum[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) psum[f] = 0.f;
+  auto add = [&](int f, float v) { psum[f] += v; };
 
   // one block of `cur`; the next block's keys go to `nxt` (the same
   // registers where there is no room for two blocks)
@@ -407,9 +473,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
       if (item < n_items) base = item_base(item);
     }
     if (kAhead && item < n_items) fetch(nxt, base, off);
-    // a remainder of at most 32 keys takes half a block's products
-    if (c - o > 32) compute(cur, c - o, std::integral_constant<int, NS>{});
-    else compute(cur, c - o, std::integral_constant<int, 2>{});
+    compute(cur, c - o, add);
     if (!kAhead && item < n_items) fetch(nxt, base, off);
     if (last) {
       float* dst = summ + ((int64_t)(it / (uint32_t)seg_count) * s_cap + seg_of(it)) * n + fbase;
@@ -435,32 +499,115 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
   }
 }
 
-// Features per workgroup (16 NF): as many as n has, up to 512 (each key is
-// read once per slice), halved while the call has too few (segment, slice)
-// items to give every SIMD two waves. A feature's sum does not depend on the
-// slice, so a segment close and a rebuild agree bit for bit.
-template <int D, int NF>
-radar_status launch_build_bf16(const Shape& s, const void* K, const void* omega,
-                               float* summ, int seg_first, int seg_count,
-                               const int64_t* pos, hipStream_t st) {
-  const int64_t items = (int64_t)s.B * s.Hkv * seg_count;
-  if constexpr (NF > 2) {
-    if (16 * NF > s.n || items * (s.n / (16 * NF)) < 8 * num_cu())
-      return launch_build_bf16<D, NF / 2>(s, K, omega, summ, seg_first, seg_count, pos, st);
+// Features per workgroup (16 nf), waves per workgroup and whether they share
+// a segment, by the time the call should take: rounds of the persistent grid,
+// times 64-key blocks per wave, times a wave's time per block. The last was
+// measured at d = 128 (us, for nf = 2, 4, 8, 16, 32) with two waves per SIMD
+// and with one: below nf = 8 the keys' way through the L1 bounds it, above it
+// the products, so wide slices win where there is work for every wave (4.2 M
+// keys at n = 512: 548 us at nf = 32, 705 at 8, 1852 at 2), narrow ones or
+// split segments where there is not (36 segments of 647 keys at n = 1024: 19 us
+// at nf = 16 split eight ways, 27 at nf = 4 and 138 at nf = 32 unsplit; 340 of
+// 700 at n = 512: 52 split at nf = 16, 58 at 8 and 145 at 32 unsplit). The
+// estimate is within 15% of those; d = 64 keeps the order. A feature's sum
+// depends on none of this, so a segment close and a rebuild agree bit for bit.
+struct BuildPlan {
+  int nf, nw;
+  bool split;
+  int64_t per_round;   // items of a full round of the grid
+  float us;            // estimate
+};
+BuildPlan build_plan(int64_t items, int n, int c) {
+  constexpr float kTwo[] = {3.4f, 3.5f, 5.2f, 8.6f, 16.1f};
+  constexpr float kOne[] = {2.0f, 2.2f, 3.2f, 5.5f, 10.0f};
+  const int64_t cus = num_cu(), nblk = ceil_div(c, 64);
+  BuildPlan best{2, 4, false, 1, INFINITY};
+  for (int i = 0; i < 5 && (32 << i) <= n; ++i) {
+    const int nf = 2 << i;
+    for (int split = 0; split < 3; ++split) {  // no, over 4 waves, over 8
+      const int nw = split ? 4 * split : nf >= 16 ? 8 : 4;
+      if (split && (nf > 16 || nblk < 2 || (split == 2 && nblk <= 4))) continue;
+      const int64_t slices = n / (16 * nf);
+      // (a split workgroup of nf = 16 has 96 KB of LDS or more)
+      const int64_t slots =
+          std::max<int64_t>(1, (nw == 8 || (split && nf == 16) ? 1 : 2) * cus / slices);
+      const int64_t groups = split ? items : ceil_div(items, nw);
+      const int64_t gx = std::min(groups, slots);
+      const int64_t rounds = ceil_div(groups, gx) * (split ? ceil_div(nblk, nw) : nblk);
+      const bool one = nw == 4 && (gx * slices <= cus || (split && nf == 16));
+      const float us = (float)rounds * (one ? kOne[i] : kTwo[i]) + 0.15f * (float)nf;
+      if (us < best.us) best = {nf, nw, split != 0, gx * (split ? 1 : nw), us};
+    }
   }
-  if (items == 0) return RADAR_OK;
-  if (items >= ((int64_t)1 << 31)) return RADAR_EUNSUPPORTED;   // 32-bit item ids
-  constexpr int NW = NF >= 16 ? 8 : 4;     // 8 waves share 64 or 128 KB of Omega
+  return best;
+}
+
+template <int D, int NF, int NW, bool SPLIT>
+void launch_build_bf16(const Shape& s, const void* K, const void* omega, float* summ,
+                       int seg_first, int seg_count, int64_t item0, int64_t items,
+                       const int64_t* pos, hipStream_t st) {
   const int slices = s.n / (16 * NF);
   const int64_t resident = std::max<int64_t>(1, (8 / NW) * (int64_t)num_cu() / slices);
-  const int64_t gx = std::min<int64_t>(ceil_div(items, NW), resident);
+  const int64_t todo = items - item0;
+  const int64_t gx = std::min<int64_t>(SPLIT ? todo : ceil_div(todo, NW), resident);
   const float s1 = kLog2e / std::pow((float)s.d, 0.25f);
   const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
   const float out_scale = 1.f / ((float)s.c * std::sqrt((float)s.n));
-  launch(RADAR_K_BUILD, k_build_bf16<D, NF, NW>, dim3((unsigned)gx, (unsigned)slices),
+  launch(RADAR_K_BUILD, k_build_bf16<D, NF, NW, SPLIT>, dim3((unsigned)gx, (unsigned)slices),
          dim3(64 * NW), 0, st, reinterpret_cast<const bf16_t*>(K), omega, s.obf, summ, s.n, s.c,
-         s.cap, s.s_cap, seg_first, seg_count, (uint32_t)items, s1, s2, out_scale, pos, s.Hkv,
-         s.n_sink);
+         s.cap, s.s_cap, seg_first, seg_count, (uint32_t)item0, (uint32_t)items, s1, s2,
+         out_scale, pos, s.Hkv, s.n_sink);
+}
+
+// items [item0, items) of the call by plan p
+template <int D>
+void launch_build_plan(const BuildPlan& p, const Shape& s, const void* K, const void* omega,
+                       float* summ, int seg_first, int seg_count, int64_t item0, int64_t items,
+                       const int64_t* pos, hipStream_t st) {
+  auto go = [&](auto f, auto w, auto sp) {
+    launch_build_bf16<D, decltype(f)::value, decltype(w)::value, decltype(sp)::value>(
+        s, K, omega, summ, seg_first, seg_count, item0, items, pos, st);
+  };
+  auto go_f = [&](auto f) {
+    constexpr int NF = decltype(f)::value;
+    if constexpr (NF <= 16) {
+      if (p.split && p.nw == 4) return go(f, std::integral_constant<int, 4>{}, std::true_type{});
+      if (p.split) return go(f, std::integral_constant<int, 8>{}, std::true_type{});
+    }
+    // 8 waves share 64 or 128 KB of Omega where a wave takes a segment
+    return go(f, std::integral_constant<int, NF >= 16 ? 8 : 4>{}, std::false_type{});
+  };
+  switch (p.nf) {
+    case 2: return go_f(std::integral_constant<int, 2>{});
+    case 4: return go_f(std::integral_constant<int, 4>{});
+    case 8: return go_f(std::integral_constant<int, 8>{});
+    case 16: return go_f(std::integral_constant<int, 16>{});
+    default: return go_f(std::integral_constant<int, 32>{});
+  }
+}
+
+template <int D>
+radar_status launch_build_bf16_any(const Shape& s, const void* K, const void* omega,
+                                   float* summ, int seg_first, int seg_count,
+                                   const int64_t* pos, hipStream_t st) {
+  const int64_t items = (int64_t)s.B * s.Hkv * seg_count;
+  if (items == 0) return RADAR_OK;
+  if (items >= ((int64_t)1 << 31)) return RADAR_EUNSUPPORTED;   // 32-bit item ids
+  const BuildPlan p = build_plan(items, s.n, s.c);
+  // a last round that is mostly empty goes to a launch of its own with a plan
+  // for few items, where the estimates say that it pays for the launch (4256
+  // segments of 300 keys, d = 64, n = 256: 81 us, one launch 95)
+  const int64_t full = items / p.per_round * p.per_round;
+  if (full > 0 && full < items) {
+    const BuildPlan rest = build_plan(items - full, s.n, s.c);
+    const BuildPlan most = build_plan(full, s.n, s.c);
+    if (most.us + rest.us + 4.f < p.us) {
+      launch_build_plan<D>(most, s, K, omega, summ, seg_first, seg_count, 0, full, pos, st);
+      launch_build_plan<D>(rest, s, K, omega, summ, seg_first, seg_count, full, items, pos, st);
+      return launch_status();
+    }
+  }
+  launch_build_plan<D>(p, s, K, omega, summ, seg_first, seg_count, 0, items, pos, st);
   return launch_status();
 }
 
@@ -501,8 +648,8 @@ radar_status launch_build(const Shape& s, const void* K, const void* omega,
                           float* summ, int seg_first, int seg_count,
                           const int64_t* pos, hipStream_t st) {
   if (s.dt == RADAR_BF16)
-    return s.d == 64 ? launch_build_bf16<64, 32>(s, K, omega, summ, seg_first, seg_count, pos, st)
-                     : launch_build_bf16<128, 32>(s, K, omega, summ, seg_first, seg_count, pos, st);
+    return s.d == 64 ? launch_build_bf16_any<64>(s, K, omega, summ, seg_first, seg_count, pos, st)
+                     : launch_build_bf16_any<128>(s, K, omega, summ, seg_first, seg_count, pos, st);
   return s.d == 64 ? launch_build_f32<64, 8>(s, K, omega, summ, seg_first, seg_count, pos, st)
                    : launch_build_f32<128, 4>(s, K, omega, summ, seg_first, seg_count, pos, st);
 }

@@ -64,6 +64,25 @@ def test_slice_widths(n, segs):
     _check(cfg, K, omega, t, summ, [0, 7])
 
 
+@pytest.mark.parametrize("c,n,d,pairs,segs", [
+    (300, 256, 64, 16, 266), (300, 256, 128, 8, 300), (129, 512, 128, 3, 198), (647, 1024, 128, 6, 6),
+    (100, 128, 64, 32, 120), (70, 2048, 128, 4, 35), (1000, 64, 128, 2, 9), (64, 256, 128, 16, 129)])
+def test_plans_agree(c, n, d, pairs, segs):
+    """One pair alone (few items: narrow slices, segments split over waves)
+    and all pairs together (wide slices, a wave per segment, a last round in a
+    launch of its own) give the same bits."""
+    print(f"[case] plans c={c} n={n} d={d} pairs={pairs} segs={segs}", flush=True)
+    cfg, K, omega, t = _case(c, n, d, pairs, segs, seed=c)
+    summ = radar.new_summaries(cfg, "cuda")
+    radar.build_index(cfg, K, omega, t, summ)
+    _check(cfg, K, omega, min(t, 3 * c), summ[:, :, :3], [0])
+    one = dataclasses.replace(cfg, n_q_heads=1, n_kv_heads=1)
+    for p in {0, pairs // 2, pairs - 1}:
+        alone = radar.new_summaries(one, "cuda")
+        radar.build_index(one, K[:, p].contiguous(), omega, t, alone)
+        assert torch.equal(alone[0, 0], summ[0, p]), p
+
+
 @pytest.mark.parametrize("c,n,d", [(33, 64, 64), (100, 256, 128), (64, 512, 128), (130, 2048, 64)])
 def test_close_equals_rebuild(c, n, d):
     print(f"[case] close c={c} n={n} d={d}", flush=True)
