@@ -58,7 +58,6 @@ __global__ __launch_bounds__(512) void k_decode_fused(
   constexpr bool SEL = MODE == kFusedSelect;
   constexpr bool SCORED = MODE == kFusedScored;
   constexpr int NW = kFusedWaves;
-  constexpr int QPL = D / 16;              // q elements per lane (phase 1)
   constexpr int FPL = N / 64;              // features per lane (phase 2)
   using TA = Tile<T, D, G>;
   // One LDS area serves the phases in turn: phi(q), the scores and the top-k
@@ -66,7 +65,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
   // waves' accumulators at the end. The waves that attend window tiles
   // beside the top-k are those >= G: their K rows lie past the first part
   // (at d = 64 with many features all K rows follow it).
-  constexpr int SEL_BYTES = (SCORED ? 0 : G * (N + kFusedMaxCand) * 4) + G * kMaxK * 8;
+  constexpr int SEL_BYTES = G * ((SCORED ? 0 : N) + kFusedMaxCand) * 4 + G * kMaxK * 8;
   constexpr int MRG_BYTES = NW * G * D * 4;
   constexpr int KROWS = SEL ? 0 : NW * TA::kLdsBytes;
   constexpr int KOFF = SEL_BYTES <= G * TA::kLdsBytes ? 0 : SEL_BYTES;
@@ -82,7 +81,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
   __shared__ int ucnt_lds;
   u64* list_lds = reinterpret_cast<u64*>(area);          // [G][kMaxK]
   float* phq = reinterpret_cast<float*>(area + G * kMaxK * 8);   // [G][N]
-  float* sc = phq + G * N;                               // [G][kFusedMaxCand]
+  float* sc = phq + (SCORED ? 0 : G * N);                // [G][kFusedMaxCand]
   float* wacc = reinterpret_cast<float*>(area);          // [NW][G][D]
 
   const int tid = threadIdx.x;
@@ -160,112 +159,39 @@ __global__ __launch_bounds__(512) void k_decode_fused(
 
     // ---- 1. phi(q) -----------------------------------------------------
     // 16 lanes per Omega row, 4 rows per wave and pass, NP passes in chunks
-    // of at most 8 (PhiBf16; one fma chain per feature and head for fp32
-    // caches). The first chunk's Omega loads go out first, then q, then the
-    // summary rows (when they fit in registers next to them). For bf16 caches
-    // the phase is compiled once per Omega storage type and one copy runs, so
-    // all those loads stay in flight together.
+    // of at most 8. The first chunk's Omega loads go out first, then q, then
+    // the summary rows (when they fit in registers next to them). For bf16
+    // caches the phase is compiled once per Omega storage type and one copy
+    // runs, so all those loads stay in flight together.
     const int rb0 = wave * 16 * RB;
-    if constexpr (sizeof(T) == 2) {
-      auto phase1 = [&](auto bf_tag) {
-        constexpr bool BF = decltype(bf_tag)::value;
-        constexpr int NP = N / (4 * NW);
-        constexpr int PC = NP < 8 ? NP : 8;
-        using PM = PhiBf16<D, G, PC>;
-        PM pm;
+    auto phase1 = [&](auto bf_tag) {
+      constexpr bool BF = decltype(bf_tag)::value;
+      constexpr int NP = N / (4 * NW);
+      constexpr int PC = NP < 8 ? NP : 8;
+      using PM = PhiRows<T, D, G, PC>;
+      PM pm;
 #pragma unroll
-        for (int c0 = 0; c0 < NP; c0 += PC) {
-          typename PM::template Om<BF> om;
-          PM::template load<BF>(om, omega, c0 * 4 * NW + wave * 4 + (lane >> 4), 4 * NW, lane);
-          if (c0 == 0) {
-            pm.load_q(q0, lane);
-            // rows clamp to the last candidate; a wave whose first row is
-            // past it has no rows (the candidate count is uniform)
-            if (N <= 256 && rb0 < n_cand) load_rows(rb0);
-            pm.norm(s2, lane);
-          }
-          pm.template features<BF>(om, s1, inv_sqrt_n, lane, [&](int g, int p, float v) {
-            phq[g * N + (c0 + p) * 4 * NW + wave * 4 + (lane >> 4)] = v;
-          });
+      for (int c0 = 0; c0 < NP; c0 += PC) {
+        typename PM::template Om<BF> om;
+        PM::template load<BF>(om, omega, c0 * 4 * NW + wave * 4 + (lane >> 4), 4 * NW, lane);
+        if (c0 == 0) {
+          pm.load_q(q0, lane);
+          // rows clamp to the last candidate; a wave whose first row is
+          // past it has no rows (the candidate count is uniform)
+          if (N <= 256 && rb0 < n_cand) load_rows(rb0);
+          pm.norm(s2, lane);
         }
-        if (N == 512 && rb0 < n_cand) load_rows(rb0);
-      };
+        pm.template features<BF>(om, s1, inv_sqrt_n, lane, [&](int g, int p, float v) {
+          phq[g * N + (c0 + p) * 4 * NW + wave * 4 + (lane >> 4)] = v;
+        });
+      }
+      if (N == 512 && rb0 < n_cand) load_rows(rb0);
+    };
+    if constexpr (sizeof(T) == 2) {
       if (obf) phase1(std::true_type{});
       else phase1(std::false_type{});
     } else {
-      constexpr int NP = N / (4 * NW);       // passes
-      constexpr int PC = NP < 8 ? NP : 8;    // passes per load chunk
-      constexpr bool kPrefetch = NP <= 8;
-      const int r = lane >> 4, jj = lane & 15;
-      float qv[G][QPL], nrm[G];
-      // above n = 512 each chunk's features go to LDS at once (all NP
-      // passes would not fit in registers)
-      constexpr bool kChunkOut = N > 512;
-      float ph[kChunkOut ? PC : NP][G];
-#pragma unroll
-      for (int c0 = 0; c0 < NP; c0 += PC) {
-        uint4 om[PC][QPL / 4];
-        load_omega_rows<PC, QPL>(om, static_cast<const float*>(omega), [&](int p) {
-          return (int64_t)((c0 + p) * 4 * NW + wave * 4 + r) * D + jj * QPL;
-        });
-        if (c0 == 0) {
-#pragma unroll
-          for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int e = 0; e < QPL; ++e) qv[g][e] = q0[g * D + jj * QPL + e];
-        }
-        // rows clamp to the last candidate; a wave whose first row is past
-        // it has no rows (the candidate count is uniform)
-        if (kPrefetch && c0 == 0 && rb0 < n_cand) load_rows(rb0);
-        if (c0 == 0) {
-#pragma unroll
-          for (int g = 0; g < G; ++g) {
-            float sq = 0.f;
-#pragma unroll
-            for (int e = 0; e < QPL; ++e) sq = fmaf(qv[g][e], qv[g][e], sq);
-            nrm[g] = row_sum(sq);
-          }
-        }
-#pragma unroll
-        for (int p = 0; p < PC; ++p) {
-          float a[G];
-#pragma unroll
-          for (int g = 0; g < G; ++g) a[g] = 0.f;
-#pragma unroll
-          for (int e4 = 0; e4 < QPL / 4; ++e4) {
-            const float4 o = omega_f4(om[p][e4]);
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-              a[g] = fmaf(o.x, qv[g][4 * e4], a[g]);
-              a[g] = fmaf(o.y, qv[g][4 * e4 + 1], a[g]);
-              a[g] = fmaf(o.z, qv[g][4 * e4 + 2], a[g]);
-              a[g] = fmaf(o.w, qv[g][4 * e4 + 3], a[g]);
-            }
-          }
-#pragma unroll
-          for (int g = 0; g < G; ++g)
-            ph[kChunkOut ? p : c0 + p][g] =
-                fast_exp2(fmaf(row_sum(a[g]), s1, -nrm[g] * s2)) * inv_sqrt_n;
-        }
-        if constexpr (kChunkOut) {
-          if (jj == 0) {
-#pragma unroll
-            for (int p = 0; p < PC; ++p)
-#pragma unroll
-              for (int g = 0; g < G; ++g)
-                phq[g * N + (c0 + p) * 4 * NW + wave * 4 + r] = ph[p][g];
-          }
-        }
-      }
-      if constexpr (!kChunkOut) {
-        if (!kPrefetch && rb0 < n_cand) load_rows(rb0);
-        if (jj == 0) {
-#pragma unroll
-          for (int p = 0; p < NP; ++p)
-#pragma unroll
-            for (int g = 0; g < G; ++g) phq[g * N + p * 4 * NW + wave * 4 + r] = ph[p][g];
-        }
-      }
+      phase1(std::false_type{});
     }
     __syncthreads();
     stamp(1);
@@ -392,18 +318,21 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     float* sco = sel_scores && rj == 0 ? sel_scores + (b * Hq + hq) * (int64_t)k : nullptr;
     const float* src = SCORED ? gscores + (b * Hq + hq) * (int64_t)nc_cap
                               : sc + wave * kFusedMaxCand;
+    if (SCORED && nsl > 1) {               // uniform; n_cand <= kFusedMaxCand
+      add_slices(src, nsl, sl_stride, n_cand, sc + wave * kFusedMaxCand, lane);
+      src = sc + wave * kFusedMaxCand;
+    }
     int* row = sel_lds + wave * k_eff;
     u64* list = list_lds + wave * kMaxK;
     const int npl = (n_cand + 63) / 64;
-    const int nsl_ = SCORED ? nsl : 1;
-    if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
-    else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
-    else if (npl <= 4) head_topk<4>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
-    else if (npl <= 8) head_topk<8>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
+    if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    else if (npl <= 4) head_topk<4>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    else if (npl <= 8) head_topk<8>(src, n_cand, k, k_eff, row, so, sco, lane, list);
     else if (!SCORED || npl <= 16)
-      head_topk<16>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
+      head_topk<16>(src, n_cand, k, k_eff, row, so, sco, lane, list);
     else if constexpr (SCORED)             // up to 2048 candidates
-      head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl_, sl_stride);
+      head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list);
   } else if constexpr (!SEL) {
     ta.run(K, V, rj + (wave - G) * R, extra_tiles, (NW - G) * R, krows, extra_tile);
   }
@@ -518,16 +447,16 @@ radar_status launch_fused_td(const FusedArgs& a) {
   }
 }
 
-// fp32 caches with d = 128 have no fused or scored instantiation (their
-// tiles need more registers than the fused kernel has to spare): the select
-// kernel serves them, and the host never asks for the others
+// fp32 caches with d = 128 have no instantiation of the whole step (reading
+// 16 KB of Omega per 32 features in every workgroup costs more than the two
+// score kernels' launch): the host asks for their selection or scored modes
 template <int MODE>
 radar_status launch_fused_mode(const FusedArgs& a) {
   const Shape& s = *a.s;
   if (s.dt == RADAR_BF16)
     return s.d == 64 ? launch_fused_td<bf16_t, 64, MODE>(a) : launch_fused_td<bf16_t, 128, MODE>(a);
   if (s.d == 64) return launch_fused_td<float, 64, MODE>(a);
-  if constexpr (MODE == kFusedSelect) return launch_fused_td<float, 128, kFusedSelect>(a);
+  if constexpr (MODE != kFusedFull) return launch_fused_td<float, 128, MODE>(a);
   return RADAR_EUNSUPPORTED;
 }
 

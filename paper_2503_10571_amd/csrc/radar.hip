@@ -14,10 +14,9 @@
 //                  and merge. Its select-only instantiation (phases up to the
 //                  union) is the first kernel of the select path.
 //   k_phi_score    phi(q), Eq. 4, and the Eq. 6 scores of every candidate
-//                  segment for bf16 caches (split and scored paths): phi(q) of
-//                  a feature slice in LDS, HBM-bound GEMV over the fp32
-//                  summaries, DPP transpose-reduce.
-//   k_phi_q, k_score  the same as two kernels for fp32 caches.
+//                  segment (split and scored paths): phi(q) of a feature slice
+//                  in LDS, HBM-bound GEMV over the fp32 summaries, DPP
+//                  transpose-reduce.
 //   k_topk_union   per query head top-k (score desc, index asc) by radix
 //                  selection; per kv head sorted union of the group.
 //   k_segment_mass ln(beta_s), the exact attention mass of every candidate
@@ -210,8 +209,10 @@ WsLayout ws_layout(const Shape& s, int k) {
   L.maxwg = (int)ceil_div((int64_t)L.umax * L.tiles_per_seg + wt, 4);
   const size_t bh = (size_t)s.B * s.Hkv;
   size_t off = 0;
-  L.phiq = off;        off += align256((size_t)s.B * s.Hq * s.n * 4);
-  L.scores = off;      off += align256((size_t)s.B * s.Hq * std::max<int64_t>(1, s.s_cap) * 4);
+  // scores in feature slices (score_plan): n + capacity / c floats per head
+  L.scores = off;
+  off += align256((size_t)s.B * s.Hq * s.n * 4) +
+         align256((size_t)s.B * s.Hq * std::max<int64_t>(1, s.s_cap) * 4);
   L.uni = off;         off += align256(bh * L.umax * 4);
   L.ucnt = off;        off += align256(bh * 4);
   L.part = off;        off += align256(bh * L.maxwg * s.G * (s.d + 4) * 4);
@@ -400,14 +401,17 @@ radar_status plan_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
   p->path = choose_path(s, sa);
   p->ag = AttendGrid{0, 1};
   p->R = 1;
-  // The split path, chosen by the library for a group of eight on a bf16
-  // cache, runs its last stages as the scored path does: one launch instead
-  // of top-k and attention, and the attention of R workgroups per pair
-  // (measured 110 against 117 us for six ragged sequences of 32K tokens).
-  // Forced, it keeps its own kernels.
+  // The split path of a bf16 cache (a group of eight) and the split and
+  // select paths of an fp32 cache at d = 128 (groups of up to four), where
+  // the library chose them, run as the scored path does: phi(q) and scores
+  // chip-wide, then one launch instead of top-k and attention and R workgroups
+  // per pair (measured 110 against 117 us for six ragged bf16 sequences of 32K
+  // tokens with eight heads per group, 26.2 against 32.4 us for an fp32 cache of
+  // two sequences of 12K). Forced, the paths keep their own kernels.
+  const bool own = g_path_override != RADAR_PATH_AUTO;
   p->tail = p->path == RADAR_PATH_SCORED ||
-            (p->path == RADAR_PATH_SPLIT && g_path_override == RADAR_PATH_AUTO &&
-             s.dt == RADAR_BF16);
+            (!own && (p->path == RADAR_PATH_SPLIT || p->path == RADAR_PATH_SELECT) &&
+             (s.dt == RADAR_BF16 || s.G <= kFusedMaxG));
   if (p->path == RADAR_PATH_FUSED || p->tail) p->R = fused_ways(s, L, sa);
   if (p->path == RADAR_PATH_FUSED || p->path == RADAR_PATH_SCORED) return RADAR_OK;
   const int u_bound = std::min(s.G * top.k_eff, top.n_cand);
@@ -429,18 +433,16 @@ radar_status run_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
   if (plan.path == RADAR_PATH_FUSED)
     return launch_fused(s, q, Kp, Vp, omega, summaries, sa, out, selected, scores, ap,
                         plan.R, w, L, stream);
-  if (plan.path == RADAR_PATH_SELECT) {
+  if (plan.path == RADAR_PATH_SELECT && !plan.tail) {
     const radar_status r = launch_select(s, q, omega, summaries, sa, selected, scores,
                                          w, L, ap, stream);
     if (r != RADAR_OK) return r;
     return launch_attend(s, q, Kp, Vp, plan.ag, sa, out, w, L, stream);
   }
-  // (bf16 caches: the slices' scores fill both arrays)
-  float* phiq = reinterpret_cast<float*>(w + L.phiq);
-  float* sc = reinterpret_cast<float*>(w + (s.dt == RADAR_BF16 ? L.phiq : L.scores));
+  float* sc = reinterpret_cast<float*>(w + L.scores);
   const ScorePlan sp = score_plan(s, top.n_cand);
   if (top.n_cand > 0)
-    launch_scores(s, q, omega, summaries, phiq, sc, top.n_cand, sp, sa, stream);
+    launch_scores(s, q, omega, summaries, sc, top.n_cand, sp, sa, stream);
   if (plan.tail) {
     float* part = plan.R > 1 ? reinterpret_cast<float*>(w + L.part) : nullptr;
     const FusedArgs a{&s, q, Kp, Vp, omega, summaries, sa, out, selected, scores,

@@ -28,6 +28,7 @@ constexpr int kMaxK = 256;         // largest k accepted
 constexpr int kMaxG = 8;           // largest query-head group
 constexpr int kMaxCand = 2048;     // largest number of candidate segments
 constexpr int kMaxWg = 1024;       // largest attention split per (b, kv head)
+constexpr int kFusedMaxCand = 1024;   // candidates whose scores fit in LDS
 
 typedef uint16_t bf16_t;           // storage type of a bfloat16 value
 typedef unsigned long long u64;   // 64-bit type of the wave shuffles
@@ -182,23 +183,6 @@ __device__ __forceinline__ float4 ld_stream_f4(const float* p) {
   return make_float4(t.x, t.y, t.z, t.w);
 }
 
-// NR rows of QPL entries of an fp32 Omega (row_idx(p): element index of row
-// p's first entry), all loads issued together and kept as raw words (fp32
-// caches; bf16 ones read Omega, fp32 or bf16, into matrix operands)
-template <int NR, int QPL, typename F>
-__device__ __forceinline__ void load_omega_rows(uint4 (&raw)[NR][QPL / 4], const float* omega,
-                                                F&& row_idx) {
-#pragma unroll
-  for (int p = 0; p < NR; ++p)
-#pragma unroll
-    for (int e4 = 0; e4 < QPL / 4; ++e4)
-      raw[p][e4] = *reinterpret_cast<const uint4*>(omega + row_idx(p) + 4 * e4);
-}
-__device__ __forceinline__ float4 omega_f4(uint4 w) {
-  return make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z),
-                     __uint_as_float(w.w));
-}
-
 // ---------------------------------------------------------------------------
 // cross-lane exchanges
 // ---------------------------------------------------------------------------
@@ -212,6 +196,21 @@ constexpr int kDppHalfMirror = 0x141;
 constexpr int kDppMirror = 0x140;
 constexpr int kDppRowBcast0 = 0x150;
 constexpr int kDppRowRor0 = 0x120;         // + n: lane i of a row takes lane i - n mod 16
+
+// the value of lane l ^ MASK of the 16-lane row, for any MASK below 16
+template <int MASK>
+__device__ __forceinline__ float row_xor(float v) {
+  static_assert(MASK == 1 || MASK == 2 || MASK == 4 || MASK == 8, "distance");
+  const int x = __float_as_int(v);
+  if constexpr (MASK == 1) return __int_as_float(__builtin_amdgcn_mov_dpp(x, kDppQuadSwap1, 0xf, 0xf, true));
+  else if constexpr (MASK == 2) return __int_as_float(__builtin_amdgcn_mov_dpp(x, kDppQuadSwap2, 0xf, 0xf, true));
+  else if constexpr (MASK == 8) return __int_as_float(__builtin_amdgcn_mov_dpp(x, kDppRowRor0 + 8, 0xf, 0xf, true));
+  else {
+    // quads 0 and 2 take the quad above (row_shl:4), 1 and 3 the one below
+    const int up = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xf, 0x5, false);
+    return __int_as_float(__builtin_amdgcn_update_dpp(up, x, 0x114, 0xf, 0xa, false));
+  }
+}
 
 // compile-time loop: f(std::integral_constant<int, I>) for I = B .. E-1
 template <int B, int E, typename F>
@@ -416,34 +415,15 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
   return x + (row > 0 ? r0 : 0) + (row > 1 ? r1 : 0) + (row > 2 ? r2 : 0);
 }
 
-//
-// The scores may come in nsl slices of the features, `stride` floats apart,
-// that are added in slice order (several slices' loads in flight at once).
 template <int NPL>
 __device__ void head_topk(const float* __restrict__ src, int n_cand, int k,
                           int k_eff, int* sel_row, int32_t* sel_out,
-                          float* sc_out, int lane, u64* list, int nsl = 1,
-                          int64_t stride = 0) {
+                          float* sc_out, int lane, u64* list) {
   uint32_t u[NPL];                         // ordered score keys, 0 = absent
   if (n_cand > 0) {
     float v[NPL];
 #pragma unroll
     for (int m = 0; m < NPL; ++m) v[m] = src[min(m * 64 + lane, n_cand - 1)];
-    if (nsl > 1) {                         // uniform
-      constexpr int SG = NPL <= 2 ? 7 : NPL <= 8 ? 3 : 1;
-      for (int s0 = 1; s0 < nsl; s0 += SG) {
-        float x[SG][NPL];
-#pragma unroll
-        for (int z = 0; z < SG; ++z)
-#pragma unroll
-          for (int m = 0; m < NPL; ++m)
-            x[z][m] = src[min(s0 + z, nsl - 1) * stride + min(m * 64 + lane, n_cand - 1)];
-#pragma unroll
-        for (int z = 0; z < SG; ++z)
-#pragma unroll
-          for (int m = 0; m < NPL; ++m) v[m] += s0 + z < nsl ? x[z][m] : 0.f;
-      }
-    }
 #pragma unroll
     for (int m = 0; m < NPL; ++m)
       u[m] = (m * 64 + lane < n_cand) ? (uint32_t)(order_key(v[m], 0) >> 32) : 0u;
@@ -542,6 +522,33 @@ __device__ void head_topk(const float* __restrict__ src, int n_cand, int k,
   }
 }
 
+// One head's scores from nsl (2 to 8) slices of the features, `stride` floats
+// apart, added in slice order into dst (LDS) by one wave, up to 32 loads in
+// flight. Only where there are at most kFusedMaxCand candidates.
+__device__ __forceinline__ void add_slices(const float* __restrict__ src, int nsl, int64_t stride,
+                                           int n_cand, float* dst, int lane) {
+  for (int i0 = 0; i0 < n_cand; i0 += 4 * kWave) {
+    float x[8][4];
+#pragma unroll
+    for (int z = 0; z < 8; ++z)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        x[z][m] = src[min(z, nsl - 1) * stride + min(i0 + m * kWave + lane, n_cand - 1)];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      float v = x[0][m];
+#pragma unroll
+      for (int z = 1; z < 8; ++z) v = z < nsl ? v + x[z][m] : v;
+      const int i = i0 + m * kWave + lane;
+      if (i < n_cand) dst[i] = v;
+    }
+  }
+  // (the wave reads what it wrote)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Union of the group's selections: sel[h * per .. h * per + per) holds the
 // segment ids of head h < G (-1 = none, every other id < kMaxCand). The ids
 // are set in an LDS bitmap (one per head when masks are wanted); the first
@@ -619,16 +626,17 @@ struct TileRef {
 // RPI whole rows contiguously (rows past the tile end re-read its last row
 // and are masked). q.k partials (fma of the pre-scaled query) are
 // transpose-reduced so that each lane ends with one token's logit, softmax
-// runs across the wave, and p is broadcast back to the lanes that hold the
-// matching V chunks.
+// runs across the wave, and p is broadcast back (DPP row broadcast) to the
+// lanes that hold the matching V chunks. At d = 128 a tile is done in two
+// halves of 32 rows: 64 rows of K and V would take 256 registers.
 template <int D, int G>
 struct TileVec {
   static constexpr int kLdsBytes = 0;           // per wave
   static constexpr int EPL = 4;                 // elements per 16-byte chunk
-  static constexpr int LPR = D / EPL;           // lanes per row
+  static constexpr int LPR = D / EPL;           // lanes per row: 16 or 32
   static constexpr int RPI = kWave / LPR;       // rows per load instruction
-  static constexpr int ITER = kTile / RPI;      // load instructions per tile
-  static_assert(ITER == LPR, "tile shape");
+  static constexpr int ITER = 16;               // load instructions per pass
+  static constexpr int ROWS = ITER * RPI;       // rows per pass: 64 or 32
 
   float qf[G][EPL];
   float m[G], l[G], acc[G][EPL];
@@ -648,22 +656,24 @@ struct TileVec {
     }
   }
 
-  // (a head that has attended nothing yet keeps m = -inf, l = 0, acc = 0)
-  __device__ __forceinline__ void tile(const float* __restrict__ K, const float* __restrict__ V,
-                                       const TileRef& t) {
+  // rows [row0, row0 + len), len <= ROWS (a head that has attended nothing
+  // yet keeps m = -inf, l = 0, acc = 0)
+  __device__ __forceinline__ void pass(const float* __restrict__ K, const float* __restrict__ V,
+                                       int64_t row0, int len, unsigned hmask) {
     const int r = lane / LPR;
     const int jj = lane % LPR;
     uint4 kr[ITER], vr[ITER];
-    const float* kbase = K + t.row0 * D + jj * EPL;
-    const float* vbase = V + t.row0 * D + jj * EPL;
+    const float* kbase = K + row0 * D + jj * EPL;
+    const float* vbase = V + row0 * D + jj * EPL;
 #pragma unroll
     for (int i = 0; i < ITER; ++i)
-      kr[i] = ld_stream(kbase + (int64_t)min(i * RPI + r, t.len - 1) * D);
+      kr[i] = ld_stream(kbase + (int64_t)min(i * RPI + r, len - 1) * D);
 #pragma unroll
     for (int i = 0; i < ITER; ++i)
-      vr[i] = ld_stream(vbase + (int64_t)min(i * RPI + r, t.len - 1) * D);
+      vr[i] = ld_stream(vbase + (int64_t)min(i * RPI + r, len - 1) * D);
 
-    // logits: lane (r, jj) ends with the logit of tile row jj * RPI + r
+    // logits: lane (r, jj) ends with the logit of row (jj % 16) * RPI + r
+    // (at d = 128 lanes jj and jj + 16 both hold it)
     float lg[G];
     {
       float pl[G][ITER];
@@ -681,21 +691,21 @@ struct TileVec {
       }
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        transpose_reduce<LPR>(pl[g], lane);
-        lg[g] = pl[g][0];
+        transpose_reduce<16>(pl[g], lane);
+        lg[g] = LPR == 32 ? xor_sum<16>(pl[g][0]) : pl[g][0];
       }
     }
-    const bool mine_ok = (jj * RPI + r) < t.len;
+    const bool mine_ok = ((jj & 15) * RPI + r) < len;
     float p[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const bool on = mine_ok && ((t.hmask >> g) & 1u);
+      const bool on = mine_ok && ((hmask >> g) & 1u);
       const float mt = wave_max(on ? lg[g] : -INFINITY);
       const float mn = fmaxf(m[g], mt);
       const float mref = mn == -INFINITY ? 0.f : mn;
       const float scale = fast_exp2(m[g] - mref);  // 0 on the head's first tile
       p[g] = on ? fast_exp2(lg[g] - mref) : 0.f;
-      l[g] = fmaf(l[g], scale, wave_sum(p[g]));
+      l[g] = fmaf(l[g], scale, wave_sum(jj < 16 ? p[g] : 0.f));
       m[g] = mn;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) acc[g][e] *= scale;
@@ -706,16 +716,17 @@ struct TileVec {
       unpack16<float>(vr[i], vf);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        // p of row (i, r) lives in lane i of this lane's LPR-lane group
-        float pb;
-        if constexpr (LPR == 16)
-          pb = dpp_f<kDppRowBcast0 + i>(p[g]);
-        else
-          pb = __shfl(p[g], r * LPR + i);
+        // p of row (i, r) lives in lane i of every 16-lane row of the group
+        const float pb = dpp_f<kDppRowBcast0 + i>(p[g]);
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(pb, vf[e], acc[g][e]);
       }
     });
+  }
+  __device__ __forceinline__ void tile(const float* K, const float* V, const TileRef& t) {
+#pragma unroll 1
+    for (int off = 0; off < t.len; off += ROWS)
+      pass(K, V, t.row0 + off, min(ROWS, t.len - off), t.hmask);
   }
 
   // tiles first, first + step, ... < end of at(i); wave-uniform call
@@ -1032,27 +1043,28 @@ template <typename T, int D, int G>
 using Tile = typename std::conditional<sizeof(T) == 2, TileMfma<D, G>, TileVec<D, G>>::type;
 
 // ---------------------------------------------------------------------------
-// phi(q) of a group's heads (Eq. 4) for bf16 caches
+// phi(q) of a group's heads (Eq. 4)
 // ---------------------------------------------------------------------------
 // 16 lanes per Omega row, 4 rows per wave and pass: a lane multiplies its
-// D / 16 dims (v_dot2_f32_bf16 on the raw pairs; an fp32 Omega is rounded to
-// bf16 first), and the NP * G sums of a lane's passes and heads are
-// transpose-reduced over the 16 lanes, so each lane ends with one sum per 16
-// and the exponent, exp2 and store run once per feature and head. (One fma
-// chain, one 16-lane reduction and one exp2 in every lane per feature and
-// head, the form fp32 caches keep, is three times the instructions. The matrix
+// D / 16 dims (bf16 caches: v_dot2_f32_bf16 on the raw pairs, an fp32 Omega
+// rounded to bf16 first; fp32 caches: an fma chain), and the NP * G sums of a
+// lane's passes and heads are transpose-reduced over the 16 lanes, so each
+// lane ends with one sum per 16 and the exponent, exp2 and store run once per
+// feature and head. (A 16-lane reduction and an exp2 in every lane per feature
+// and head, the form before, is three times the instructions. The matrix
 // cores take fewer still, but their sums put the scores of a 512K context off
 // by 1e-6 where these are off by 2e-7, and reading Omega in operand layout, 16
 // rows per load, was 1 us slower.)
-template <int D, int G, int NP>
-struct PhiBf16 {
+template <typename T, int D, int G, int NP>
+struct PhiRows {
+  static constexpr bool HALF = sizeof(T) == 2;
   static constexpr int QPL = D / 16;       // dims per lane
-  static constexpr int W = QPL / 2;        // bf16 pairs per lane
+  static constexpr int W = HALF ? QPL / 2 : QPL;   // words of q or Omega per lane
   static constexpr int NVAL = NP * G;      // sums per lane
-  // NP passes of Omega rows in flight: raw words, as stored
+  // NP passes of Omega rows in flight: raw words, as stored (BF: bf16)
   template <bool BF> struct Om { uint32_t w[NP][BF ? W : QPL]; };
   uint32_t qw[G][W];
-  float nrm;                               // |q|^2 s2 of head lane % G
+  float nrm;                               // |q|^2 s2 of the head this lane ends with
 
   template <int NWORD>
   __device__ static __forceinline__ void load_words(uint32_t (&w)[NWORD], const void* src) {
@@ -1078,22 +1090,31 @@ struct PhiBf16 {
       else load_words(om.w[p], static_cast<const float*>(omega) + at);
     }
   }
-  __device__ __forceinline__ void load_q(const bf16_t* q0, int lane) {
+  __device__ __forceinline__ void load_q(const T* q0, int lane) {
 #pragma unroll
     for (int g = 0; g < G; ++g) load_words(qw[g], q0 + g * D + (lane & 15) * QPL);
   }
+  // the four bits of jj in reverse order
+  __device__ static __forceinline__ int reversed(int jj) {
+    return ((jj & 1) << 3) | ((jj & 2) << 1) | ((jj & 4) >> 1) | (jj >> 3);
+  }
   __device__ static __forceinline__ float dot(uint32_t a, uint32_t b, float c) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v_t, a),
-                                           __builtin_bit_cast(bf16x2v_t, b), c, false);
+    if constexpr (HALF)
+      return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v_t, a),
+                                             __builtin_bit_cast(bf16x2v_t, b), c, false);
+    else
+      return fmaf(__uint_as_float(a), __uint_as_float(b), c);
   }
   __device__ __forceinline__ void norm(float s2, int lane) {
+    constexpr int GRP = NVAL < 16 ? NVAL : 16;
+    const int mine = reversed(lane & 15) / (16 / GRP);   // its sum (features)
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       float sq = 0.f;
 #pragma unroll
       for (int i = 0; i < W; ++i) sq = dot(qw[g][i], qw[g][i], sq);
       sq = row_sum(sq) * s2;
-      nrm = g == 0 || lane % G == g ? sq : nrm;
+      nrm = g == 0 || mine % G == g ? sq : nrm;
     }
   }
   // phi of the loaded rows: put(head, pass, value)
@@ -1108,7 +1129,7 @@ struct PhiBf16 {
       uint32_t w[W];
 #pragma unroll
       for (int i = 0; i < W; ++i) {
-        if constexpr (BF) w[i] = om.w[p][i];
+        if constexpr (BF || !HALF) w[i] = om.w[p][i];
         else w[i] = f32_to_bf16(__uint_as_float(om.w[p][2 * i])) |
                     (f32_to_bf16(__uint_as_float(om.w[p][2 * i + 1])) << 16);
       }
@@ -1122,24 +1143,33 @@ struct PhiBf16 {
     }
 #pragma unroll
     for (int q = 0; q < NVAL / GRP; ++q) {
-      float* x = v + q * GRP;
-      // fewer than 16 sums: first add the lanes that share a place
-      if constexpr (GRP <= 8) {
+      // lowest lane bit first, so that every sum adds its 16 terms in the
+      // order of row_sum; lanes that share a sum keep adding
+      float x[GRP];
 #pragma unroll
-        for (int i = 0; i < GRP; ++i) x[i] += partner<8>(x[i], lane);
-      }
-      if constexpr (GRP <= 4) {
+      for (int i = 0; i < GRP; ++i) x[i] = v[q * GRP + i];
+      auto step = [&](auto mask, auto count) {
+        constexpr int M = decltype(mask)::value, C = decltype(count)::value;
+        if constexpr (C > 1) {
+          const bool up = (lane & M) != 0;
 #pragma unroll
-        for (int i = 0; i < GRP; ++i) x[i] += partner<4>(x[i], lane);
-      }
-      if constexpr (GRP <= 2) {
-#pragma unroll
-        for (int i = 0; i < GRP; ++i) x[i] += partner<2>(x[i], lane);
-      }
-      transpose_reduce<GRP>(x, lane);
-      const int at = q * GRP + jj % GRP;
+          for (int i = 0; i < C / 2; ++i) {
+            const float lo = x[i], hi = x[i + C / 2];
+            x[i] = (up ? hi : lo) + row_xor<M>(up ? lo : hi);
+          }
+        } else {
+          x[0] += row_xor<M>(x[0]);
+        }
+      };
+      step(std::integral_constant<int, 1>{}, std::integral_constant<int, GRP>{});
+      step(std::integral_constant<int, 2>{}, std::integral_constant<int, GRP / 2>{});
+      step(std::integral_constant<int, 4>{}, std::integral_constant<int, GRP / 4>{});
+      step(std::integral_constant<int, 8>{}, std::integral_constant<int, GRP / 8>{});
+      // the first lane bit chose the upper half of the sums, and so on
+      const int rev = reversed(jj);
+      const int at = q * GRP + rev / (16 / GRP);
       const float ph = fast_exp2(fmaf(x[0], s1, -nrm)) * inv_sqrt_n;
-      if (jj < GRP) put(at % G, at / G, ph);
+      if (rev % (16 / GRP) == 0) put(at % G, at / G, ph);
     }
   }
 };
@@ -1153,7 +1183,6 @@ constexpr int kFusedScored = 2;
 constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxG = 4;
 constexpr int kScoredMaxG = 8;     // bf16 caches (4 for fp32 ones)
-constexpr int kFusedMaxCand = 1024;
 
 // ---------------------------------------------------------------------------
 // host side
@@ -1214,7 +1243,7 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
-  size_t phiq, scores, uni, ucnt, part, total;
+  size_t scores, uni, ucnt, part, total;
   int umax, maxwg, tiles_per_seg;
 };
 
@@ -1250,16 +1279,15 @@ radar_status launch_build(const Shape& s, const void* K, const void* omega,
                           const int64_t* pos, hipStream_t st);
 
 // split.hip: the split path's stages
-// Eq. 6 scores of up to n_cand candidates of every query head into `sc`, in
-// ScorePlan's slices; bf16 caches in one kernel, fp32 ones in two (phi(q) to
-// `phiq` first)
+// phi(q) and Eq. 6 scores of up to n_cand candidates of every query head into
+// `sc`, in ScorePlan's slices
 struct ScorePlan {
   int nsl;             // slices of the features
   int64_t stride;      // floats between them
 };
 ScorePlan score_plan(const Shape& s, int n_cand);
 void launch_scores(const Shape& s, const void* q, const void* omega, const float* summ,
-                   float* phiq, float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
+                   float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
                    hipStream_t st);
 // ln(beta) of candidates [0, n_cand) into rows of nc_cap scores; with_rest
 // also the mass of the window and sinks at index n_cand

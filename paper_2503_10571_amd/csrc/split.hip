@@ -1,5 +1,5 @@
 // The split decode path's stages, each spread over the whole chip: phi(q) and
-// Eq. 6 scores (one kernel for bf16 caches, two for fp32 ones), the exact segment mass, top-k and union, the given-selection
+// Eq. 6 scores, the exact segment mass, top-k and union, the given-selection
 // union, the gather attention and the merge of its partials (also used by
 // the fused path when several workgroups share a pair).
 #include "radar_impl.h"
@@ -7,225 +7,8 @@
 namespace radar_impl {
 
 // ---------------------------------------------------------------------------
-// k_phi_q: phi(q) (Eq. 4) of the G query heads of one (b, kv head), one
-// block of 64 features per workgroup (fp32 caches)
-// ---------------------------------------------------------------------------
-// Grid (n / 64, B * Hkv): each workgroup reads only its 64 rows of Omega.
-// 16 lanes share one Omega row (D/16 floats each); wave w covers rows
-// 16 w .. 16 w + 15 in 4 passes of 4 rows, and the 4 partial sums of each
-// lane are reduced across its 16 lanes (transpose-reduce over 4 lanes, then
-// two butterflies), so lane jj < 4 of row group r ends with feature
-// 16 w + 4 jj + r.
-template <int D, int G>
-__global__ __launch_bounds__(256) void k_phi_q(const float* __restrict__ q,
-                                               const float* __restrict__ omega,
-                                               float* __restrict__ phiq,
-                                               int n, int Hq, int Hkv, float s1,
-                                               float s2, float inv_sqrt_n) {
-  constexpr int QPL = D / 16;              // q elements per lane
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int r = lane >> 4, jj = lane & 15;
-  const int64_t bh = blockIdx.y;
-  const int64_t b = bh / Hkv, hk = bh % Hkv;
-  const int64_t hq0 = b * Hq + hk * G;     // the group's first (b, q head)
-  const int f0 = blockIdx.x * 64 + wave * 16;
-
-  uint4 om[4][QPL / 4];
-  load_omega_rows<4, QPL>(om, omega, [&](int p) {
-    return (int64_t)(f0 + p * 4 + r) * D + jj * QPL;
-  });
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    float qv[QPL];
-#pragma unroll
-    for (int e = 0; e < QPL; ++e) qv[e] = q[(hq0 + g) * D + jj * QPL + e];
-    float nrm = 0.f;
-#pragma unroll
-    for (int e = 0; e < QPL; ++e) nrm = fmaf(qv[e], qv[e], nrm);
-    nrm = row_sum(nrm);
-    float part[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      float a = 0.f;
-#pragma unroll
-      for (int e4 = 0; e4 < QPL / 4; ++e4) {
-        const float4 o = omega_f4(om[p][e4]);
-        a = fmaf(o.x, qv[4 * e4], a);
-        a = fmaf(o.y, qv[4 * e4 + 1], a);
-        a = fmaf(o.z, qv[4 * e4 + 2], a);
-        a = fmaf(o.w, qv[4 * e4 + 3], a);
-      }
-      part[p] = a;
-    }
-    transpose_reduce<4>(part, lane);
-    float v = part[0];
-    v += __shfl_xor(v, 4);
-    v += __shfl_xor(v, 8);
-    if (jj < 4)
-      phiq[(hq0 + g) * n + f0 + jj * 4 + r] =
-          fast_exp2(fmaf(v, s1, -nrm * s2)) * inv_sqrt_n;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// k_score: a[h][s] = phi(q_h) . summ[s], Eq. 6 (fp32 caches)
-// ---------------------------------------------------------------------------
-// Workgroup = 1, 2 or 4 waves x (16 * RB) summary rows of one (b, kv head)
-// (fewer waves per workgroup when that spreads a small call over more CUs;
-// the waves are independent). Lane l holds FPL = n / 64 features of phi(q)
-// for the G heads of the group, in chunks of at most 8 (n = 1024 and 2048
-// take 2 to 8 chunks, so the rows of a batch fit in registers); each chunk
-// of a row is one contiguous wave load, and all of a batch's rows are loaded
-// before any is reduced. A 16-row batch is transpose-reduced inside each
-// 16-lane row with DPP, then summed over the four rows.
-// With S > 1 the S waves of a workgroup share one batch of rows instead and
-// each takes NCH / S of the chunks (one round trip to memory instead of
-// NCH / 2 for a wave that walks them all); the waves' row sums are added in
-// LDS in wave order.
-template <int N, int G, int S>
-__global__ __launch_bounds__(256) void k_score(const float* __restrict__ phiq,
-                                               const float* __restrict__ summ,
-                                               float* __restrict__ scores,
-                                               int Hq, int Hkv, SeqArgs sa,
-                                               int64_t s_cap, int nc_cap) {
-  constexpr int FPL = N / 64;
-  // features per lane per chunk: all of them up to n = 512; above, 8 (4
-  // for G >= 4, whose accumulators take more registers)
-  constexpr int FC = FPL <= 8 ? FPL : (G >= 4 ? 4 : 8);
-  constexpr int NCH = FPL / FC;            // chunks (1 for n <= 512)
-  constexpr int RB = N <= 256 ? 2 : 1;     // 16-row batches per wave
-  static_assert(NCH % S == 0 && (S == 1 || RB == 1), "feature split");
-  constexpr int CPW = NCH / S;             // chunks of each wave
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int64_t bh = blockIdx.y;
-  const int64_t b = bh / Hkv, hk = bh % Hkv;
-  const int n_cand = seq_span(sa, b).n_cand;
-  const int wrow0 = S > 1 ? blockIdx.x * 16
-                          : (blockIdx.x * (blockDim.x >> 6) + wave) * (16 * RB);
-  // wave-uniform, and workgroup-uniform with S > 1 (the waves share rows),
-  // so the barrier below is reached by all waves or by none
-  if (wrow0 >= n_cand) return;
-  const int ch0 = S > 1 ? wave * CPW : 0;  // this wave's first chunk
-
-  // chunk ch holds features ch * 64 * FC + lane * FC + e (e < FC) of lane
-  // `lane`, so each chunk of a row is one contiguous 64 * FC * 4-byte wave
-  // load; with one chunk (n <= 512) lane l holds features l * FPL .. + FPL
-  const float* base = summ + (bh * s_cap) * N + lane * FC;
-  // per row and head a running dot product over the chunks
-  float part[RB][G][16];
-#pragma unroll
-  for (int bt = 0; bt < RB; ++bt)
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) part[bt][g][r] = 0.f;
-  // a chunk's phi(q) features and rows
-  auto load_chunk = [&](int ch, float (&pq)[G][FC], float (&x)[RB][16][FC]) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float* src = phiq + ((b * Hq + hk * G + g) * N) + ch * 64 * FC + lane * FC;
-#pragma unroll
-      for (int e = 0; e < FC; ++e) pq[g][e] = src[e];
-    }
-#pragma unroll
-    for (int bt = 0; bt < RB; ++bt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = min(wrow0 + bt * 16 + r, n_cand - 1);
-        const float* src = base + (int64_t)row * N + ch * 64 * FC;
-        if constexpr (FC % 4 == 0) {
-#pragma unroll
-          for (int e = 0; e < FC; e += 4) {
-            const float4 v = ld_stream_f4(src + e);
-            x[bt][r][e] = v.x; x[bt][r][e + 1] = v.y;
-            x[bt][r][e + 2] = v.z; x[bt][r][e + 3] = v.w;
-          }
-        } else if constexpr (FC == 2) {
-          const float2 v = *reinterpret_cast<const float2*>(src);
-          x[bt][r][0] = v.x; x[bt][r][1] = v.y;
-        } else {
-          x[bt][r][0] = src[0];
-        }
-      }
-  };
-  auto add_chunk = [&](const float (&pq)[G][FC], const float (&x)[RB][16][FC]) {
-#pragma unroll
-    for (int bt = 0; bt < RB; ++bt)
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float a = part[bt][g][r];
-#pragma unroll
-          for (int e = 0; e < FC; ++e) a = fmaf(x[bt][r][e], pq[g][e], a);
-          part[bt][g][r] = a;
-        }
-  };
-  // Several chunks at G = 4 (four features per lane): two chunks in flight,
-  // the next one's loads issued before this one's products (same products,
-  // same order; 376 registers, one wave per SIMD, as these launches run);
-  // otherwise one chunk's rows live at a time (G = 8 would not fit).
-  constexpr bool kTwo = CPW > 1 && CPW % 2 == 0 && FC == 4 && G == 4;
-  if constexpr (kTwo) {
-    float pqa[G][FC], xa[RB][16][FC], pqb[G][FC], xb[RB][16][FC];
-    load_chunk(ch0, pqa, xa);
-#pragma unroll 1
-    for (int ch = ch0; ch < ch0 + CPW; ch += 2) {
-      load_chunk(ch + 1, pqb, xb);
-      __builtin_amdgcn_sched_barrier(0);
-      add_chunk(pqa, xa);
-      if (ch + 2 < ch0 + CPW) load_chunk(ch + 2, pqa, xa);
-      __builtin_amdgcn_sched_barrier(0);
-      add_chunk(pqb, xb);
-    }
-  } else {
-#pragma unroll 1
-    for (int ch = ch0; ch < ch0 + CPW; ++ch) {
-      float pq[G][FC], x[RB][16][FC];
-      load_chunk(ch, pq, x);
-      // with several chunks the compiler would sink each load to its first
-      // use and wait on one load at a time; keep the chunk's loads together
-      if constexpr (CPW > 1) __builtin_amdgcn_sched_barrier(0);
-      add_chunk(pq, x);
-    }
-  }
-  __shared__ float red[S > 1 ? S : 1][G][16];
-#pragma unroll
-  for (int bt = 0; bt < RB; ++bt) {
-    const int row = wrow0 + bt * 16 + (lane & 15);
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      transpose_reduce<16>(part[bt][g], lane);
-      float v = part[bt][g][0];
-      v = xor_sum<16>(v);
-      v = xor_sum<32>(v);
-      if constexpr (S > 1) {
-        if (lane < 16) red[wave][g][lane] = v;
-      } else {
-        if (lane < 16 && row < n_cand)
-          scores[(b * Hq + hk * G + g) * (int64_t)nc_cap + row] = v;
-      }
-    }
-  }
-  if constexpr (S > 1) {
-    __syncthreads();
-    if (wave == 0 && lane < 16 && wrow0 + lane < n_cand) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float v = red[0][g][lane];
-#pragma unroll
-        for (int w = 1; w < S; ++w) v += red[w][g][lane];
-        scores[(b * Hq + hk * G + g) * (int64_t)nc_cap + wrow0 + lane] = v;
-      }
-    }
-  }
-}
-
-
-// ---------------------------------------------------------------------------
-// k_phi_score: phi(q) and the Eq. 6 scores in one kernel (bf16 caches)
+// k_phi_score: phi(q) (Eq. 4) and the segment scores a[h][s] = phi(q_h) .
+// summ[s] (Eq. 6) in one kernel
 // ---------------------------------------------------------------------------
 // Grid (row groups, pairs, feature slices). A workgroup computes phi(q) of its
 // slice of fs features into LDS, with its first summary rows already in
@@ -239,9 +22,9 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ phiq,
 // 30.2 us (80.0 to 78.7 us at 512K, 104 to 101 us for six ragged sequences with
 // eight heads per group). Slices are what spreads few rows with many features
 // over the chip without every workgroup reading all of Omega.
-template <int D, int G, int FPL, int NW>
+template <typename T, int D, int G, int FPL, int NW>
 __global__ __launch_bounds__(64 * NW) void k_phi_score(
-    const bf16_t* __restrict__ q, const void* __restrict__ omega, bool obf,
+    const T* __restrict__ q, const void* __restrict__ omega, bool obf,
     const float* __restrict__ summ, float* __restrict__ scores, int Hq, int Hkv, int n, int fs,
     SeqArgs sa, int64_t s_cap, int nc_cap, int64_t sl_stride, float s1, float s2,
     float inv_sqrt_n) {
@@ -255,7 +38,7 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   const int n_cand = seq_span(sa, b).n_cand;
   if ((int)blockIdx.x * 16 * NW >= n_cand) return;     // workgroup-uniform
   const int f0 = blockIdx.z * fs;
-  const bf16_t* q0 = q + (b * Hq + hk * G) * D;
+  const T* q0 = q + (b * Hq + hk * G) * D;
   const float* base = summ + bh * s_cap * n + f0 + lane * FPL;
 
   float x[16][FPL];
@@ -280,8 +63,10 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   // product stay in flight together
   auto phi = [&](auto bf_tag) {
     constexpr bool BF = decltype(bf_tag)::value;
-    constexpr int NP = FC / (4 * NW) < 8 ? FC / (4 * NW) : 8;
-    using PM = PhiBf16<D, G, NP>;
+    // (fp32 words of eight heads: half the passes, for the registers)
+    constexpr int kMost = sizeof(T) == 4 && G == 8 ? 4 : 8;
+    constexpr int NP = FC / (4 * NW) < kMost ? FC / (4 * NW) : kMost;
+    using PM = PhiRows<T, D, G, NP>;
     PM pm;
     for (int c0 = 0; c0 < fs; c0 += NP * 4 * NW) {
       typename PM::template Om<BF> om;
@@ -297,8 +82,12 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
       });
     }
   };
-  if (obf) phi(std::true_type{});
-  else phi(std::false_type{});
+  if constexpr (sizeof(T) == 2) {
+    if (obf) phi(std::true_type{});
+    else phi(std::false_type{});
+  } else {
+    phi(std::false_type{});
+  }
   __syncthreads();
 
   float* out = scores + blockIdx.z * sl_stride + (b * Hq + hk * G) * (int64_t)nc_cap;
@@ -353,6 +142,7 @@ __global__ __launch_bounds__(256) void k_topk_union(
   __shared__ int sel_lds[kMaxG * kMaxK];
   __shared__ unsigned bits_lds[kMaxG * kBitmapWords];
   __shared__ u64 list_lds[4][kMaxK];
+  __shared__ float sum_lds[4][kFusedMaxCand];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int64_t bh = blockIdx.x;
@@ -367,15 +157,19 @@ __global__ __launch_bounds__(256) void k_topk_union(
   for (int hl = wave; hl < G; hl += 4) {
     const int64_t hq = hk * G + hl;
     const float* src = scores + (b * Hq + hq) * (int64_t)nc_cap;
+    if (nsl > 1) {                         // uniform; n_cand <= kFusedMaxCand
+      add_slices(src, nsl, sl_stride, n_cand, sum_lds[wave], lane);
+      src = sum_lds[wave];
+    }
     int32_t* so = selected ? selected + (b * Hq + hq) * (int64_t)k : nullptr;
     float* sco = sel_scores ? sel_scores + (b * Hq + hq) * (int64_t)k : nullptr;
     int* row = sel_lds + hl * k_eff;
-    if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
-    else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
-    else if (npl <= 4) head_topk<4>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
-    else if (npl <= 8) head_topk<8>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
-    else if (npl <= 16) head_topk<16>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
-    else head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list, nsl, sl_stride);
+    if (npl <= 1) head_topk<1>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    else if (npl <= 2) head_topk<2>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    else if (npl <= 4) head_topk<4>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    else if (npl <= 8) head_topk<8>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    else if (npl <= 16) head_topk<16>(src, n_cand, k, k_eff, row, so, sco, lane, list);
+    else head_topk<32>(src, n_cand, k, k_eff, row, so, sco, lane, list);
   }
   __syncthreads();
   group_union(sel_lds, bits_lds, G, k_eff, per_head != 0, uni + bh * umax,
@@ -706,91 +500,20 @@ __global__ __launch_bounds__(NT) void k_combine(
 }
 
 // ---- decode pieces -------------------------------------------------------
-template <int D>
-void launch_phi_q(const Shape& s, const void* q, const void* omega, float* phiq,
-                  hipStream_t st) {
-  const float s1 = kLog2e / std::pow((float)s.d, 0.25f);
-  const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
-  const dim3 grid((unsigned)(s.n / 64), (unsigned)(s.B * s.Hkv));
-  auto go = [&](auto g) {
-    launch(RADAR_K_PHI_Q, k_phi_q<D, decltype(g)::value>, grid, dim3(256), 0, st,
-           static_cast<const float*>(q), static_cast<const float*>(omega), phiq, s.n, s.Hq, s.Hkv,
-           s1, s2, 1.f / std::sqrt((float)s.n));
-  };
-  switch (s.G) {
-    case 1: go(std::integral_constant<int, 1>{}); break;
-    case 2: go(std::integral_constant<int, 2>{}); break;
-    case 4: go(std::integral_constant<int, 4>{}); break;
-    default: go(std::integral_constant<int, 8>{}); break;
-  }
-}
-
-// n_cand: the largest candidate count of the call (grid size); each
-// workgroup reads its sequence's own from sa
-template <int N, int G>
-void launch_score_ng(const Shape& s, const float* phiq, const float* summ,
-                     float* scores, int n_cand, const SeqArgs& sa, hipStream_t st) {
-  // above n = 512 the waves of a workgroup split a batch's chunks, two
-  // chunks each (the four features per lane at G = 4 keep two in flight)
-  constexpr int FPL = N / 64;
-  constexpr int NCH = FPL <= 8 ? 1 : FPL / (G >= 4 ? 4 : 8);
-  constexpr int S = NCH >= 4 ? NCH / 2 : 1;
-  if constexpr (S > 1) {
-    const dim3 grid((unsigned)ceil_div(n_cand, 16), (unsigned)(s.B * s.Hkv));
-    const int nc_cap = (int)std::max<int64_t>(1, s.s_cap);
-    launch(RADAR_K_SCORE, k_score<N, G, S>, grid, dim3(64 * S), 0, st, phiq, summ, scores,
-           s.Hq, s.Hkv, sa, s.s_cap, nc_cap);
-  } else {
-    constexpr int rows_per_wave = 16 * (N <= 256 ? 2 : 1);
-    // waves per workgroup: 4 when that still gives two workgroups per CU,
-    // else fewer, so that the rows spread over more CUs
-    int wpb = 4;
-    while (wpb > 1 && ceil_div(n_cand, rows_per_wave * wpb) * s.B * s.Hkv < 2 * num_cu())
-      wpb >>= 1;
-    const dim3 grid((unsigned)ceil_div(n_cand, rows_per_wave * wpb), (unsigned)(s.B * s.Hkv));
-    const int nc_cap = (int)std::max<int64_t>(1, s.s_cap);
-    launch(RADAR_K_SCORE, k_score<N, G, 1>, grid, dim3(64 * wpb), 0, st, phiq, summ, scores,
-           s.Hq, s.Hkv, sa, s.s_cap, nc_cap);
-  }
-}
-
-template <int N>
-void launch_score_n(const Shape& s, const float* phiq, const float* summ,
-                    float* scores, int n_cand, const SeqArgs& sa, hipStream_t st) {
-  switch (s.G) {
-    case 1: launch_score_ng<N, 1>(s, phiq, summ, scores, n_cand, sa, st); break;
-    case 2: launch_score_ng<N, 2>(s, phiq, summ, scores, n_cand, sa, st); break;
-    case 4: launch_score_ng<N, 4>(s, phiq, summ, scores, n_cand, sa, st); break;
-    default: launch_score_ng<N, 8>(s, phiq, summ, scores, n_cand, sa, st); break;
-  }
-}
-
-void launch_score(const Shape& s, const float* phiq, const float* summ,
-                  float* scores, int n_cand, const SeqArgs& sa, hipStream_t st) {
-  switch (s.n) {
-    case 64: launch_score_n<64>(s, phiq, summ, scores, n_cand, sa, st); break;
-    case 128: launch_score_n<128>(s, phiq, summ, scores, n_cand, sa, st); break;
-    case 256: launch_score_n<256>(s, phiq, summ, scores, n_cand, sa, st); break;
-    case 512: launch_score_n<512>(s, phiq, summ, scores, n_cand, sa, st); break;
-    case 1024: launch_score_n<1024>(s, phiq, summ, scores, n_cand, sa, st); break;
-    default: launch_score_n<2048>(s, phiq, summ, scores, n_cand, sa, st); break;
-  }
-}
-
 // Feature slices of k_phi_score: one, doubled (down to 256 features each)
-// while the call has fewer workgroups than CUs and the slices' scores fit in
-// the workspace's phi(q) and score arrays, which lie next to each other.
+// while the call has fewer workgroups than CUs, the slices' scores fit in the
+// workspace's array of n + capacity / c floats per query head, and a head's
+// sums fit in LDS.
 ScorePlan score_plan(const Shape& s, int n_cand) {
   const int64_t cap = std::max<int64_t>(1, s.s_cap);
   const int64_t stride = (int64_t)s.B * s.Hq * cap;
-  if (s.dt != RADAR_BF16) return {1, 0};
   const int64_t rows = std::max<int64_t>(1, ceil_div(n_cand, 128)) * s.B * s.Hkv;
   int nsl = 1;
-  while (s.n / nsl > 256 && rows * nsl < num_cu() && 2 * nsl * cap <= s.n + cap) nsl *= 2;
+  while (n_cand <= kFusedMaxCand && s.n / nsl > 256 && rows * nsl < num_cu() && 2 * nsl * cap <= s.n + cap) nsl *= 2;
   return {nsl, stride};
 }
 
-template <int D, int G>
+template <typename T, int D, int G>
 void launch_phi_score(const Shape& s, const void* q, const void* omega, const float* summ,
                       float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
                       hipStream_t st) {
@@ -807,8 +530,8 @@ void launch_phi_score(const Shape& s, const void* q, const void* omega, const fl
   const dim3 grid((unsigned)groups, (unsigned)P, (unsigned)sp.nsl);
   auto go = [&](auto fpl, auto nw) {
     constexpr int NW = decltype(nw)::value;
-    launch(RADAR_K_SCORE, k_phi_score<D, G, decltype(fpl)::value, NW>, grid, dim3(64 * NW),
-           (size_t)G * fs * 4, st, static_cast<const bf16_t*>(q), omega, s.obf, summ, sc, s.Hq,
+    launch(RADAR_K_SCORE, k_phi_score<T, D, G, decltype(fpl)::value, NW>, grid, dim3(64 * NW),
+           (size_t)G * fs * 4, st, static_cast<const T*>(q), omega, s.obf, summ, sc, s.Hq,
            s.Hkv, s.n, fs, sa, s.s_cap, (int)std::max<int64_t>(1, s.s_cap), sp.stride, s1, s2,
            1.f / std::sqrt((float)s.n));
   };
@@ -822,18 +545,17 @@ void launch_phi_score(const Shape& s, const void* q, const void* omega, const fl
 }
 
 void launch_scores(const Shape& s, const void* q, const void* omega, const float* summ,
-                   float* phiq, float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
+                   float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
                    hipStream_t st) {
-  if (s.dt != RADAR_BF16) {
-    if (s.d == 64) launch_phi_q<64>(s, q, omega, phiq, st);
-    else launch_phi_q<128>(s, q, omega, phiq, st);
-    launch_score(s, phiq, summ, sc, n_cand, sa, st);
-    return;
-  }
-  auto go = [&](auto g) {
+  auto go_t = [&](auto tag, auto g) {
+    typedef decltype(tag) T;
     constexpr int G = decltype(g)::value;
-    if (s.d == 64) launch_phi_score<64, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
-    else launch_phi_score<128, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
+    if (s.d == 64) launch_phi_score<T, 64, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
+    else launch_phi_score<T, 128, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
+  };
+  auto go = [&](auto g) {
+    if (s.dt == RADAR_BF16) go_t(bf16_t{}, g);
+    else go_t(float{}, g);
   };
   switch (s.G) {
     case 1: go(std::integral_constant<int, 1>{}); break;
