@@ -158,8 +158,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     };
 
     // ---- 1. phi(q) -----------------------------------------------------
-    // 16 lanes per Omega row, 4 rows per wave and pass, NP passes in chunks
-    // of at most 8. The first chunk's Omega loads go out first, then q, then
+    // 16 lanes per Omega row, 4 rows per wave and pass, NP passes in chunks. The first chunk's Omega loads go out first, then q, then
     // the summary rows (when they fit in registers next to them). For bf16
     // caches the phase is compiled once per Omega storage type and one copy
     // runs, so all those loads stay in flight together.
@@ -167,7 +166,8 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     auto phase1 = [&](auto bf_tag) {
       constexpr bool BF = decltype(bf_tag)::value;
       constexpr int NP = N / (4 * NW);
-      constexpr int PC = NP < 8 ? NP : 8;
+      // (no summary rows are held beside them above n = 256)
+      constexpr int PC = N > 256 && sizeof(T) == 2 ? 16 : (NP < 8 ? NP : 8);
       using PM = PhiRows<T, D, G, PC>;
       PM pm;
 #pragma unroll

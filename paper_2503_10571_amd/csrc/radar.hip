@@ -17,6 +17,7 @@
 //                  segment (split and scored paths): phi(q) of a feature slice
 //                  in LDS, HBM-bound GEMV over the fp32 summaries, DPP
 //                  transpose-reduce.
+//   k_phi, k_score the same as two kernels, for large summary tables.
 //   k_topk_union   per query head top-k (score desc, index asc) by radix
 //                  selection; per kv head sorted union of the group.
 //   k_segment_mass ln(beta_s), the exact attention mass of every candidate
@@ -408,11 +409,24 @@ radar_status plan_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
   // per pair (measured 110 against 117 us for six ragged bf16 sequences of 32K
   // tokens with eight heads per group, 26.2 against 32.4 us for an fp32 cache of
   // two sequences of 12K). Forced, the paths keep their own kernels.
-  const bool own = g_path_override != RADAR_PATH_AUTO;
+  // An fp32 cache whose pairs times R leave more than an eighth of the CUs idle
+  // and that streams more than 64 MB in all keeps the split attention, whose
+  // grid the hardware balances (96 pairs of 1.1 MB, R = 2: 150 us, 178 in the
+  // scored kernel; 56 pairs of 7 MB, R = 4: 182 and 79).
+  const int ways = fused_ways(s, L, sa);
+  const int64_t P = (int64_t)s.B * s.Hkv;
+  const bool fills = P * ways * 8 >= (int64_t)num_cu() * 7 ||
+                     P * pair_bytes(s, sa) <= (64 << 20);
+  // So does the select path where its one workgroup per pair has little to
+  // read (Omega and summary rows up to 128 KB: 20.3 us for 8 pairs with 5
+  // candidates and n = 128, 24.4 in the scored kernel).
+  const bool light = p->path == RADAR_PATH_SELECT &&
+                     (int64_t)s.n * (s.d + top.n_cand) * 4 <= (128 << 10);
   p->tail = p->path == RADAR_PATH_SCORED ||
-            (!own && (p->path == RADAR_PATH_SPLIT || p->path == RADAR_PATH_SELECT) &&
-             (s.dt == RADAR_BF16 || s.G <= kFusedMaxG));
-  if (p->path == RADAR_PATH_FUSED || p->tail) p->R = fused_ways(s, L, sa);
+            (g_path_override == RADAR_PATH_AUTO &&
+             (p->path == RADAR_PATH_SPLIT || p->path == RADAR_PATH_SELECT) &&
+             (s.dt == RADAR_BF16 || (s.G <= kFusedMaxG && fills && !light)));
+  if (p->path == RADAR_PATH_FUSED || p->tail) p->R = ways;
   if (p->path == RADAR_PATH_FUSED || p->path == RADAR_PATH_SCORED) return RADAR_OK;
   const int u_bound = std::min(s.G * top.k_eff, top.n_cand);
   p->ag = attend_grid(s, L, u_bound, extra_tiles(s, sa));
@@ -439,10 +453,11 @@ radar_status run_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
     if (r != RADAR_OK) return r;
     return launch_attend(s, q, Kp, Vp, plan.ag, sa, out, w, L, stream);
   }
-  float* sc = reinterpret_cast<float*>(w + L.scores);
   const ScorePlan sp = score_plan(s, top.n_cand);
+  float* base = reinterpret_cast<float*>(w + L.scores);
+  float* sc = scores_of(s, base, sp);
   if (top.n_cand > 0)
-    launch_scores(s, q, omega, summaries, sc, top.n_cand, sp, sa, stream);
+    launch_scores(s, q, omega, summaries, base, top.n_cand, sp, sa, stream);
   if (plan.tail) {
     float* part = plan.R > 1 ? reinterpret_cast<float*>(w + L.part) : nullptr;
     const FusedArgs a{&s, q, Kp, Vp, omega, summaries, sa, out, selected, scores,

@@ -627,16 +627,20 @@ struct TileRef {
 // and are masked). q.k partials (fma of the pre-scaled query) are
 // transpose-reduced so that each lane ends with one token's logit, softmax
 // runs across the wave, and p is broadcast back (DPP row broadcast) to the
-// lanes that hold the matching V chunks. At d = 128 a tile is done in two
-// halves of 32 rows: 64 rows of K and V would take 256 registers.
-template <int D, int G>
+// lanes that hold the matching V chunks. At d = 128 the 64 rows of K and V take
+// 256 registers, which k_attend has for one or two heads (IT = 32: 150 us for
+// 96 pairs of 1.1 MB with two heads, 197 in halves); with more heads, and in
+// the 512-thread workgroups of the scored kernel, a tile is done in two halves
+// of 32 rows (IT = 16: 309 us instead of 610 for 40 pairs with eight heads).
+template <int D, int G, int IT = 16>
 struct TileVec {
   static constexpr int kLdsBytes = 0;           // per wave
   static constexpr int EPL = 4;                 // elements per 16-byte chunk
   static constexpr int LPR = D / EPL;           // lanes per row: 16 or 32
   static constexpr int RPI = kWave / LPR;       // rows per load instruction
-  static constexpr int ITER = 16;               // load instructions per pass
+  static constexpr int ITER = IT;               // load instructions per pass
   static constexpr int ROWS = ITER * RPI;       // rows per pass: 64 or 32
+  static_assert(ITER == 16 || ITER == LPR, "tile shape");
 
   float qf[G][EPL];
   float m[G], l[G], acc[G][EPL];
@@ -672,8 +676,8 @@ struct TileVec {
     for (int i = 0; i < ITER; ++i)
       vr[i] = ld_stream(vbase + (int64_t)min(i * RPI + r, len - 1) * D);
 
-    // logits: lane (r, jj) ends with the logit of row (jj % 16) * RPI + r
-    // (at d = 128 lanes jj and jj + 16 both hold it)
+    // logits: lane (r, jj) ends with the logit of row (jj % ITER) * RPI + r
+    // (in a half tile lanes jj and jj + 16 both hold it)
     float lg[G];
     {
       float pl[G][ITER];
@@ -691,11 +695,11 @@ struct TileVec {
       }
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        transpose_reduce<16>(pl[g], lane);
-        lg[g] = LPR == 32 ? xor_sum<16>(pl[g][0]) : pl[g][0];
+        transpose_reduce<ITER>(pl[g], lane);
+        lg[g] = LPR != ITER ? xor_sum<16>(pl[g][0]) : pl[g][0];
       }
     }
-    const bool mine_ok = ((jj & 15) * RPI + r) < len;
+    const bool mine_ok = ((jj % ITER) * RPI + r) < len;
     float p[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -705,7 +709,7 @@ struct TileVec {
       const float mref = mn == -INFINITY ? 0.f : mn;
       const float scale = fast_exp2(m[g] - mref);  // 0 on the head's first tile
       p[g] = on ? fast_exp2(lg[g] - mref) : 0.f;
-      l[g] = fmaf(l[g], scale, wave_sum(jj < 16 ? p[g] : 0.f));
+      l[g] = fmaf(l[g], scale, wave_sum(jj < ITER ? p[g] : 0.f));
       m[g] = mn;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) acc[g][e] *= scale;
@@ -716,17 +720,24 @@ struct TileVec {
       unpack16<float>(vr[i], vf);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        // p of row (i, r) lives in lane i of every 16-lane row of the group
-        const float pb = dpp_f<kDppRowBcast0 + i>(p[g]);
+        // p of row (i, r) lives in lane i of its row's lanes (of both 16-lane
+        // rows of them in a half tile)
+        float pb;
+        if constexpr (ITER == 16) pb = dpp_f<kDppRowBcast0 + i>(p[g]);
+        else pb = __shfl(p[g], r * LPR + i);
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(pb, vf[e], acc[g][e]);
       }
     });
   }
   __device__ __forceinline__ void tile(const float* K, const float* V, const TileRef& t) {
+    if constexpr (ROWS == kTile) {
+      pass(K, V, t.row0, t.len, t.hmask);
+    } else {
 #pragma unroll 1
-    for (int off = 0; off < t.len; off += ROWS)
-      pass(K, V, t.row0 + off, min(ROWS, t.len - off), t.hmask);
+      for (int off = 0; off < t.len; off += ROWS)
+        pass(K, V, t.row0 + off, min(ROWS, t.len - off), t.hmask);
+    }
   }
 
   // tiles first, first + step, ... < end of at(i); wave-uniform call
@@ -1041,6 +1052,9 @@ struct TileMfma {
 
 template <typename T, int D, int G>
 using Tile = typename std::conditional<sizeof(T) == 2, TileMfma<D, G>, TileVec<D, G>>::type;
+template <typename T, int D, int G>
+using AttendTile = typename std::conditional<sizeof(T) == 2, TileMfma<D, G>,
+                                             TileVec<D, G, D == 128 && G <= 2 ? 32 : 16>>::type;
 
 // ---------------------------------------------------------------------------
 // phi(q) of a group's heads (Eq. 4)
@@ -1280,14 +1294,18 @@ radar_status launch_build(const Shape& s, const void* K, const void* omega,
 
 // split.hip: the split path's stages
 // phi(q) and Eq. 6 scores of up to n_cand candidates of every query head into
-// `sc`, in ScorePlan's slices
+// scores_of(base), in ScorePlan's slices; base: the workspace's score array
 struct ScorePlan {
-  int nsl;             // slices of the features
+  int nsl;             // slices of the features; 0: two kernels, one slice
   int64_t stride;      // floats between them
 };
 ScorePlan score_plan(const Shape& s, int n_cand);
+// (the two kernels' phi(q) lies before the scores)
+inline float* scores_of(const Shape& s, float* base, const ScorePlan& sp) {
+  return base + (sp.nsl == 0 ? (int64_t)s.B * s.Hq * s.n : 0);
+}
 void launch_scores(const Shape& s, const void* q, const void* omega, const float* summ,
-                   float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
+                   float* base, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
                    hipStream_t st);
 // ln(beta) of candidates [0, n_cand) into rows of nc_cap scores; with_rest
 // also the mass of the window and sinks at index n_cand

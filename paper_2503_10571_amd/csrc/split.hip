@@ -41,8 +41,8 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   const T* q0 = q + (b * Hq + hk * G) * D;
   const float* base = summ + bh * s_cap * n + f0 + lane * FPL;
 
-  float x[16][FPL];
-  auto load_rows = [&](int row0, int ch) {
+  float xa[16][FPL];
+  auto load_rows = [&](float (&x)[16][FPL], int row0, int ch) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float* src = base + (int64_t)min(row0 + r, n_cand - 1) * n + ch * FC;
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
       PM::template load<BF>(om, omega, f0 + mine, 4 * NW, lane);
       if (c0 == 0) {
         pm.load_q(q0, lane);
-        if (row0 < n_cand) load_rows(row0, 0);
+        if (row0 < n_cand) load_rows(xa, row0, 0);
         pm.norm(s2, lane);
       }
       pm.template features<BF>(om, s1, inv_sqrt_n, lane, [&](int g, int p, float v) {
@@ -93,37 +93,231 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   float* out = scores + blockIdx.z * sl_stride + (b * Hq + hk * G) * (int64_t)nc_cap;
   const int nch = fs / FC;
   const int step = (int)gridDim.x * 16 * NW;
-  for (bool first = true; row0 < n_cand; row0 += step, first = false) {
-    float part[G][16];
+  if (row0 >= n_cand) return;              // wave-uniform, no barrier follows
+  float part[G][16];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[g][r] = 0.f;
+  int ch = 0;
+  // one chunk of a row block; the next chunk's loads (of this block or the
+  // wave's next one) go out first where the registers hold two (up to four
+  // heads), into `nxt`
+  constexpr bool kAhead = G <= 4;
+  auto chunk = [&](float (&cur)[16][FPL], float (&nxt)[16][FPL]) -> bool {
+    const int r0 = row0, c0 = ch;
+    if (++ch == nch) { ch = 0; row0 += step; }
+    const bool more = row0 < n_cand;
+    if (kAhead && more) load_rows(nxt, row0, ch);
+    float pq[G][FPL];
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) part[g][r] = 0.f;
-#pragma unroll 1
-    for (int ch = 0; ch < nch; ++ch) {
-      if (!first || ch > 0) load_rows(row0, ch);
-      float pq[G][FPL];
+      for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * fs + c0 * FC + lane * FPL + e];
+    // keep the chunk's loads together (the compiler would otherwise sink
+    // each to its first use and wait on one at a time)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int g = 0; g < G; ++g)
+    for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * fs + ch * FC + lane * FPL + e];
-      // keep the chunk's loads together (the compiler would otherwise sink
-      // each to its first use and wait on one at a time)
-      __builtin_amdgcn_sched_barrier(0);
+      for (int r = 0; r < 16; ++r)
 #pragma unroll
-      for (int g = 0; g < G; ++g)
+        for (int e = 0; e < FPL; ++e) part[g][r] = fmaf(cur[r][e], pq[g][e], part[g][r]);
+    if (!kAhead && more) load_rows(nxt, row0, ch);
+    if (c0 == nch - 1) {                   // the block is complete
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
+      for (int g = 0; g < G; ++g) {
+        transpose_reduce<16>(part[g], lane);
+        float v = part[g][0];
+        v = xor_sum<16>(v);
+        v = xor_sum<32>(v);
+        if (lane < 16 && r0 + lane < n_cand) out[g * (int64_t)nc_cap + r0 + lane] = v;
 #pragma unroll
-          for (int e = 0; e < FPL; ++e) part[g][r] = fmaf(x[r][e], pq[g][e], part[g][r]);
+        for (int r = 0; r < 16; ++r) part[g][r] = 0.f;
+      }
     }
+    return more;
+  };
+  if constexpr (kAhead) {
+    float xb[16][FPL];
+    while (chunk(xa, xb) && chunk(xb, xa)) {}
+  } else {
+    while (chunk(xa, xa)) {}
+  }
+}
+
+// ---------------------------------------------------------------------------
+// k_phi, k_score: the same as two kernels, for large summary tables
+// ---------------------------------------------------------------------------
+// k_phi: phi(q) of 64 features of one (b, kv head) per workgroup.
+template <typename T, int D, int G, bool BF>
+__global__ __launch_bounds__(256) void k_phi(const T* __restrict__ q,
+                                             const void* __restrict__ omega,
+                                             float* __restrict__ phiq, int n, int Hq, int Hkv,
+                                             float s1, float s2, float inv_sqrt_n) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t bh = blockIdx.y;
+  const int64_t hq0 = bh / Hkv * Hq + bh % Hkv * G;    // the group's first (b, q head)
+  using PM = PhiRows<T, D, G, 4>;
+  PM pm;
+  typename PM::template Om<BF> om;
+  const int row = blockIdx.x * 64 + wave * 4 + (lane >> 4);
+  PM::template load<BF>(om, omega, row, 16, lane);
+  pm.load_q(q + hq0 * D, lane);
+  pm.norm(s2, lane);
+  pm.template features<BF>(om, s1, inv_sqrt_n, lane, [&](int g, int p, float v) {
+    phiq[(hq0 + g) * n + row + 16 * p] = v;
+  });
+}
+
+// k_score: workgroup = 1, 2 or 4 waves x (16 * RB) summary rows of one (b, kv head)
+// (fewer waves per workgroup when that spreads a small call over more CUs;
+// the waves are independent). Lane l holds FPL = n / 64 features of phi(q)
+// for the G heads of the group, in chunks of at most 8 (n = 1024 and 2048
+// take 2 to 8 chunks, so the rows of a batch fit in registers); each chunk
+// of a row is one contiguous wave load, and all of a batch's rows are loaded
+// before any is reduced. A 16-row batch is transpose-reduced inside each
+// 16-lane row with DPP, then summed over the four rows.
+// With S > 1 the S waves of a workgroup share one batch of rows instead and
+// each takes NCH / S of the chunks (one round trip to memory instead of
+// NCH / 2 for a wave that walks them all); the waves' row sums are added in
+// LDS in wave order.
+template <int N, int G, int S>
+__global__ __launch_bounds__(256) void k_score(const float* __restrict__ phiq,
+                                               const float* __restrict__ summ,
+                                               float* __restrict__ scores,
+                                               int Hq, int Hkv, SeqArgs sa,
+                                               int64_t s_cap, int nc_cap) {
+  constexpr int FPL = N / 64;
+  // features per lane per chunk: all of them up to n = 512; above, 8 (4
+  // for G >= 4, whose accumulators take more registers)
+  constexpr int FC = FPL <= 8 ? FPL : (G >= 4 ? 4 : 8);
+  constexpr int NCH = FPL / FC;            // chunks (1 for n <= 512)
+  constexpr int RB = N <= 256 ? 2 : 1;     // 16-row batches per wave
+  static_assert(NCH % S == 0 && (S == 1 || RB == 1), "feature split");
+  constexpr int CPW = NCH / S;             // chunks of each wave
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int64_t bh = blockIdx.y;
+  const int64_t b = bh / Hkv, hk = bh % Hkv;
+  const int n_cand = seq_span(sa, b).n_cand;
+  const int wrow0 = S > 1 ? blockIdx.x * 16
+                          : (blockIdx.x * (blockDim.x >> 6) + wave) * (16 * RB);
+  // wave-uniform, and workgroup-uniform with S > 1 (the waves share rows),
+  // so the barrier below is reached by all waves or by none
+  if (wrow0 >= n_cand) return;
+  const int ch0 = S > 1 ? wave * CPW : 0;  // this wave's first chunk
+
+  // chunk ch holds features ch * 64 * FC + lane * FC + e (e < FC) of lane
+  // `lane`, so each chunk of a row is one contiguous 64 * FC * 4-byte wave
+  // load; with one chunk (n <= 512) lane l holds features l * FPL .. + FPL
+  const float* base = summ + (bh * s_cap) * N + lane * FC;
+  // per row and head a running dot product over the chunks
+  float part[RB][G][16];
+#pragma unroll
+  for (int bt = 0; bt < RB; ++bt)
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[bt][g][r] = 0.f;
+  // a chunk's phi(q) features and rows
+  auto load_chunk = [&](int ch, float (&pq)[G][FC], float (&x)[RB][16][FC]) {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      transpose_reduce<16>(part[g], lane);
-      float v = part[g][0];
+      const float* src = phiq + ((b * Hq + hk * G + g) * N) + ch * 64 * FC + lane * FC;
+#pragma unroll
+      for (int e = 0; e < FC; ++e) pq[g][e] = src[e];
+    }
+#pragma unroll
+    for (int bt = 0; bt < RB; ++bt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = min(wrow0 + bt * 16 + r, n_cand - 1);
+        const float* src = base + (int64_t)row * N + ch * 64 * FC;
+        if constexpr (FC % 4 == 0) {
+#pragma unroll
+          for (int e = 0; e < FC; e += 4) {
+            const float4 v = ld_stream_f4(src + e);
+            x[bt][r][e] = v.x; x[bt][r][e + 1] = v.y;
+            x[bt][r][e + 2] = v.z; x[bt][r][e + 3] = v.w;
+          }
+        } else if constexpr (FC == 2) {
+          const float2 v = *reinterpret_cast<const float2*>(src);
+          x[bt][r][0] = v.x; x[bt][r][1] = v.y;
+        } else {
+          x[bt][r][0] = src[0];
+        }
+      }
+  };
+  auto add_chunk = [&](const float (&pq)[G][FC], const float (&x)[RB][16][FC]) {
+#pragma unroll
+    for (int bt = 0; bt < RB; ++bt)
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float a = part[bt][g][r];
+#pragma unroll
+          for (int e = 0; e < FC; ++e) a = fmaf(x[bt][r][e], pq[g][e], a);
+          part[bt][g][r] = a;
+        }
+  };
+  // Several chunks at G = 4 (four features per lane): two chunks in flight,
+  // the next one's loads issued before this one's products (same products,
+  // same order; 376 registers, one wave per SIMD, as these launches run);
+  // otherwise one chunk's rows live at a time (G = 8 would not fit).
+  constexpr bool kTwo = CPW > 1 && CPW % 2 == 0 && FC == 4 && G == 4;
+  if constexpr (kTwo) {
+    float pqa[G][FC], xa[RB][16][FC], pqb[G][FC], xb[RB][16][FC];
+    load_chunk(ch0, pqa, xa);
+#pragma unroll 1
+    for (int ch = ch0; ch < ch0 + CPW; ch += 2) {
+      load_chunk(ch + 1, pqb, xb);
+      __builtin_amdgcn_sched_barrier(0);
+      add_chunk(pqa, xa);
+      if (ch + 2 < ch0 + CPW) load_chunk(ch + 2, pqa, xa);
+      __builtin_amdgcn_sched_barrier(0);
+      add_chunk(pqb, xb);
+    }
+  } else {
+#pragma unroll 1
+    for (int ch = ch0; ch < ch0 + CPW; ++ch) {
+      float pq[G][FC], x[RB][16][FC];
+      load_chunk(ch, pq, x);
+      // with several chunks the compiler would sink each load to its first
+      // use and wait on one load at a time; keep the chunk's loads together
+      if constexpr (CPW > 1) __builtin_amdgcn_sched_barrier(0);
+      add_chunk(pq, x);
+    }
+  }
+  __shared__ float red[S > 1 ? S : 1][G][16];
+#pragma unroll
+  for (int bt = 0; bt < RB; ++bt) {
+    const int row = wrow0 + bt * 16 + (lane & 15);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      transpose_reduce<16>(part[bt][g], lane);
+      float v = part[bt][g][0];
       v = xor_sum<16>(v);
       v = xor_sum<32>(v);
-      if (lane < 16 && row0 + lane < n_cand) out[g * (int64_t)nc_cap + row0 + lane] = v;
+      if constexpr (S > 1) {
+        if (lane < 16) red[wave][g][lane] = v;
+      } else {
+        if (lane < 16 && row < n_cand)
+          scores[(b * Hq + hk * G + g) * (int64_t)nc_cap + row] = v;
+      }
+    }
+  }
+  if constexpr (S > 1) {
+    __syncthreads();
+    if (wave == 0 && lane < 16 && wrow0 + lane < n_cand) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        float v = red[0][g][lane];
+#pragma unroll
+        for (int w = 1; w < S; ++w) v += red[w][g][lane];
+        scores[(b * Hq + hk * G + g) * (int64_t)nc_cap + wrow0 + lane] = v;
+      }
     }
   }
 }
@@ -311,7 +505,7 @@ __global__ __launch_bounds__(256) void k_attend(
     float* __restrict__ part, int Hq, int Hkv, int64_t cap,
     int tiles_per_seg, SeqArgs sa, int per_head, int umax, int maxwg, int tpw,
     float qscale) {
-  using TA = Tile<T, D, G>;
+  using TA = AttendTile<T, D, G>;
   constexpr int PSTRIDE = D + 4;
   constexpr int kMerge = 4 * G * D * 4;
   constexpr int kLds = 4 * TA::kLdsBytes > kMerge ? 4 * TA::kLdsBytes : kMerge;
@@ -500,13 +694,70 @@ __global__ __launch_bounds__(NT) void k_combine(
 }
 
 // ---- decode pieces -------------------------------------------------------
+// n_cand: the largest candidate count of the call (grid size); each
+// workgroup reads its sequence's own from sa
+template <int N, int G>
+void launch_score_ng(const Shape& s, const float* phiq, const float* summ,
+                     float* scores, int n_cand, const SeqArgs& sa, hipStream_t st) {
+  // above n = 512 the waves of a workgroup split a batch's chunks, two
+  // chunks each (the four features per lane at G = 4 keep two in flight)
+  constexpr int FPL = N / 64;
+  constexpr int NCH = FPL <= 8 ? 1 : FPL / (G >= 4 ? 4 : 8);
+  constexpr int S = NCH >= 4 ? NCH / 2 : 1;
+  if constexpr (S > 1) {
+    const dim3 grid((unsigned)ceil_div(n_cand, 16), (unsigned)(s.B * s.Hkv));
+    const int nc_cap = (int)std::max<int64_t>(1, s.s_cap);
+    launch(RADAR_K_SCORE, k_score<N, G, S>, grid, dim3(64 * S), 0, st, phiq, summ, scores,
+           s.Hq, s.Hkv, sa, s.s_cap, nc_cap);
+  } else {
+    constexpr int rows_per_wave = 16 * (N <= 256 ? 2 : 1);
+    // waves per workgroup: 4 when that still gives two workgroups per CU,
+    // else fewer, so that the rows spread over more CUs
+    int wpb = 4;
+    while (wpb > 1 && ceil_div(n_cand, rows_per_wave * wpb) * s.B * s.Hkv < 2 * num_cu())
+      wpb >>= 1;
+    const dim3 grid((unsigned)ceil_div(n_cand, rows_per_wave * wpb), (unsigned)(s.B * s.Hkv));
+    const int nc_cap = (int)std::max<int64_t>(1, s.s_cap);
+    launch(RADAR_K_SCORE, k_score<N, G, 1>, grid, dim3(64 * wpb), 0, st, phiq, summ, scores,
+           s.Hq, s.Hkv, sa, s.s_cap, nc_cap);
+  }
+}
+
+template <int N>
+void launch_score_n(const Shape& s, const float* phiq, const float* summ,
+                    float* scores, int n_cand, const SeqArgs& sa, hipStream_t st) {
+  switch (s.G) {
+    case 1: launch_score_ng<N, 1>(s, phiq, summ, scores, n_cand, sa, st); break;
+    case 2: launch_score_ng<N, 2>(s, phiq, summ, scores, n_cand, sa, st); break;
+    case 4: launch_score_ng<N, 4>(s, phiq, summ, scores, n_cand, sa, st); break;
+    default: launch_score_ng<N, 8>(s, phiq, summ, scores, n_cand, sa, st); break;
+  }
+}
+
+void launch_score(const Shape& s, const float* phiq, const float* summ,
+                  float* scores, int n_cand, const SeqArgs& sa, hipStream_t st) {
+  switch (s.n) {
+    case 64: launch_score_n<64>(s, phiq, summ, scores, n_cand, sa, st); break;
+    case 128: launch_score_n<128>(s, phiq, summ, scores, n_cand, sa, st); break;
+    case 256: launch_score_n<256>(s, phiq, summ, scores, n_cand, sa, st); break;
+    case 512: launch_score_n<512>(s, phiq, summ, scores, n_cand, sa, st); break;
+    case 1024: launch_score_n<1024>(s, phiq, summ, scores, n_cand, sa, st); break;
+    default: launch_score_n<2048>(s, phiq, summ, scores, n_cand, sa, st); break;
+  }
+}
+
 // Feature slices of k_phi_score: one, doubled (down to 256 features each)
 // while the call has fewer workgroups than CUs, the slices' scores fit in the
 // workspace's array of n + capacity / c floats per query head, and a head's
 // sums fit in LDS.
+// Large summary tables (from 64 MB) take k_phi and k_score: streaming is all
+// there is to them then, and k_score's many small workgroups balance better
+// (56 pairs x 1302 rows x 2048 features, four heads: 161 us a step, 183 with
+// k_phi_score; 8 x 120 x 2048: 32.9 and 30.2).
 ScorePlan score_plan(const Shape& s, int n_cand) {
   const int64_t cap = std::max<int64_t>(1, s.s_cap);
   const int64_t stride = (int64_t)s.B * s.Hq * cap;
+  if ((int64_t)n_cand * s.n * 4 * s.B * s.Hkv >= (64 << 20)) return {0, 0};
   const int64_t rows = std::max<int64_t>(1, ceil_div(n_cand, 128)) * s.B * s.Hkv;
   int nsl = 1;
   while (n_cand <= kFusedMaxCand && s.n / nsl > 256 && rows * nsl < num_cu() && 2 * nsl * cap <= s.n + cap) nsl *= 2;
@@ -523,10 +774,11 @@ void launch_phi_score(const Shape& s, const void* q, const void* omega, const fl
   // four waves per workgroup where eight would leave CUs idle
   const bool narrow = ceil_div(n_cand, 128) * P * sp.nsl < num_cu();
   const int rows = narrow ? 64 : 128;
-  // row groups: one block of rows each while the workgroups do not outnumber
-  // two per CU (a workgroup's phi(q) serves all its blocks)
-  const int64_t most = std::max<int64_t>(1, 2 * (int64_t)num_cu() / ((int64_t)P * sp.nsl));
-  const int64_t groups = std::min<int64_t>(ceil_div(n_cand, rows), most);
+  // row groups: one block of rows each up to four workgroups per CU, then
+  // equal numbers of blocks (a workgroup's phi(q) serves all its blocks)
+  const int64_t blocks = ceil_div(n_cand, rows);
+  const int64_t per = std::max<int64_t>(1, blocks * P * sp.nsl / (4 * (int64_t)num_cu()));
+  const int64_t groups = ceil_div(blocks, per);
   const dim3 grid((unsigned)groups, (unsigned)P, (unsigned)sp.nsl);
   auto go = [&](auto fpl, auto nw) {
     constexpr int NW = decltype(nw)::value;
@@ -544,14 +796,37 @@ void launch_phi_score(const Shape& s, const void* q, const void* omega, const fl
   else go_nw(std::integral_constant<int, 1>{});
 }
 
+template <typename T, int D, int G>
+void launch_phi(const Shape& s, const void* q, const void* omega, float* phiq, hipStream_t st) {
+  const float s1 = kLog2e / std::pow((float)s.d, 0.25f);
+  const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
+  const dim3 grid((unsigned)(s.n / 64), (unsigned)(s.B * s.Hkv));
+  auto go = [&](auto bf) {
+    launch(RADAR_K_PHI_Q, k_phi<T, D, G, decltype(bf)::value>, grid, dim3(256), 0, st,
+           static_cast<const T*>(q), omega, phiq, s.n, s.Hq, s.Hkv, s1, s2,
+           1.f / std::sqrt((float)s.n));
+  };
+  if constexpr (sizeof(T) == 2) {
+    if (s.obf) return go(std::true_type{});
+  }
+  go(std::false_type{});
+}
+
 void launch_scores(const Shape& s, const void* q, const void* omega, const float* summ,
-                   float* sc, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
+                   float* base, int n_cand, const ScorePlan& sp, const SeqArgs& sa,
                    hipStream_t st) {
+  float* sc = scores_of(s, base, sp);
   auto go_t = [&](auto tag, auto g) {
     typedef decltype(tag) T;
     constexpr int G = decltype(g)::value;
-    if (s.d == 64) launch_phi_score<T, 64, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
-    else launch_phi_score<T, 128, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
+    if (sp.nsl == 0) {
+      if (s.d == 64) launch_phi<T, 64, G>(s, q, omega, base, st);
+      else launch_phi<T, 128, G>(s, q, omega, base, st);
+      launch_score(s, base, summ, sc, n_cand, sa, st);
+    } else {
+      if (s.d == 64) launch_phi_score<T, 64, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
+      else launch_phi_score<T, 128, G>(s, q, omega, summ, sc, n_cand, sp, sa, st);
+    }
   };
   auto go = [&](auto g) {
     if (s.dt == RADAR_BF16) go_t(bf16_t{}, g);
