@@ -104,11 +104,17 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   // wave's next one) go out first where the registers hold two (up to four
   // heads), into `nxt`
   constexpr bool kAhead = G <= 4;
+  bool loaded = true;                      // (eight heads: the first chunk only)
   auto chunk = [&](float (&cur)[16][FPL], float (&nxt)[16][FPL]) -> bool {
     const int r0 = row0, c0 = ch;
     if (++ch == nch) { ch = 0; row0 += step; }
     const bool more = row0 < n_cand;
-    if (kAhead && more) load_rows(nxt, row0, ch);
+    if constexpr (kAhead) {
+      if (more) load_rows(nxt, row0, ch);
+    } else {
+      if (!loaded) load_rows(cur, r0, c0);
+      loaded = false;
+    }
     float pq[G][FPL];
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -123,7 +129,6 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
       for (int r = 0; r < 16; ++r)
 #pragma unroll
         for (int e = 0; e < FPL; ++e) part[g][r] = fmaf(cur[r][e], pq[g][e], part[g][r]);
-    if (!kAhead && more) load_rows(nxt, row0, ch);
     if (c0 == nch - 1) {                   // the block is complete
 #pragma unroll
       for (int g = 0; g < G; ++g) {
