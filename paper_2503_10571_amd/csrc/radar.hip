@@ -430,7 +430,7 @@ radar_status plan_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
   if (p->path == RADAR_PATH_FUSED || p->path == RADAR_PATH_SCORED) return RADAR_OK;
   const int u_bound = std::min(s.G * top.k_eff, top.n_cand);
   p->ag = attend_grid(s, L, u_bound, extra_tiles(s, sa));
-  return p->ag.grid_x > kMaxWg ? RADAR_EUNSUPPORTED : RADAR_OK;
+  return RADAR_OK;
 }
 
 // The decode launches. The first per-(b, kv head) kernel of the path (the
@@ -798,8 +798,6 @@ radar_status radar_decode_exact(const radar_config* cfg, const void* q,
   const void* Vp = after_sinks(s, V);
   const int u_bound = std::min(s.G * top.k_eff, top.n_cand);
   const AttendGrid ag = attend_grid(s, L, u_bound, extra_tiles(s, sa));
-  if (ag.grid_x > kMaxWg) return RADAR_EUNSUPPORTED;
-
   unsigned char* w = reinterpret_cast<unsigned char*>(workspace);
   float* sc = reinterpret_cast<float*>(w + L.scores);
   if (top.n_cand > 0)
@@ -849,7 +847,6 @@ radar_status radar_attend_selected(const radar_config* cfg, const void* q,
   const Span top = make_span(t, sa);
   const int u_bound = std::min(s.G * k, top.n_cand);
   const AttendGrid ag = attend_grid(s, L, u_bound, extra_tiles(s, sa));
-  if (ag.grid_x > kMaxWg) return RADAR_EUNSUPPORTED;
   unsigned char* w = reinterpret_cast<unsigned char*>(workspace);
   launch_union_given(s, selected, k, sa, reinterpret_cast<int*>(w + L.uni),
                      reinterpret_cast<int*>(w + L.ucnt), L.umax, stream);

@@ -909,12 +909,15 @@ int64_t extra_tiles(const Shape& s, const SeqArgs& sa) {
 // holds about eight workgroups per CU (a grid only just above the resident
 // count leaves a long tail), but no more (fewer, larger workgroups mean fewer
 // partials to merge); and the grid width per (b, kv head) for the largest
-// union.
+// union, at most the kMaxWg partials that a merge takes: a pair with more
+// tiles gives its waves more of them.
 AttendGrid attend_grid(const Shape& s, const WsLayout& L, int u_bound,
                        int64_t extra) {
   const int64_t per_bh = (int64_t)u_bound * L.tiles_per_seg + extra;
   const int64_t tiles = per_bh * s.B * s.Hkv;
-  const int64_t tpw = std::min<int64_t>(8, std::max<int64_t>(1, tiles / (4 * 8 * num_cu())));
+  const int64_t tpw =
+      std::max(std::min<int64_t>(8, std::max<int64_t>(1, tiles / (4 * 8 * num_cu()))),
+               ceil_div(per_bh, 4 * kMaxWg));
   return {(int)ceil_div(per_bh, 4 * tpw), (int)tpw};
 }
 

@@ -124,3 +124,41 @@ def test_group_of_eight_route(opt, d):
         assert np.array_equal(np.isnan(x), np.isnan(y))
         bad = np.abs(x - y) > 2.0 ** -7 * np.abs(y) + 8e-5
         assert not bad.any()
+
+
+@pytest.mark.parametrize("call", ["decode", "split", "append_decode", "exact", "given"])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_more_tiles_than_partials(call, dtype):
+    """A pair whose tiles, one per wave, would need more workgroups than a
+    merge takes partials (a window of 4110 tiles; 4 waves, 1024 partials): its
+    waves take several. The sums stay short: at most three tiles of 64 tokens
+    per wave, four waves, and 32 partials per thread and 32 threads in the
+    merge, so the 400 products of _close hold."""
+    G, w = 8, 4110 * 64 - 5
+    t = w + 300
+    print(f"[case] wide attention {call} {dtype} t={t}", flush=True)
+    cfg = radar.Config(1, G, 1, 64, 64, 64, w, t, dtype)
+    K, V, q, omega = _inputs(cfg, 5)
+    summ = radar.new_summaries(cfg, "cuda")
+    radar.build_index(cfg, K, omega, t, summ)
+    ws, n_cand = orc.window_split(t, 64, w, 0)
+    k = 2
+    sel = torch.empty(1, G, k, dtype=torch.int32, device="cuda")
+    if call == "append_decode":
+        out = radar.append_decode(cfg, q, K, V, K[:, :, -1].clone(), V[:, :, -1].clone(), omega,
+                                  summ, t, k, selected=sel)
+    elif call == "exact":
+        out = radar.decode_exact(cfg, q, K, V, t, k, selected=sel)
+    elif call == "given":
+        sel[:] = torch.arange(k, dtype=torch.int32) * 2
+        out = radar.attend_selected(cfg, q, K, V, sel, t)
+    else:
+        radar.set_decode_path(radar.PATH_SPLIT if call == "split" else radar.PATH_AUTO)
+        try:
+            out = radar.decode(cfg, q, K, V, omega, summ, t, k, selected=sel)
+        finally:
+            radar.set_decode_path(radar.PATH_AUTO)
+    toks = orc.attended_tokens([int(s) for s in sel.flatten().tolist()], 64, ws, t, 0)
+    keys, vals = H.f64(K[0, 0]), H.f64(V[0, 0])
+    for h in (0, G - 1):
+        _close(H.f64(out[0, h]), orc.attend(H.f64(q[0, h]), keys, vals, toks), dtype)
