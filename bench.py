@@ -772,7 +772,9 @@ def main():
         dom, dom_name, dom_bytes = "attend", "k_attend", kv_bytes
         avg = {k: prof[k][0] / max(prof[k][1], 1) for k in ("attend", "score")}
         if prof["score"][1] and avg["score"] > avg["attend"]:
-            dom, dom_name, dom_bytes = "score", "k_score", summ_bytes
+            # (phi(q) has no launch of its own where the score kernel does both)
+            dom, dom_bytes = "score", summ_bytes
+            dom_name = "k_score" if prof["phi_q"][1] else "k_phi_score"
     dom_ms, dom_n = prof[dom]
     dom_avg_ms = dom_ms / max(dom_n, 1)
     per_launch = dom_bytes / (Ksteps * NL)     # one launch per layer and step

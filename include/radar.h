@@ -290,17 +290,17 @@ radar_status radar_schedule_sqrt(int64_t t, int32_t* seg_len, int32_t* window);
  * pair's selection and share its attention (R = 1 when the pairs fill the
  * chip or a step is small; with R > 1 a merge kernel follows); the select
  * path runs phi(q), scores, top-k and union of each pair in one workgroup
- * and then the split path's attention and merge. All compute the same
- * method; their fp32 summation orders differ. Left to its own choice the
- * library runs the split path of a group of eight on a bf16 cache from its
- * top-k on as the scored path does; a forced split path keeps its kernels. */
+ * and then the split path's attention and merge; the scored path takes the
+ * split path's scores and runs the rest as the fused path does. All compute
+ * the same method; their fp32 summation orders differ. */
 typedef enum {
   RADAR_PATH_AUTO = 0,   /* fused when the shape fits and either B * Hkv >=
                             #CUs, one pair's step reads <= 256 KB, or a
-                            pair's summary rows are <= 384 KB; else select
-                            when the rows are <= 384 KB; else scored when
-                            G <= 4 and not fp32 with d = 128; split
-                            otherwise                                       */
+                            pair's summary rows are <= 384 KB; else scored
+                            where it is available, except fp32 calls with
+                            d = 128 whose selection has little to read or
+                            whose pairs leave CUs idle: those take select
+                            (rows <= 384 KB) or split, as does the rest     */
   RADAR_PATH_SPLIT = 1,
   RADAR_PATH_FUSED = 2,  /* used when the shape fits (G <= 4, at most 1024
                             candidate segments, not fp32 with d = 128),
@@ -311,25 +311,26 @@ typedef enum {
                             chip-wide kernels, then R workgroups per pair
                             that each take the pair's top-k and union from
                             those scores and share its attention (the fused
-                            kernel from its top-k on); used when G <= 4 and
-                            not fp32 with d = 128, else split              */
+                            kernel from its top-k on); used for bf16 caches
+                            and, when G <= 4, for fp32 ones, else split     */
 } radar_path;
 
 /* Choose the decode path for later calls from this host thread (default
  * RADAR_PATH_AUTO). For tests and tuning; results stay within tolerance. */
 radar_status radar_set_decode_path(int32_t path);
 
-/* The path radar_decode would take for this shape, t (the length, or the
- * bound of a ragged call's lengths) and k on this thread (RADAR_PATH_SPLIT,
- * RADAR_PATH_FUSED or RADAR_PATH_SELECT; -1 if the arguments are invalid). */
+/* The path radar_decode takes for this shape, t (the length, or the bound of
+ * a ragged call's lengths) and k on this thread (RADAR_PATH_SPLIT, _FUSED,
+ * _SELECT or _SCORED; -1 if the arguments are invalid). */
 int32_t radar_decode_path(const radar_config* cfg, int64_t t, int32_t k);
 
 /* Kernel kinds reported by the measurement hook below. */
 typedef enum {
   RADAR_K_APPEND = 0,   /* k/v row write                                   */
   RADAR_K_BUILD = 1,    /* segment summaries (build or segment close)      */
-  RADAR_K_PHI_Q = 2,    /* phi(q)                                          */
-  RADAR_K_SCORE = 3,    /* Eq. 6 segment scores (exact mass: its kernel)   */
+  RADAR_K_PHI_Q = 2,    /* phi(q), where it has a kernel of its own        */
+  RADAR_K_SCORE = 3,    /* Eq. 6 segment scores, with phi(q) where one
+                           kernel does both (exact mass: its kernel)       */
   RADAR_K_TOPK = 4,     /* top-k and per-kv-head union (or given union)    */
   RADAR_K_ATTEND = 5,   /* gather-attention partials                       */
   RADAR_K_COMBINE = 6,  /* merge of the partials                           */

@@ -243,9 +243,6 @@ radar_status launch_fused(const Shape& s, const void* q, const void* K, const vo
                           const AppendArgs& ap, int R, unsigned char* w,
                           const WsLayout& L, hipStream_t st) {
   float* part = R > 1 ? reinterpret_cast<float*>(w + L.part) : nullptr;
-  // fp32 caches with d = 128 keep the split path: their tiles need more
-  // registers than the fused kernel has to spare
-  if (s.dt == RADAR_F32 && s.d == 128) return RADAR_EUNSUPPORTED;
   const FusedArgs a{&s, q, K, V, omega, summ, sa, out, selected, sel_scores, nullptr,
                     nullptr, 0, ap, R, part, L.maxwg, st, nullptr, 0, {1, 0}};
   const radar_status r = launch_fused_any(a, false);
@@ -278,28 +275,49 @@ int64_t pair_bytes(const Shape& s, const SeqArgs& sa) {
          (u * s.c + (sp.t - sp.ws) + sp.sink) * 2 * s.d * skv;
 }
 
+#ifndef RADAR_FUSED_WAYS_MAX
+#define RADAR_FUSED_WAYS_MAX 1024
+#endif
+
+// Workgroups per pair for the fused kernel: one 512-thread workgroup per
+// CU overall, at most one per partial slot of the workspace, and 1 when the
+// pairs alone fill the chip or a pair's step is small.
+int fused_ways(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
+  const int64_t P = (int64_t)s.B * s.Hkv;
+  if (P >= num_cu() || pair_bytes(s, sa) <= (256 << 10)) return 1;
+  return (int)std::max<int64_t>(
+      1, std::min<int64_t>({num_cu() / P, (int64_t)L.maxwg, RADAR_FUSED_WAYS_MAX}));
+}
+
 // Which decode path a call takes.
 //  - fused: the shape fits its LDS plan and either there are enough (b, kv
 //    head) pairs to occupy every CU (one workgroup per pair), or each pair's
 //    step is small enough (<= 256 KB) that one workgroup streams it in a few
 //    microseconds, or a pair's summary rows are few (<= 384 KB): then R
 //    workgroups per pair each repeat the selection (the repeated rows mostly
-//    hit the caches) and share the attention (measured: 47k vs 36k tokens/s
-//    for the select path at 16K, 87k vs 86k at 64K GQA; with the 1.5 MB of
-//    rows per pair at 512K the repetition costs more than it saves);
-//  - select: fp32 caches with d = 128 (outside the fused kernel's register
-//    plan) and summary rows <= 384 KB: one workgroup per pair selects, then
-//    the split attention spreads the K/V gather over the chip;
-//  - scored: otherwise, where the fused kernel's register plan fits (G <= 4,
-//    not fp32 with d = 128): the split path's chip-wide phi(q) and score
-//    kernels, then the fused kernel from its top-k on, R workgroups per pair;
-//  - split: the rest (G = 8, fp32 caches at d = 128 with many rows):
-//    phi(q), scores and top-k as separate chip-wide kernels.
-int choose_path(const Shape& s, const SeqArgs& sa) {
+//    hit the caches) and share the attention; with the 1.5 MB of rows per
+//    pair at 512K the repetition costs more than it saves;
+//  - scored: otherwise, where the kernel is instantiated (bf16 caches, and
+//    fp32 ones with groups of up to four): phi(q) and scores chip-wide, then
+//    the fused kernel from its top-k on, R workgroups per pair (against the
+//    split path's kernels: 110 and 117 us for six ragged bf16 sequences of
+//    32K tokens with eight heads per group; against the select path's: 26.2
+//    and 32.4 us for an fp32 cache of two sequences of 12K, d = 128);
+//  - select: fp32 caches with d = 128 and summary rows <= 384 KB, where the
+//    scored kernel loses: its pairs times R leave more than an eighth of the
+//    CUs idle while the call streams more than 64 MB in all (the split
+//    attention's grid balances itself), or one workgroup per pair has little
+//    to read for the selection (Omega and summary rows up to 128 KB: 20.3 us
+//    for 8 pairs with 5 candidates and n = 128, 24.4 in the scored kernel);
+//  - split: the rest (fp32 caches with groups of eight, or at d = 128 with
+//    many rows and idle CUs as above): phi(q), scores and top-k as separate
+//    chip-wide kernels.
+int choose_path(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
   const int n_cand = make_span(sa.t_max, sa).n_cand;
+  const bool f32_d128 = s.dt == RADAR_F32 && s.d == 128;
   const bool fits_select = s.G <= kFusedMaxG && n_cand <= kFusedMaxCand;
-  const bool fits_fused = fits_select && !(s.dt == RADAR_F32 && s.d == 128);
-  const bool fits_scored = s.G <= kFusedMaxG && !(s.dt == RADAR_F32 && s.d == 128);
+  const bool fits_fused = fits_select && !f32_d128;
+  const bool fits_scored = s.G <= (s.dt == RADAR_BF16 ? kScoredMaxG : kFusedMaxG);
   switch (g_path_override) {
     case RADAR_PATH_SPLIT: return RADAR_PATH_SPLIT;
     case RADAR_PATH_FUSED: return fits_fused ? RADAR_PATH_FUSED : RADAR_PATH_SPLIT;
@@ -307,16 +325,18 @@ int choose_path(const Shape& s, const SeqArgs& sa) {
     case RADAR_PATH_SCORED: return fits_scored ? RADAR_PATH_SCORED : RADAR_PATH_SPLIT;
     default: break;
   }
+  const int64_t P = (int64_t)s.B * s.Hkv;
   const bool few_rows = (int64_t)n_cand * s.n * 4 <= (384 << 10);
-  if (fits_fused && ((int64_t)s.B * s.Hkv >= num_cu() ||
-                     pair_bytes(s, sa) <= (256 << 10) || few_rows))
+  if (fits_fused && (P >= num_cu() || pair_bytes(s, sa) <= (256 << 10) || few_rows))
     return RADAR_PATH_FUSED;
-  if (fits_select && few_rows) return RADAR_PATH_SELECT;
-  // the rest: the scored path where the fused kernel's register plan fits
-  // (measured 89.3 vs 90.5 us per step at 512K, 43.4 vs 47.2 us at the
-  // paper's settings at 16K), the split path otherwise (G = 8, fp32 d = 128)
-  if (fits_scored) return RADAR_PATH_SCORED;
-  return RADAR_PATH_SPLIT;
+  if (!fits_scored) return RADAR_PATH_SPLIT;
+  if (!f32_d128) return RADAR_PATH_SCORED;
+  const bool select = fits_select && few_rows;
+  const bool fills = P * fused_ways(s, L, sa) * 8 >= (int64_t)num_cu() * 7 ||
+                     P * pair_bytes(s, sa) <= (64 << 20);
+  const bool light = select && (int64_t)s.n * (s.d + n_cand) * 4 <= (128 << 10);
+  if (fills && !light) return RADAR_PATH_SCORED;
+  return select ? RADAR_PATH_SELECT : RADAR_PATH_SPLIT;
 }
 
 // Argument checks shared by the decode-side calls: pointers, k, the length
@@ -376,61 +396,19 @@ radar_status refresh_closed(const Shape& s, const void* K, const void* omega,
 // Which kernels a decode runs, decided (and checked) before any launch.
 struct DecodePlan {
   int path;
-  AttendGrid ag;
-  int R;               // fused kernel: workgroups per pair
-  bool tail;           // top-k, union and attention in the fused kernel's
-                       // scored mode (the scored path; see plan_decode)
+  AttendGrid ag;       // split attention (split and select paths)
+  int R;               // fused and scored paths: workgroups per pair
 };
 
-#ifndef RADAR_FUSED_WAYS_MAX
-#define RADAR_FUSED_WAYS_MAX 1024
-#endif
-
-// Workgroups per pair for the fused kernel: one 512-thread workgroup per
-// CU overall, at most one per partial slot of the workspace, and 1 when the
-// pairs alone fill the chip or a pair's step is small.
-int fused_ways(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
-  const int64_t P = (int64_t)s.B * s.Hkv;
-  if (P >= num_cu() || pair_bytes(s, sa) <= (256 << 10)) return 1;
-  return (int)std::max<int64_t>(
-      1, std::min<int64_t>({num_cu() / P, (int64_t)L.maxwg, RADAR_FUSED_WAYS_MAX}));
-}
-
-radar_status plan_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
-                         DecodePlan* p) {
-  const Span top = make_span(sa.t_max, sa);
-  p->path = choose_path(s, sa);
-  p->ag = AttendGrid{0, 1};
-  p->R = 1;
-  // The split path of a bf16 cache (a group of eight) and the split and
-  // select paths of an fp32 cache at d = 128 (groups of up to four), where
-  // the library chose them, run as the scored path does: phi(q) and scores
-  // chip-wide, then one launch instead of top-k and attention and R workgroups
-  // per pair (measured 110 against 117 us for six ragged bf16 sequences of 32K
-  // tokens with eight heads per group, 26.2 against 32.4 us for an fp32 cache of
-  // two sequences of 12K). Forced, the paths keep their own kernels.
-  // An fp32 cache whose pairs times R leave more than an eighth of the CUs idle
-  // and that streams more than 64 MB in all keeps the split attention, whose
-  // grid the hardware balances (96 pairs of 1.1 MB, R = 2: 150 us, 178 in the
-  // scored kernel; 56 pairs of 7 MB, R = 4: 182 and 79).
-  const int ways = fused_ways(s, L, sa);
-  const int64_t P = (int64_t)s.B * s.Hkv;
-  const bool fills = P * ways * 8 >= (int64_t)num_cu() * 7 ||
-                     P * pair_bytes(s, sa) <= (64 << 20);
-  // So does the select path where its one workgroup per pair has little to
-  // read (Omega and summary rows up to 128 KB: 20.3 us for 8 pairs with 5
-  // candidates and n = 128, 24.4 in the scored kernel).
-  const bool light = p->path == RADAR_PATH_SELECT &&
-                     (int64_t)s.n * (s.d + top.n_cand) * 4 <= (128 << 10);
-  p->tail = p->path == RADAR_PATH_SCORED ||
-            (g_path_override == RADAR_PATH_AUTO &&
-             (p->path == RADAR_PATH_SPLIT || p->path == RADAR_PATH_SELECT) &&
-             (s.dt == RADAR_BF16 || (s.G <= kFusedMaxG && fills && !light)));
-  if (p->path == RADAR_PATH_FUSED || p->tail) p->R = ways;
-  if (p->path == RADAR_PATH_FUSED || p->path == RADAR_PATH_SCORED) return RADAR_OK;
-  const int u_bound = std::min(s.G * top.k_eff, top.n_cand);
-  p->ag = attend_grid(s, L, u_bound, extra_tiles(s, sa));
-  return RADAR_OK;
+DecodePlan plan_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
+  DecodePlan p{choose_path(s, L, sa), AttendGrid{0, 1}, 1};
+  if (p.path == RADAR_PATH_FUSED || p.path == RADAR_PATH_SCORED) {
+    p.R = fused_ways(s, L, sa);
+  } else {
+    const Span top = make_span(sa.t_max, sa);
+    p.ag = attend_grid(s, L, std::min(s.G * top.k_eff, top.n_cand), extra_tiles(s, sa));
+  }
+  return p;
 }
 
 // The decode launches. The first per-(b, kv head) kernel of the path (the
@@ -447,7 +425,7 @@ radar_status run_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
   if (plan.path == RADAR_PATH_FUSED)
     return launch_fused(s, q, Kp, Vp, omega, summaries, sa, out, selected, scores, ap,
                         plan.R, w, L, stream);
-  if (plan.path == RADAR_PATH_SELECT && !plan.tail) {
+  if (plan.path == RADAR_PATH_SELECT) {
     const radar_status r = launch_select(s, q, omega, summaries, sa, selected, scores,
                                          w, L, ap, stream);
     if (r != RADAR_OK) return r;
@@ -458,7 +436,7 @@ radar_status run_decode(const Shape& s, const WsLayout& L, const SeqArgs& sa,
   float* sc = scores_of(s, base, sp);
   if (top.n_cand > 0)
     launch_scores(s, q, omega, summaries, base, top.n_cand, sp, sa, stream);
-  if (plan.tail) {
+  if (plan.path == RADAR_PATH_SCORED) {
     float* part = plan.R > 1 ? reinterpret_cast<float*>(w + L.part) : nullptr;
     const FusedArgs a{&s, q, Kp, Vp, omega, summaries, sa, out, selected, scores,
                       nullptr, nullptr, 0, ap, plan.R, part, L.maxwg, stream, sc,
@@ -494,9 +472,7 @@ radar_status append_decode_impl(const radar_config* cfg, const void* q, void* K,
   r = check_decode(cfg, &s, t, pos, k, workspace, workspace_bytes, &L, &sa);
   if (r != RADAR_OK) return r;
   sa.lens_add = pos ? 1 : 0;
-  DecodePlan plan;
-  r = plan_decode(s, L, sa, &plan);
-  if (r != RADAR_OK) return r;
+  const DecodePlan plan = plan_decode(s, L, sa);
   unsigned char* w = static_cast<unsigned char*>(workspace);
   const AppendArgs ap = append_args(s, K, V, k_new, v_new, pos, t - 1);
   if (s.w == 0) {
@@ -594,7 +570,7 @@ int32_t radar_decode_path(const radar_config* cfg, int64_t t, int32_t k) {
   Shape s;
   if (check_cfg(cfg, &s) != RADAR_OK || k < 1 || k > kMaxK || t < 1 || t > s.cap)
     return -1;
-  return choose_path(s, SeqArgs{nullptr, t, s.c, s.w, s.n_sink, k});
+  return choose_path(s, ws_layout(s, k), SeqArgs{nullptr, t, s.c, s.w, s.n_sink, k});
 }
 
 radar_status radar_set_phase_clock(uint64_t* clocks, int32_t max_wgs) {
@@ -741,9 +717,7 @@ radar_status radar_decode(const radar_config* cfg, const void* q, const void* K,
   SeqArgs sa;
   radar_status r = check_decode(cfg, &s, t, lens, k, workspace, workspace_bytes, &L, &sa);
   if (r != RADAR_OK) return r;
-  DecodePlan plan;
-  r = plan_decode(s, L, sa, &plan);
-  if (r != RADAR_OK) return r;
+  const DecodePlan plan = plan_decode(s, L, sa);
   return run_decode(s, L, sa, plan, q, K, V, omega, summaries, out, selected, scores,
                     static_cast<unsigned char*>(workspace), AppendArgs{}, stream);
 }

@@ -85,45 +85,99 @@ def test_infinite_value(G, d):
             _close(H.f64(out[0, h, rest]), ref, torch.bfloat16)
 
 
-@pytest.mark.parametrize("opt", ["plain", "sinks", "per_head", "ragged", "no_candidates", "w0"])
-@pytest.mark.parametrize("d", [64, 128])
-def test_group_of_eight_route(opt, d):
-    """The library's choice for a group of eight (its last stages in one
-    kernel) against the forced split path: the same selection, outputs
-    within their rounding, for both call forms."""
-    print(f"[case] g8 route {opt} d={d}", flush=True)
-    t = 1500 if opt != "no_candidates" else 60
-    cfg = radar.Config(3, 16, 2, d, 128, 37, 0 if opt == "w0" else 90, t + 4, torch.bfloat16,
-                       5 if opt == "sinks" else 0,
-                       radar.GQA_PER_HEAD if opt == "per_head" else radar.GQA_UNION)
+def _same_as_split(cfg, t, k, lens, want):
+    """decode and append_decode by the library's own choice, which has to be
+    `want` by its query and by the kernels that ran, against the forced split
+    path: the same selections, scores, rows and summaries, outputs within
+    their rounding."""
     K, V, q, omega = _inputs(cfg, 11)
     summ = radar.new_summaries(cfg, "cuda")
     radar.build_index(cfg, K, omega, t, summ)
-    lens = torch.tensor([t, t // 2, 0], device="cuda") if opt == "ragged" else None
-    k = 7
+    kernel = {radar.PATH_SPLIT: "topk", radar.PATH_SELECT: "select", radar.PATH_SCORED: "scored"}
     res = {}
     for path in (radar.PATH_AUTO, radar.PATH_SPLIT):
         radar.set_decode_path(path)
+        radar.profile_enable(True)
         try:
-            assert radar.decode_path(cfg, t, k) == radar.PATH_SPLIT
-            sel = torch.empty(3, 16, k, dtype=torch.int32, device="cuda")
-            sc = torch.empty(3, 16, k, device="cuda")
+            takes = radar.decode_path(cfg, t, k)
+            assert takes == (want if path == radar.PATH_AUTO else radar.PATH_SPLIT)
+            sel = torch.empty(cfg.batch, cfg.n_q_heads, k, dtype=torch.int32, device="cuda")
+            sc = torch.empty(cfg.batch, cfg.n_q_heads, k, device="cuda")
             out = radar.decode(cfg, q, K, V, omega, summ, t, k, selected=sel, scores=sc, lens=lens)
+            ran = radar.profile_read()
+            for p, name in kernel.items():
+                assert ran[name][1] == (1 if p == takes else 0), (name, ran)
             K2, V2, summ2 = K.clone(), V.clone(), summ.clone()
             step = radar.append_decode(cfg, q, K2, V2, K[:, :, t].clone(), V[:, :, t].clone(),
                                        omega, summ2, t + 1, k, pos=lens)
             res[path] = (out, sel, sc, step, K2, V2, summ2)
         finally:
+            radar.profile_enable(False)
+            radar.profile_read()
             radar.set_decode_path(radar.PATH_AUTO)
     a, b = res[radar.PATH_AUTO], res[radar.PATH_SPLIT]
     for i in (1, 4, 5, 6):
         assert torch.equal(a[i], b[i]), i
     assert torch.equal(a[2].nan_to_num(-1.0), b[2].nan_to_num(-1.0))
+    ulp = 2.0 ** -7 if cfg.dtype == torch.bfloat16 else 0.0
     for i in (0, 3):
         x, y = H.f64(a[i]), H.f64(b[i])
         assert np.array_equal(np.isnan(x), np.isnan(y))
-        bad = np.abs(x - y) > 2.0 ** -7 * np.abs(y) + 8e-5
+        bad = np.abs(x - y) > ulp * np.abs(y) + 8e-5
         assert not bad.any()
+
+
+OPTIONS = ["plain", "sinks", "per_head", "ragged", "no_candidates", "w0"]
+
+
+def _route(opt, G, d, dtype, n=128):
+    t = 1500 if opt != "no_candidates" else 60
+    cfg = radar.Config(3, 2 * G, 2, d, n, 37, 0 if opt == "w0" else 90, t + 4, dtype,
+                       5 if opt == "sinks" else 0,
+                       radar.GQA_PER_HEAD if opt == "per_head" else radar.GQA_UNION)
+    lens = torch.tensor([t, t // 2, 0], device="cuda") if opt == "ragged" else None
+    return cfg, t, lens
+
+
+@pytest.mark.parametrize("opt", OPTIONS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_group_of_eight_route(opt, d):
+    """The library's choice for a group of eight."""
+    print(f"[case] g8 route {opt} d={d}", flush=True)
+    cfg, t, lens = _route(opt, 8, d, torch.bfloat16)
+    _same_as_split(cfg, t, 7, lens, radar.PATH_SCORED)
+
+
+@pytest.mark.parametrize("opt", OPTIONS)
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_f32_d128_route(opt, G):
+    """The library's choice for fp32 caches at d = 128. Without candidates
+    there is only Omega's 128 KB to read, which is light."""
+    print(f"[case] fp32 route {opt} G={G}", flush=True)
+    cfg, t, lens = _route(opt, G, 128, torch.float32, n=256)
+    want = radar.PATH_SCORED if opt != "no_candidates" else radar.PATH_SELECT
+    _same_as_split(cfg, t, 7, lens, want if G < 8 else radar.PATH_SPLIT)
+
+
+@pytest.mark.parametrize("n,want", [(128, radar.PATH_SELECT), (2048, radar.PATH_SPLIT)])
+def test_f32_d128_idle_cus(n, want):
+    """fp32 calls at d = 128 that stream more than 64 MB with fewer than seven
+    eighths of the CUs busy: 144 pairs (one workgroup each) of 1 MB, with few
+    summary rows and with many."""
+    print(f"[case] fp32 idle n={n}", flush=True)
+    pairs = torch.cuda.get_device_properties(0).multi_processor_count * 9 // 16
+    cfg = radar.Config(1, pairs, pairs, 128, n, 24, 60, 1604, torch.float32)
+    _same_as_split(cfg, 1600, 40, None, want)
+
+
+@pytest.mark.parametrize("n_cand,k", [(1025, 7), (2047, 256), (300, 256)])
+@pytest.mark.parametrize("per_head", [radar.GQA_UNION, radar.GQA_PER_HEAD])
+def test_group_of_eight_many_candidates(n_cand, k, per_head):
+    """More candidates than the fused kernel takes, and the largest k."""
+    print(f"[case] g8 n_cand={n_cand} k={k}", flush=True)
+    t = 3 * n_cand + 5
+    cfg = radar.Config(2, 16, 2, 128, 64, 3, 4, t + 2, torch.bfloat16, 0, per_head)
+    _same_as_split(cfg, t, k, None, radar.PATH_SCORED)
 
 
 @pytest.mark.parametrize("call", ["decode", "split", "append_decode", "exact", "given"])

@@ -154,9 +154,11 @@ def test_large_feature_counts(n, G, dtype):
 def test_path_choice():
     """The fused path serves shapes with at least one (b, kv head) pair per
     CU, small steps, or few summary rows per pair (several workgroups per
-    pair); the select path fp32 d = 128 caches with few rows; the scored
-    path the other shapes with G <= 4 (many rows per pair, more than 1024
-    candidates); G = 8 and fp32 d = 128 with many rows the split path."""
+    pair); the scored path the other bf16 shapes (many rows per pair, more
+    than 1024 candidates, groups of eight) and the other fp32 ones with
+    G <= 4; the select path fp32 d = 128 caches whose selection is light or
+    whose pairs leave CUs idle; the split path such calls with many rows and
+    fp32 groups of eight."""
     def cfg(wl):
         return H.config_of(wl, wl.t0 + 1)
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
@@ -168,19 +170,29 @@ def test_path_choice():
     pd = WORKLOADS["paper_16k"]
     assert radar.decode_path(cfg(pd), pd.t0 + 1, pd.top_k) == radar.PATH_SCORED
     f32_many = WORKLOADS["gqa_512k"].scaled(dtype="f32")
-    assert radar.decode_path(cfg(f32_many), f32_many.t0 + 1, 32) == radar.PATH_SPLIT
+    assert radar.decode_path(cfg(f32_many), f32_many.t0 + 1, 32) == radar.PATH_SCORED
+    f32_g8 = f32_many.scaled(n_q_heads=64)
+    assert radar.decode_path(cfg(f32_g8), f32_g8.t0 + 1, 32) == radar.PATH_SPLIT
     # a small step per pair (launch-bound): fused even with few pairs
     tiny = WORKLOADS["tiny"]
     assert radar.decode_path(cfg(tiny), tiny.t0 + 1, tiny.top_k) == radar.PATH_FUSED
     g8 = mha.scaled(n_q_heads=32, n_kv_heads=4, batch=128)
-    assert radar.decode_path(cfg(g8), g8.t0 + 1, 16) == radar.PATH_SPLIT
+    assert radar.decode_path(cfg(g8), g8.t0 + 1, 16) == radar.PATH_SCORED
     # few pairs with few summary rows each: fused, several workgroups a pair
     for name in ("llama2_16k", "gqa_64k"):
         w = WORKLOADS[name]
         assert radar.decode_path(cfg(w), w.t0 + 1, w.top_k) == radar.PATH_FUSED, name
-    # the same with an fp32 cache at d = 128: select
+    # the same with an fp32 cache at d = 128: scored; select where the pairs'
+    # workgroups leave more than an eighth of the CUs idle and the call streams
+    # more than 64 MB (split with many rows), or there is little to select from
     f32 = WORKLOADS["llama2_16k"].scaled(dtype="f32")
-    assert radar.decode_path(cfg(f32), f32.t0 + 1, f32.top_k) == radar.PATH_SELECT
+    assert radar.decode_path(cfg(f32), f32.t0 + 1, f32.top_k) == radar.PATH_SCORED
+    idle = f32.scaled(n_q_heads=n_cu * 3 // 4, n_kv_heads=n_cu * 3 // 4)
+    assert radar.decode_path(cfg(idle), idle.t0 + 1, idle.top_k) == radar.PATH_SELECT
+    idle_many = idle.scaled(n_features=2048)
+    assert radar.decode_path(cfg(idle_many), idle_many.t0 + 1, idle_many.top_k) == radar.PATH_SPLIT
+    light = f32.scaled(t0=1000, n_features=128, n_q_heads=8, n_kv_heads=8)
+    assert radar.decode_path(cfg(light), light.t0 + 1, light.top_k) == radar.PATH_SELECT
     radar.set_decode_path(radar.PATH_FUSED)
     try:
         assert radar.decode_path(cfg(g5), g5.t0 + 1, g5.top_k) == radar.PATH_FUSED
@@ -195,8 +207,9 @@ def test_path_choice():
         radar.set_decode_path(radar.PATH_SCORED)
         assert radar.decode_path(cfg(mha), mha.t0 + 1, 16) == radar.PATH_SCORED
         assert radar.decode_path(cfg(many), many.t0 + 1, 16) == radar.PATH_SCORED
-        assert radar.decode_path(cfg(g8), g8.t0 + 1, 16) == radar.PATH_SPLIT
-        assert radar.decode_path(cfg(f32_many), f32_many.t0 + 1, 32) == radar.PATH_SPLIT
+        assert radar.decode_path(cfg(g8), g8.t0 + 1, 16) == radar.PATH_SCORED
+        assert radar.decode_path(cfg(f32_many), f32_many.t0 + 1, 32) == radar.PATH_SCORED
+        assert radar.decode_path(cfg(f32_g8), f32_g8.t0 + 1, 32) == radar.PATH_SPLIT
     finally:
         radar.set_decode_path(radar.PATH_AUTO)
 
