@@ -298,9 +298,10 @@ typedef enum {
                             #CUs, one pair's step reads <= 256 KB, or a
                             pair's summary rows are <= 384 KB; else scored
                             where it is available, except fp32 calls with
-                            d = 128 whose selection has little to read or
-                            whose pairs leave CUs idle: those take select
-                            (rows <= 384 KB) or split, as does the rest     */
+                            d = 128 of one head whose selection has little
+                            to read, or that leave CUs idle in a long
+                            stream: those take select (rows <= 384 KB) or
+                            split; split otherwise                          */
   RADAR_PATH_SPLIT = 1,
   RADAR_PATH_FUSED = 2,  /* used when the shape fits (G <= 4, at most 1024
                             candidate segments, not fp32 with d = 128),

@@ -303,15 +303,24 @@ int fused_ways(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
 //    split path's kernels: 110 and 117 us for six ragged bf16 sequences of
 //    32K tokens with eight heads per group; against the select path's: 26.2
 //    and 32.4 us for an fp32 cache of two sequences of 12K, d = 128);
-//  - select: fp32 caches with d = 128 and summary rows <= 384 KB, where the
-//    scored kernel loses: its pairs times R leave more than an eighth of the
-//    CUs idle while the call streams more than 64 MB in all (the split
-//    attention's grid balances itself), or one workgroup per pair has little
-//    to read for the selection (Omega and summary rows up to 128 KB: 20.3 us
-//    for 8 pairs with 5 candidates and n = 128, 24.4 in the scored kernel);
-//  - split: the rest (fp32 caches with groups of eight, or at d = 128 with
-//    many rows and idle CUs as above): phi(q), scores and top-k as separate
-//    chip-wide kernels.
+//  - select and split: the rest, fp32 caches at d = 128 (select with summary
+//    rows <= 384 KB, split with more) and groups of eight. At d = 128 fp32
+//    calls take them where the scored kernel loses. One is a single head with
+//    a light step (up to 3 MB, a selection from up to 256 KB of Omega and 96 KB
+//    of summary rows, which one workgroup reads while two launches start): 40
+//    pairs of 0.7 MB 20.2 us against 23.5, 8 pairs of 2.3 MB 19.8 against 23.3;
+//    with 4.1 MB it turns (32 pairs: 35.1 and 32.7), with 100 KB of rows too (32
+//    pairs: 29.7 and 27.3), and with two heads it already has (50 KB: 23.9 and
+//    22.7). The other is idle CUs in a stream of more than 64 MB: P pairs of R
+//    workgroups leave 256 - P R of them out where the split attention's grid
+//    takes all. What they would have read decides: one head, from 24 MB (144
+//    pairs, R = 1, of 3 MB, 337 MB: 78.3 and 101.6 us; 216 of 3 MB, 120 MB: 108.4
+//    and 115.9; 56 pairs, R = 4, of 10 MB, 80 MB: 98.6 and 108.7; 40 pairs, R = 6,
+//    of 10 MB, 27 MB: 76.4 and 81.2; 80 pairs, R = 3, of 4.4 MB, 24 MB: 84.7 and
+//    71.4), the others, whose attention is slower in the split kernel, from 256
+//    MB (144 pairs of 5.4 MB, 608 MB: 113.0 and 127.0; 104 of 11 MB, 269 MB: 160.7
+//    and 164.8; 144 of 1.7 MB, 191 MB, and 160 of 1 MB, 102 MB: equal to 1%).
+//    Over 170 fp32 calls the rule is within 0.5% of the faster one in the mean.
 int choose_path(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
   const int n_cand = make_span(sa.t_max, sa).n_cand;
   const bool f32_d128 = s.dt == RADAR_F32 && s.d == 128;
@@ -332,11 +341,15 @@ int choose_path(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
   if (!fits_scored) return RADAR_PATH_SPLIT;
   if (!f32_d128) return RADAR_PATH_SCORED;
   const bool select = fits_select && few_rows;
-  const bool fills = P * fused_ways(s, L, sa) * 8 >= (int64_t)num_cu() * 7 ||
-                     P * pair_bytes(s, sa) <= (64 << 20);
-  const bool light = select && (int64_t)s.n * (s.d + n_cand) * 4 <= (128 << 10);
-  if (fills && !light) return RADAR_PATH_SCORED;
-  return select ? RADAR_PATH_SELECT : RADAR_PATH_SPLIT;
+  const int64_t busy = P * fused_ways(s, L, sa);
+  const int64_t pair = pair_bytes(s, sa);
+  const int64_t idle_bytes =
+      P * pair > (64 << 20) ? P * pair / busy * std::max<int64_t>(0, num_cu() - busy) : 0;
+  const bool light = s.G == 1 && pair <= (3 << 20) && s.n * s.d * 4 <= (256 << 10) &&
+                     (int64_t)n_cand * s.n * 4 <= (96 << 10);
+  if (select && (light || idle_bytes > (s.G == 1 ? 24 << 20 : 256 << 20)))
+    return RADAR_PATH_SELECT;
+  return !select && idle_bytes > (256 << 20) ? RADAR_PATH_SPLIT : RADAR_PATH_SCORED;
 }
 
 // Argument checks shared by the decode-side calls: pointers, k, the length

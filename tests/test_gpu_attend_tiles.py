@@ -151,23 +151,23 @@ def test_group_of_eight_route(opt, d):
 @pytest.mark.parametrize("opt", OPTIONS)
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_f32_d128_route(opt, G):
-    """The library's choice for fp32 caches at d = 128. Without candidates
-    there is only Omega's 128 KB to read, which is light."""
+    """The library's choice for fp32 caches at d = 128: with one head these
+    170 KB of Omega and summary rows make a light selection."""
     print(f"[case] fp32 route {opt} G={G}", flush=True)
     cfg, t, lens = _route(opt, G, 128, torch.float32, n=256)
-    want = radar.PATH_SCORED if opt != "no_candidates" else radar.PATH_SELECT
-    _same_as_split(cfg, t, 7, lens, want if G < 8 else radar.PATH_SPLIT)
+    want = {1: radar.PATH_SELECT, 8: radar.PATH_SPLIT}.get(G, radar.PATH_SCORED)
+    _same_as_split(cfg, t, 7, lens, want)
 
 
-@pytest.mark.parametrize("n,want", [(128, radar.PATH_SELECT), (2048, radar.PATH_SPLIT)])
-def test_f32_d128_idle_cus(n, want):
-    """fp32 calls at d = 128 that stream more than 64 MB with fewer than seven
-    eighths of the CUs busy: 144 pairs (one workgroup each) of 1 MB, with few
-    summary rows and with many."""
-    print(f"[case] fp32 idle n={n}", flush=True)
+@pytest.mark.parametrize("G,n,want", [(2, 256, radar.PATH_SELECT), (1, 2048, radar.PATH_SPLIT)])
+def test_f32_d128_idle_cus(G, n, want):
+    """fp32 calls at d = 128 whose idle CUs leave much of the stream to the
+    others: 9/16 as many pairs (one workgroup each) as CUs, of 3 MB or more, with
+    few summary rows and with many."""
+    print(f"[case] fp32 idle G={G} n={n}", flush=True)
     pairs = torch.cuda.get_device_properties(0).multi_processor_count * 9 // 16
-    cfg = radar.Config(1, pairs, pairs, 128, n, 24, 60, 1604, torch.float32)
-    _same_as_split(cfg, 1600, 40, None, want)
+    cfg = radar.Config(1, G * pairs, pairs, 128, n, 64, 60, 4104, torch.float32)
+    _same_as_split(cfg, 4100, 40, None, want)
 
 
 @pytest.mark.parametrize("n_cand,k", [(1025, 7), (2047, 256), (300, 256)])

@@ -156,9 +156,9 @@ def test_path_choice():
     CU, small steps, or few summary rows per pair (several workgroups per
     pair); the scored path the other bf16 shapes (many rows per pair, more
     than 1024 candidates, groups of eight) and the other fp32 ones with
-    G <= 4; the select path fp32 d = 128 caches whose selection is light or
-    whose pairs leave CUs idle; the split path such calls with many rows and
-    fp32 groups of eight."""
+    G <= 4; the select path fp32 d = 128 calls of one head whose selection is
+    light or that leave CUs idle in a long stream; the split path the latter
+    with many rows and fp32 groups of eight."""
     def cfg(wl):
         return H.config_of(wl, wl.t0 + 1)
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
@@ -182,17 +182,19 @@ def test_path_choice():
     for name in ("llama2_16k", "gqa_64k"):
         w = WORKLOADS[name]
         assert radar.decode_path(cfg(w), w.t0 + 1, w.top_k) == radar.PATH_FUSED, name
-    # the same with an fp32 cache at d = 128: scored; select where the pairs'
-    # workgroups leave more than an eighth of the CUs idle and the call streams
-    # more than 64 MB (split with many rows), or there is little to select from
-    f32 = WORKLOADS["llama2_16k"].scaled(dtype="f32")
+    # the same with an fp32 cache at d = 128: scored, but select for one head
+    # with a light step (up to 96 KB of rows) or where idle CUs leave more
+    # than 24 MB to the others (split with many rows, from 256 MB)
+    light = WORKLOADS["llama2_16k"].scaled(dtype="f32", t0=8000)
+    assert radar.decode_path(cfg(light), light.t0 + 1, light.top_k) == radar.PATH_SELECT
+    f32 = light.scaled(t0=16384)
     assert radar.decode_path(cfg(f32), f32.t0 + 1, f32.top_k) == radar.PATH_SCORED
-    idle = f32.scaled(n_q_heads=n_cu * 3 // 4, n_kv_heads=n_cu * 3 // 4)
+    two = light.scaled(n_q_heads=64)
+    assert radar.decode_path(cfg(two), two.t0 + 1, two.top_k) == radar.PATH_SCORED
+    idle = f32.scaled(n_q_heads=n_cu * 9 // 16, n_kv_heads=n_cu * 9 // 16)
     assert radar.decode_path(cfg(idle), idle.t0 + 1, idle.top_k) == radar.PATH_SELECT
     idle_many = idle.scaled(n_features=2048)
     assert radar.decode_path(cfg(idle_many), idle_many.t0 + 1, idle_many.top_k) == radar.PATH_SPLIT
-    light = f32.scaled(t0=1000, n_features=128, n_q_heads=8, n_kv_heads=8)
-    assert radar.decode_path(cfg(light), light.t0 + 1, light.top_k) == radar.PATH_SELECT
     radar.set_decode_path(radar.PATH_FUSED)
     try:
         assert radar.decode_path(cfg(g5), g5.t0 + 1, g5.top_k) == radar.PATH_FUSED
