@@ -291,8 +291,9 @@ radar_status radar_schedule_sqrt(int64_t t, int32_t* seg_len, int32_t* window);
  * chip or a step is small; with R > 1 a merge kernel follows); the select
  * path runs phi(q), scores, top-k and union of each pair in one workgroup
  * and then the split path's attention and merge; the scored path takes the
- * split path's scores and runs the rest as the fused path does. All compute
- * the same method; their fp32 summation orders differ. */
+ * split path's scores and runs the rest as the fused path does. All give a
+ * sequence the same bits of scores, and so the same selections, whatever
+ * shares its batch; the fp32 summation orders of their attention differ. */
 typedef enum {
   RADAR_PATH_AUTO = 0,   /* fused when the shape fits and either B * Hkv >=
                             #CUs, one pair's step reads <= 256 KB, or a

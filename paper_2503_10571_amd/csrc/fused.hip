@@ -132,7 +132,14 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     // is computed (the rows do not depend on it), so the projection's
     // latency overlaps the stream of the scores.
     constexpr int RB = FPL <= 4 ? 2 : 1;   // 16-row batches per pass
-    const float* base = summ + (bh * s_cap) * N + lane * FPL;
+    const float* base = summ + (bh * s_cap) * N;
+    // feature e of this lane's: four consecutive ones of each chunk of 256, so
+    // that a load instruction reads whole lines (eight in a row, n = 512: half of
+    // each line per instruction, 24.0 us a step instead of 20.8 for 32 pairs of
+    // one head and 175 rows)
+    auto at = [&](int e) {
+      return FPL > 4 ? e / 4 * 256 + lane * 4 + e % 4 : lane * FPL + e;
+    };
     float x[RB][16][FPL];
     auto load_rows = [&](int rb) {
 #pragma unroll
@@ -144,24 +151,25 @@ __global__ __launch_bounds__(512) void k_decode_fused(
           if constexpr (FPL % 4 == 0) {
 #pragma unroll
             for (int e = 0; e < FPL; e += 4) {
-              const float4 v = ld_stream_f4(src + e);
+              const float4 v = ld_stream_f4(src + at(e));
               x[bt][i][e] = v.x; x[bt][i][e + 1] = v.y;
               x[bt][i][e + 2] = v.z; x[bt][i][e + 3] = v.w;
             }
           } else if constexpr (FPL == 2) {
-            const float2 v = *reinterpret_cast<const float2*>(src);
+            const float2 v = *reinterpret_cast<const float2*>(src + at(0));
             x[bt][i][0] = v.x; x[bt][i][1] = v.y;
           } else {
-            x[bt][i][0] = src[0];
+            x[bt][i][0] = src[at(0)];
           }
         }
     };
 
     // ---- 1. phi(q) -----------------------------------------------------
-    // 16 lanes per Omega row, 4 rows per wave and pass, NP passes in chunks. The first chunk's Omega loads go out first, then q, then
-    // the summary rows (when they fit in registers next to them). For bf16
-    // caches the phase is compiled once per Omega storage type and one copy
-    // runs, so all those loads stay in flight together.
+    // 16 lanes per Omega row, 4 rows per wave and pass, NP passes in chunks.
+    // The first chunk's Omega loads go out first, then q, then the summary rows
+    // (when they fit in registers next to them). For bf16 caches the phase is
+    // compiled once per Omega storage type and one copy runs, so all those
+    // loads stay in flight together.
     const int rb0 = wave * 16 * RB;
     auto phase1 = [&](auto bf_tag) {
       constexpr bool BF = decltype(bf_tag)::value;
@@ -197,59 +205,81 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     stamp(1);
 
     // ---- 2. scores ------------------------------------------------------
+    // a chunk's sum of row (lane & 15) for one head (tree_add's order)
+    auto dot = [&](const float* pq, auto&& row_at) -> float {
+      constexpr int FC = FPL < 4 ? FPL : 4;
+      float part[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float* xr = row_at(i);
+        float a = 0.f;
+#pragma unroll
+        for (int e = 0; e < FC; ++e) a = fmaf(xr[e], pq[e], a);
+        part[i] = a;
+      }
+      transpose_reduce<16>(part, lane);
+      float v = part[0];
+      v = xor_sum<16>(v);
+      return xor_sum<32>(v);
+    };
     if constexpr (N > 512) {
-      // each 16-row batch in chunks of FC features per lane (chunk ch of
-      // lane l: features ch * 64 * FC + l * FC + e), the chunk layout of
-      // the split path's score kernel, so a lane holds one chunk of the
-      // batch's rows at a time
-      constexpr int FC = G >= 4 ? 4 : 8;
-      constexpr int NCH = FPL / FC;
-      const float* rbase = summ + (bh * s_cap) * N + lane * FC;
-      for (int rb = wave * 16; rb < n_cand; rb += NW * 16) {
-        float part[G][16];
+      // a 16-row batch's chunks one after another, the next one (of this batch
+      // or the wave's next) requested before this one's products
+      constexpr int NCH = FPL / 4;
+      const float* rbase = summ + (bh * s_cap) * N + lane * 4;
+      auto load_chunk = [&](float (&xx)[16][4], int rb, int ch) {
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+        for (int i = 0; i < 16; ++i) {
+          const int row = min(rb + i, n_cand - 1);
+          const float4 f = ld_stream_f4(rbase + (int64_t)row * N + ch * 256);
+          xx[i][0] = f.x; xx[i][1] = f.y; xx[i][2] = f.z; xx[i][3] = f.w;
+        }
+      };
+      auto chunk_dot = [&](const float (&xx)[16][4], int ch, int g) {
+        float pq[4];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) part[g][i] = 0.f;
+        for (int e = 0; e < 4; ++e) pq[e] = phq[g * N + ch * 256 + lane * 4 + e];
+        return dot(pq, [&](int i) { return xx[i]; });
+      };
+      // few rows: S waves share a batch, each with a run of its chunks, and their
+      // sums are added pairwise (8 candidates at n = 2048, four pairs of one head:
+      // 16.8 us a step, 18.9 with a wave per batch; 192 pairs of four heads with
+      // 10 candidates: 87.6 and 94.5)
+      int S = 1;
+      while (S * 4 <= NCH && (n_cand + 15) / 16 * (S * 2) <= NW) S *= 2;
+      const int first = wave % S * (NCH / S), last = first + NCH / S;
+      float xa[16][4], xb[16][4];
+      int rb = wave / S * 16;
+      if (rb < n_cand) load_chunk(xa, rb, first);
+      for (; rb < n_cand; rb += NW * 16) {
+        float hold[G][3], v[G];
 #pragma unroll 1
-        for (int ch = 0; ch < NCH; ++ch) {
-          float xx[16][FC];
+        for (int ch = first; ch < last; ch += 2) {
+          load_chunk(xb, rb, ch + 1);
+          // (keeps the chunk's loads together and here: the compiler would sink
+          // each to its first use and wait on one at a time)
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int row = min(rb + i, n_cand - 1);
-            const float* src = rbase + (int64_t)row * N + ch * 64 * FC;
-#pragma unroll
-            for (int e = 0; e < FC; e += 4) {
-              const float4 v = ld_stream_f4(src + e);
-              xx[i][e] = v.x; xx[i][e + 1] = v.y; xx[i][e + 2] = v.z; xx[i][e + 3] = v.w;
-            }
-          }
-          float pq[G][FC];
-#pragma unroll
-          for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int e = 0; e < FC; ++e) pq[g][e] = phq[g * N + ch * 64 * FC + lane * FC + e];
-          // keep the chunk's loads together (the compiler would otherwise
-          // sink each to its first use and wait on one at a time)
+          for (int g = 0; g < G; ++g) v[g] = chunk_dot(xa, ch, g);
+          if (ch + 2 < last) load_chunk(xa, rb, ch + 2);
+          else if (rb + NW * 16 < n_cand) load_chunk(xa, rb + NW * 16, 0);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              float a = part[g][i];
-#pragma unroll
-              for (int e = 0; e < FC; ++e) a = fmaf(xx[i][e], pq[g][e], a);
-              part[g][i] = a;
-            }
+            v[g] = tree_add(v[g] + chunk_dot(xb, ch + 1, g), (ch - first) / 2, hold[g]);
         }
         const int row = rb + (lane & 15);
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          transpose_reduce<16>(part[g], lane);
-          float v = part[g][0];
-          v = xor_sum<16>(v);
-          v = xor_sum<32>(v);
-          if (lane < 16 && row < n_cand) sc[g * kFusedMaxCand + row] = v;
+        for (int g = 0; g < G; ++g)
+          if (lane < 16 && row < n_cand) sc[g * kFusedMaxCand + wave % S * 64 + row] = v[g];
+      }
+      if (S > 1) {                         // uniform; at most 64 rows
+        __syncthreads();
+        float* mine = sc + wave * kFusedMaxCand + lane;
+        if (wave < G && lane < n_cand) {
+          float v = mine[0] + mine[64];
+          if (S == 4) v += mine[128] + mine[192];
+          mine[0] = v;
         }
       }
     } else {
@@ -257,7 +287,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
 #pragma unroll
       for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * N + lane * FPL + e];
+        for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * N + at(e)];
       for (int rb = rb0; rb < n_cand; rb += NW * 16 * RB) {
         if (rb != rb0) load_rows(rb);
 #pragma unroll
@@ -265,18 +295,8 @@ __global__ __launch_bounds__(512) void k_decode_fused(
           const int row = rb + bt * 16 + (lane & 15);
 #pragma unroll
           for (int g = 0; g < G; ++g) {
-            float part[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              float a = 0.f;
-#pragma unroll
-              for (int e = 0; e < FPL; ++e) a = fmaf(x[bt][i][e], pq[g][e], a);
-              part[i] = a;
-            }
-            transpose_reduce<16>(part, lane);
-            float v = part[0];
-            v = xor_sum<16>(v);
-            v = xor_sum<32>(v);
+            float v = dot(&pq[g][0], [&](int i) { return &x[bt][i][0]; });
+            if constexpr (FPL == 8) v += dot(&pq[g][4], [&](int i) { return &x[bt][i][4]; });
             if (lane < 16 && row < n_cand) sc[g * kFusedMaxCand + row] = v;
           }
         }

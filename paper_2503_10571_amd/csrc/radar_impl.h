@@ -522,9 +522,34 @@ __device__ void head_topk(const float* __restrict__ src, int n_cand, int k,
   }
 }
 
-// One head's scores from nsl (2 to 8) slices of the features, `stride` floats
-// apart, added in slice order into dst (LDS) by one wave, up to 32 loads in
-// flight. Only where there are at most kFusedMaxCand candidates.
+// A segment's score is the same bits on every path, whatever shares its batch:
+// the n features are taken in chunks of 256 (all of them below that), lane l
+// holding four consecutive ones (n / 64 below 256). A chunk's products are one
+// fma chain per lane, then added over the 16 lanes of a row and over the four
+// rows; the chunks are added pairwise, (0 + 1) + (2 + 3) and so on, so that any
+// split of them into aligned runs (slices, waves) adds up to the same sum.
+//
+// tree_add takes the chunks' values one by one (at most eight) and returns the
+// sum at the last.
+__device__ __forceinline__ float tree_add(float v, int i, float (&hold)[3]) {
+  if (i & 1) {
+    v = hold[0] + v;
+    if (i & 2) {
+      v = hold[1] + v;
+      if (i & 4) v = hold[2] + v;
+      else hold[2] = v;
+    } else {
+      hold[1] = v;
+    }
+  } else {
+    hold[0] = v;
+  }
+  return v;
+}
+
+// One head's scores from nsl (2, 4 or 8) slices of the features, `stride` floats
+// apart, added pairwise into dst (LDS) by one wave, up to 32 loads in flight.
+// Only where there are at most kFusedMaxCand candidates.
 __device__ __forceinline__ void add_slices(const float* __restrict__ src, int nsl, int64_t stride,
                                            int n_cand, float* dst, int lane) {
   for (int i0 = 0; i0 < n_cand; i0 += 4 * kWave) {
@@ -536,11 +561,11 @@ __device__ __forceinline__ void add_slices(const float* __restrict__ src, int ns
         x[z][m] = src[min(z, nsl - 1) * stride + min(i0 + m * kWave + lane, n_cand - 1)];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-      float v = x[0][m];
-#pragma unroll
-      for (int z = 1; z < 8; ++z) v = z < nsl ? v + x[z][m] : v;
+      const float two = x[0][m] + x[1][m];
+      const float four = two + (x[2][m] + x[3][m]);
+      const float eight = four + ((x[4][m] + x[5][m]) + (x[6][m] + x[7][m]));
       const int i = i0 + m * kWave + lane;
-      if (i < n_cand) dst[i] = v;
+      if (i < n_cand) dst[i] = nsl == 2 ? two : nsl == 4 ? four : eight;
     }
   }
   // (the wave reads what it wrote)

@@ -94,11 +94,7 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   const int nch = fs / FC;
   const int step = (int)gridDim.x * 16 * NW;
   if (row0 >= n_cand) return;              // wave-uniform, no barrier follows
-  float part[G][16];
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) part[g][r] = 0.f;
+  float hold[G][3];                        // chunk sums (tree_add)
   int ch = 0;
   // one chunk of a row block; the next chunk's loads (of this block or the
   // wave's next one) go out first where the registers hold two (up to four
@@ -124,22 +120,23 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
     // each to its first use and wait on one at a time)
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+    for (int g = 0; g < G; ++g) {
+      float part[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
+      for (int r = 0; r < 16; ++r) {
+        float a = 0.f;
 #pragma unroll
-        for (int e = 0; e < FPL; ++e) part[g][r] = fmaf(cur[r][e], pq[g][e], part[g][r]);
-    if (c0 == nch - 1) {                   // the block is complete
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        transpose_reduce<16>(part[g], lane);
-        float v = part[g][0];
-        v = xor_sum<16>(v);
-        v = xor_sum<32>(v);
-        if (lane < 16 && r0 + lane < n_cand) out[g * (int64_t)nc_cap + r0 + lane] = v;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) part[g][r] = 0.f;
+        for (int e = 0; e < FPL; ++e) a = fmaf(cur[r][e], pq[g][e], a);
+        part[r] = a;
       }
+      transpose_reduce<16>(part, lane);
+      float v = part[0];
+      v = xor_sum<16>(v);
+      v = xor_sum<32>(v);
+      v = tree_add(v, c0, hold[g]);
+      // the block is complete
+      if (c0 == nch - 1 && lane < 16 && r0 + lane < n_cand)
+        out[g * (int64_t)nc_cap + r0 + lane] = v;
     }
     return more;
   };
@@ -177,30 +174,26 @@ __global__ __launch_bounds__(256) void k_phi(const T* __restrict__ q,
 
 // k_score: workgroup = 1, 2 or 4 waves x (16 * RB) summary rows of one (b, kv head)
 // (fewer waves per workgroup when that spreads a small call over more CUs;
-// the waves are independent). Lane l holds FPL = n / 64 features of phi(q)
-// for the G heads of the group, in chunks of at most 8 (n = 1024 and 2048
-// take 2 to 8 chunks, so the rows of a batch fit in registers); each chunk
-// of a row is one contiguous wave load, and all of a batch's rows are loaded
-// before any is reduced. A 16-row batch is transpose-reduced inside each
-// 16-lane row with DPP, then summed over the four rows.
+// the waves are independent). Lane l holds min(4, n / 64) features of phi(q)
+// for the G heads of the group and a chunk of 256 features; each chunk of a
+// row is one contiguous wave load, and all of a batch's rows are loaded before
+// any is reduced. A 16-row batch is transpose-reduced inside each 16-lane row
+// with DPP, then summed over the four rows.
 // With S > 1 the S waves of a workgroup share one batch of rows instead and
-// each takes NCH / S of the chunks (one round trip to memory instead of
-// NCH / 2 for a wave that walks them all); the waves' row sums are added in
-// LDS in wave order.
+// each takes two of the chunks (one round trip to memory instead of one per
+// chunk or two for a wave that walks them all); the waves' row sums are added
+// in LDS, pairwise.
 template <int N, int G, int S>
 __global__ __launch_bounds__(256) void k_score(const float* __restrict__ phiq,
                                                const float* __restrict__ summ,
                                                float* __restrict__ scores,
                                                int Hq, int Hkv, SeqArgs sa,
                                                int64_t s_cap, int nc_cap) {
-  constexpr int FPL = N / 64;
-  // features per lane per chunk: all of them up to n = 512; above, 8 (4
-  // for G >= 4, whose accumulators take more registers)
-  constexpr int FC = FPL <= 8 ? FPL : (G >= 4 ? 4 : 8);
-  constexpr int NCH = FPL / FC;            // chunks (1 for n <= 512)
+  constexpr int FC = N < 256 ? N / 64 : 4; // features per lane and chunk
+  constexpr int NCH = N / (64 * FC);       // chunks (1 for n <= 256)
   constexpr int RB = N <= 256 ? 2 : 1;     // 16-row batches per wave
-  static_assert(NCH % S == 0 && (S == 1 || RB == 1), "feature split");
   constexpr int CPW = NCH / S;             // chunks of each wave
+  static_assert(CPW * S == NCH && CPW <= 2 && (S == 1 || RB == 1), "feature split");
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int64_t bh = blockIdx.y;
@@ -214,17 +207,8 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ phiq,
   const int ch0 = S > 1 ? wave * CPW : 0;  // this wave's first chunk
 
   // chunk ch holds features ch * 64 * FC + lane * FC + e (e < FC) of lane
-  // `lane`, so each chunk of a row is one contiguous 64 * FC * 4-byte wave
-  // load; with one chunk (n <= 512) lane l holds features l * FPL .. + FPL
+  // `lane`, so each chunk of a row is one contiguous 64 * FC * 4-byte load
   const float* base = summ + (bh * s_cap) * N + lane * FC;
-  // per row and head a running dot product over the chunks
-  float part[RB][G][16];
-#pragma unroll
-  for (int bt = 0; bt < RB; ++bt)
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) part[bt][g][r] = 0.f;
   // a chunk's phi(q) features and rows
   auto load_chunk = [&](int ch, float (&pq)[G][FC], float (&x)[RB][16][FC]) {
 #pragma unroll
@@ -239,13 +223,9 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ phiq,
       for (int r = 0; r < 16; ++r) {
         const int row = min(wrow0 + bt * 16 + r, n_cand - 1);
         const float* src = base + (int64_t)row * N + ch * 64 * FC;
-        if constexpr (FC % 4 == 0) {
-#pragma unroll
-          for (int e = 0; e < FC; e += 4) {
-            const float4 v = ld_stream_f4(src + e);
-            x[bt][r][e] = v.x; x[bt][r][e + 1] = v.y;
-            x[bt][r][e + 2] = v.z; x[bt][r][e + 3] = v.w;
-          }
+        if constexpr (FC == 4) {
+          const float4 v = ld_stream_f4(src);
+          x[bt][r][0] = v.x; x[bt][r][1] = v.y; x[bt][r][2] = v.z; x[bt][r][3] = v.w;
         } else if constexpr (FC == 2) {
           const float2 v = *reinterpret_cast<const float2*>(src);
           x[bt][r][0] = v.x; x[bt][r][1] = v.y;
@@ -254,74 +234,73 @@ __global__ __launch_bounds__(256) void k_score(const float* __restrict__ phiq,
         }
       }
   };
-  auto add_chunk = [&](const float (&pq)[G][FC], const float (&x)[RB][16][FC]) {
+  // the chunk's sum of row (lane & 15) for one head
+  auto dot = [&](const float (&pq)[FC], const float (&x)[16][FC]) -> float {
+    float part[16];
 #pragma unroll
-    for (int bt = 0; bt < RB; ++bt)
+    for (int r = 0; r < 16; ++r) {
+      float a = 0.f;
 #pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float a = part[bt][g][r];
-#pragma unroll
-          for (int e = 0; e < FC; ++e) a = fmaf(x[bt][r][e], pq[g][e], a);
-          part[bt][g][r] = a;
-        }
+      for (int e = 0; e < FC; ++e) a = fmaf(x[r][e], pq[e], a);
+      part[r] = a;
+    }
+    transpose_reduce<16>(part, lane);
+    float v = part[0];
+    v = xor_sum<16>(v);
+    return xor_sum<32>(v);
   };
-  // Several chunks at G = 4 (four features per lane): two chunks in flight,
-  // the next one's loads issued before this one's products (same products,
-  // same order; 376 registers, one wave per SIMD, as these launches run);
-  // otherwise one chunk's rows live at a time (G = 8 would not fit).
-  constexpr bool kTwo = CPW > 1 && CPW % 2 == 0 && FC == 4 && G == 4;
-  if constexpr (kTwo) {
+  float sum[RB][G];
+  // Of two chunks both are in flight before the first products up to four heads
+  // (eight would not fit).
+  if constexpr (CPW == 2 && G <= 4) {
     float pqa[G][FC], xa[RB][16][FC], pqb[G][FC], xb[RB][16][FC];
     load_chunk(ch0, pqa, xa);
-#pragma unroll 1
-    for (int ch = ch0; ch < ch0 + CPW; ch += 2) {
-      load_chunk(ch + 1, pqb, xb);
-      __builtin_amdgcn_sched_barrier(0);
-      add_chunk(pqa, xa);
-      if (ch + 2 < ch0 + CPW) load_chunk(ch + 2, pqa, xa);
-      __builtin_amdgcn_sched_barrier(0);
-      add_chunk(pqb, xb);
-    }
+    load_chunk(ch0 + 1, pqb, xb);
+    // (the compiler would otherwise sink each load to its first use and wait
+    // on one load at a time)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) sum[0][g] = dot(pqa[g], xa[0]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) sum[0][g] += dot(pqb[g], xb[0]);
   } else {
 #pragma unroll 1
-    for (int ch = ch0; ch < ch0 + CPW; ++ch) {
+    for (int ch = 0; ch < CPW; ++ch) {
       float pq[G][FC], x[RB][16][FC];
-      load_chunk(ch, pq, x);
-      // with several chunks the compiler would sink each load to its first
-      // use and wait on one load at a time; keep the chunk's loads together
+      load_chunk(ch0 + ch, pq, x);
       if constexpr (CPW > 1) __builtin_amdgcn_sched_barrier(0);
-      add_chunk(pq, x);
-    }
-  }
-  __shared__ float red[S > 1 ? S : 1][G][16];
 #pragma unroll
-  for (int bt = 0; bt < RB; ++bt) {
-    const int row = wrow0 + bt * 16 + (lane & 15);
+      for (int bt = 0; bt < RB; ++bt)
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      transpose_reduce<16>(part[bt][g], lane);
-      float v = part[bt][g][0];
-      v = xor_sum<16>(v);
-      v = xor_sum<32>(v);
-      if constexpr (S > 1) {
-        if (lane < 16) red[wave][g][lane] = v;
-      } else {
-        if (lane < 16 && row < n_cand)
-          scores[(b * Hq + hk * G + g) * (int64_t)nc_cap + row] = v;
-      }
+        for (int g = 0; g < G; ++g) {
+          const float v = dot(pq[g], x[bt]);
+          sum[bt][g] = ch > 0 ? sum[bt][g] + v : v;
+        }
     }
   }
   if constexpr (S > 1) {
+    __shared__ float red[S][G][16];
+    if (lane < 16) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) red[wave][g][lane] = sum[0][g];
+    }
     __syncthreads();
     if (wave == 0 && lane < 16 && wrow0 + lane < n_cand) {
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        float v = red[0][g][lane];
-#pragma unroll
-        for (int w = 1; w < S; ++w) v += red[w][g][lane];
+        float v = red[0][g][lane] + red[1][g][lane];
+        if constexpr (S == 4) v += red[2][g][lane] + red[3][g][lane];
         scores[(b * Hq + hk * G + g) * (int64_t)nc_cap + wrow0 + lane] = v;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int bt = 0; bt < RB; ++bt) {
+      const int row = wrow0 + bt * 16 + lane;
+      if (lane < 16 && row < n_cand) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          scores[(b * Hq + hk * G + g) * (int64_t)nc_cap + row] = sum[bt][g];
       }
     }
   }
@@ -704,11 +683,8 @@ __global__ __launch_bounds__(NT) void k_combine(
 template <int N, int G>
 void launch_score_ng(const Shape& s, const float* phiq, const float* summ,
                      float* scores, int n_cand, const SeqArgs& sa, hipStream_t st) {
-  // above n = 512 the waves of a workgroup split a batch's chunks, two
-  // chunks each (the four features per lane at G = 4 keep two in flight)
-  constexpr int FPL = N / 64;
-  constexpr int NCH = FPL <= 8 ? 1 : FPL / (G >= 4 ? 4 : 8);
-  constexpr int S = NCH >= 4 ? NCH / 2 : 1;
+  // above n = 512 the waves of a workgroup split a batch's chunks, two each
+  constexpr int S = N > 512 ? N / 512 : 1;
   if constexpr (S > 1) {
     const dim3 grid((unsigned)ceil_div(n_cand, 16), (unsigned)(s.B * s.Hkv));
     const int nc_cap = (int)std::max<int64_t>(1, s.s_cap);

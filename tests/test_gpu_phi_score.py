@@ -61,3 +61,59 @@ def test_scores(n, n_cand, G, d, pairs):
             assert sorted(ids) == list(range(n_cand))
             err = np.max(np.abs(H.f64(sc[0, h, :n_cand]) - ref[ids]) / ref[ids])
             assert err <= H.SCORE_TOL, (path, h, err)
+
+
+@pytest.mark.parametrize("n", [64, 256, 512, 1024, 2048])
+@pytest.mark.parametrize("G,d,dtype", [(1, 128, torch.bfloat16), (2, 64, torch.bfloat16),
+                                       (4, 128, torch.bfloat16), (8, 128, torch.bfloat16),
+                                       (1, 128, torch.float32), (2, 128, torch.float32),
+                                       (4, 64, torch.float32)])
+@pytest.mark.parametrize("n_cand", [40, 130])
+def test_scores_do_not_depend_on_the_call(n, G, d, dtype, n_cand):
+    """A sequence's scores are the same bits alone and in a batch (of equal
+    and of longer sequences, with tables below and above 64 MB), with another
+    capacity, and on every path."""
+    c, w, k = 2, 2, n_cand
+    t = n_cand * c + w
+    big = (1 << 26) // (n_cand * n * 4) + 1          # pairs of a 64 MB table
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + G)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=g, device="cuda").to(dtype)
+
+    long = 2400 if n == 2048 else t + 40              # 1200 candidates beside them
+    omega = normal(n, d).to(torch.bfloat16).to(torch.float32)
+    key, query = normal(1, 1, long, d), normal(1, G, d)
+    want = None
+    for B, cap, ragged in [(1, t, False), (1, 8 * t, False), (3, t + 1, False), (5, long, True),
+                           (big, t, False), (big // 2 + 1, t + 9, False)]:
+        if B * cap * d * key.element_size() > 1 << 29:
+            continue
+        cfg = radar.Config(B, G, 1, d, n, c, w, cap, dtype)
+        K = normal(B, 1, cap, d)
+        K[:, :, :t] = key[:, :, :t]
+        q = normal(B, G, d)
+        q[B // 2] = query[0]
+        lens = None
+        if ragged:
+            lens = torch.full((B,), cap, dtype=torch.int64, device="cuda")
+            lens[B // 2] = t
+        t_max = cap if ragged else t
+        summ = radar.new_summaries(cfg, "cuda")
+        radar.build_index(cfg, K, omega, t_max, summ)
+        for path in (radar.PATH_AUTO, radar.PATH_SPLIT, radar.PATH_FUSED, radar.PATH_SELECT,
+                     radar.PATH_SCORED):
+            print(f"[case] same scores n={n} G={G} d={d} {dtype} B={B} cap={cap} path={path}",
+                  flush=True)
+            radar.set_decode_path(path)
+            try:
+                sel = torch.empty(B, G, k, dtype=torch.int32, device="cuda")
+                sc = torch.empty(B, G, k, device="cuda")
+                radar.decode(cfg, q, K, K, omega, summ, t_max, k, selected=sel, scores=sc,
+                             lens=lens)
+            finally:
+                radar.set_decode_path(radar.PATH_AUTO)
+            got = (sel[B // 2].clone(), sc[B // 2].clone())
+            want = want or got
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
