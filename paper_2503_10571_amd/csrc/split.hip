@@ -728,9 +728,12 @@ void launch_score(const Shape& s, const float* phiq, const float* summ,
 }
 
 // Feature slices of k_phi_score: one, doubled (down to 256 features each)
-// while the call has fewer workgroups than CUs, the slices' scores fit in the
-// workspace's array of n + capacity / c floats per query head, and a head's
-// sums fit in LDS.
+// while the call has fewer workgroups than CUs. Where the slices would not fit
+// (their scores in the workspace's array of n + capacity / c floats per query
+// head, a head's sums in LDS), k_phi and k_score, whose waves split the
+// features within a workgroup (1180 rows x 2048 features, six pairs of four
+// heads: 40.6 us a step, 52.3 with one slice; 871 x 1024, eight pairs: 36.2 and
+// 38.6; 512 features: 29-38 us, up to 10% less than with one slice).
 // Large summary tables (from 64 MB) take k_phi and k_score: streaming is all
 // there is to them then, and k_score's many small workgroups balance better
 // (56 pairs x 1302 rows x 2048 features, four heads: 161 us a step, 183 with
@@ -741,7 +744,8 @@ ScorePlan score_plan(const Shape& s, int n_cand) {
   if ((int64_t)n_cand * s.n * 4 * s.B * s.Hkv >= (64 << 20)) return {0, 0};
   const int64_t rows = std::max<int64_t>(1, ceil_div(n_cand, 128)) * s.B * s.Hkv;
   int nsl = 1;
-  while (n_cand <= kFusedMaxCand && s.n / nsl > 256 && rows * nsl < num_cu() && 2 * nsl * cap <= s.n + cap) nsl *= 2;
+  while (s.n / nsl > 256 && rows * nsl < num_cu()) nsl *= 2;
+  if (nsl > 1 && (n_cand > kFusedMaxCand || nsl * cap > s.n + cap)) return {0, 0};
   return {nsl, stride};
 }
 
