@@ -83,6 +83,13 @@ CASES = [
     # the fused path, a segment close at t = 4352
     (_case("gqa4_close", n_q_heads=8, n_kv_heads=2, t0=4331, seg_len=256,
            window=256, top_k=16, n_features=256, steps=24), dict(n_sink=0, per_head=False)),
+    # more segments than features: phi(q) and the scores of two kernels next to
+    # each other in the workspace
+    (_case("two_kernel_scores", n_q_heads=8, n_kv_heads=2, t0=2040, seg_len=1,
+           window=8, top_k=16, n_features=512, steps=4), dict(n_sink=0, per_head=False)),
+    # few rows of many features: the scores of four slices
+    (_case("sliced_scores", n_q_heads=16, n_kv_heads=2, t0=1200, seg_len=33,
+           window=40, top_k=9, n_features=1024, steps=4), dict(n_sink=3, per_head=False)),
 ]
 
 

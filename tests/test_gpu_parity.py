@@ -140,10 +140,10 @@ def test_paper_default_16k(path):
                                          (2048, 8, "bf16"), (2048, 2, "bf16")])
 def test_large_feature_counts(n, G, dtype):
     """n = 1024 and 2048 (the paper's default feature count): the score
-    passes read each summary row in feature chunks (the split path's score
-    kernel and the fused and select kernels' phase 2); with four or more
-    chunks the split path's score kernel spreads a row batch's chunks over
-    2 or 4 waves (n = 1024 at G >= 4, n = 2048 at every G)."""
+    passes read each summary row in chunks of 256 features, four pairs' worth
+    of rows here: in slices of the features on the split and scored paths, by
+    waves that share a row batch in the fused and select kernels. (The two
+    score kernels of large tables: test_gpu_phi_score.py.)"""
     wl = Workload(f"n{n}_g{G}", batch=2, n_q_heads=2 * G, n_kv_heads=2, head_dim=128,
                   t0=2100, seg_len=64, top_k=6, n_features=n, window=64, dtype=dtype,
                   steps=6, keys="clustered", planted=2)
@@ -291,11 +291,10 @@ def test_append_equals_rebuild_bitwise():
 @pytest.mark.parametrize("c,d,n", [(129, 128, 256), (191, 64, 512), (255, 128, 64),
                                    (384, 128, 256)])
 def test_build_tiles_ragged_segments(c, d, n):
-    """bf16 keys in segments of at least 128 go through the index build in
-    128-key tiles: segment lengths that end in a partial tile (1, 63, 127
-    keys) or span three whole tiles, against the oracle's summaries at the
-    prefix and after the appends that close a segment, and appends equal to
-    a one-shot rebuild bit for bit."""
+    """bf16 keys go through the index build in blocks of 64: segment lengths
+    of several blocks that end in a partial one or in a whole one, against
+    the oracle's summaries at the prefix and after the appends that close a
+    segment, and appends equal to a one-shot rebuild bit for bit."""
     steps = c + 2                          # at least one segment closes
     wl = _edge(f"build_c{c}", t0=6 * c + 5, seg_len=c, window=c, n_features=n,
                head_dim=d, keys="clustered", batch=2, n_kv_heads=2, n_q_heads=2,

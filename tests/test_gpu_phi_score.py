@@ -117,3 +117,61 @@ def test_scores_do_not_depend_on_the_call(n, G, d, dtype, n_cand):
             got = (sel[B // 2].clone(), sc[B // 2].clone())
             want = want or got
             assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+TYPES = [(64, torch.bfloat16), (128, torch.bfloat16), (64, torch.float32), (128, torch.float32)]
+COUNTS = [64, 128, 256, 512, 1024, 2048]
+
+
+@pytest.mark.parametrize("size,n", [("large", n) for n in COUNTS] +
+                         [("few", n) for n in COUNTS if n >= 512])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_two_kernels(n, G, size):
+    """phi(q) and the scores as two kernels, which take tables from 64 MB and
+    more than 1024 candidates where slices are wanted (n >= 512, few pairs),
+    with a shorter second sequence; every feature count and group size, and
+    between them every head dim and type."""
+    d, dtype = TYPES[(COUNTS.index(n) + G.bit_length()) % 4]
+    n_cand = 301 if size == "large" else 1061
+    pairs = (1 << 26) // (n_cand * n * 4) // 2 + 1 if size == "large" else 1
+    c, w, k = 1, 1, 200
+    t = n_cand * c + w
+    print(f"[case] two kernels n={n} G={G} d={d} {dtype} {size} pairs={2 * pairs}", flush=True)
+    cfg = radar.Config(2, G * pairs, pairs, d, n, c, w, t + 2, dtype)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + G)
+    K = torch.randn(2, pairs, t + 2, d, generator=g, device="cuda").to(dtype)
+    q = torch.randn(2, G * pairs, d, generator=g, device="cuda").to(dtype)
+    omega = torch.randn(n, d, generator=g, device="cuda").to(torch.bfloat16).float()
+    lens = torch.tensor([t, t - 66], device="cuda")
+    summ = radar.new_summaries(cfg, "cuda")
+    radar.build_index(cfg, K, omega, t, summ)
+    runs = [(cfg, omega)]
+    if dtype == torch.bfloat16:
+        runs.append((dataclasses.replace(cfg, omega_dtype=dtype), omega.to(dtype)))
+    got = []
+    for path in (radar.PATH_SPLIT, radar.PATH_SCORED):
+        for cf, om in runs:
+            radar.set_decode_path(path)
+            radar.profile_enable(True)
+            try:
+                sel = torch.empty(2, G * pairs, k, dtype=torch.int32, device="cuda")
+                sc = torch.empty(2, G * pairs, k, device="cuda")
+                radar.decode(cf, q, K, K, om, summ, t, k, selected=sel, scores=sc, lens=lens)
+                assert radar.profile_read()["phi_q"][1] == 1
+            finally:
+                radar.profile_enable(False)
+                radar.profile_read()
+                radar.set_decode_path(radar.PATH_AUTO)
+            got.append((sel, sc))
+    for sel, sc in got[1:]:
+        assert torch.equal(sel, got[0][0]) and torch.equal(sc, got[0][1])
+    sel, sc = got[0]
+    for b, count in ((0, n_cand), (1, n_cand - 66)):
+        for h in {0, G - 1, G * (pairs // 2), G * pairs - 1}:
+            s64 = H.f64(summ[b, h // G, :count])
+            ref = orc.segment_scores(orc.random_features(H.f64(q[b, h]), H.f64(omega)), s64)
+            ids = sel[b, h].cpu().numpy()
+            H.check_selection(ids, ref, k, count)
+            err = np.max(np.abs(H.f64(sc[b, h]) - ref[ids]) / ref[ids])
+            assert err <= H.SCORE_TOL, (b, h, err)
