@@ -10,11 +10,10 @@ namespace radar_impl {
 // k_phi_score: phi(q) (Eq. 4) and the segment scores a[h][s] = phi(q_h) .
 // summ[s] (Eq. 6) in one kernel
 // ---------------------------------------------------------------------------
-// Grid (row groups, pairs, feature slices). A workgroup computes phi(q) of its
+// Grid (row blocks, pairs, feature slices). A workgroup computes phi(q) of its
 // slice of fs features into LDS, with its first summary rows already in
-// flight, and then scores blocks of 16 * NW rows of the slice, 16 per wave, in
-// chunks of 64 * FPL features (each chunk of a row one contiguous
-// wave load). A slice's scores go to their own array; the top-k adds the
+// flight, and then scores 16 * NW rows of the slice, 16 per wave, in chunks of
+// 64 * FPL features (each chunk of a row one contiguous wave load). A slice's scores go to their own array; the top-k adds the
 // slices in order.
 // Small calls are bound by latency: two kernels, with phi(q) through memory
 // between them, took 11.5 us for the paper's 16K settings (8 pairs, 120 rows
@@ -58,7 +57,7 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
     }
   };
 
-  int row0 = (int)blockIdx.x * 16 * NW + wave * 16;
+  const int row0 = (int)blockIdx.x * 16 * NW + wave * 16;
   // compiled once per Omega storage type, so that all loads before the first
   // product stay in flight together
   auto phi = [&](auto bf_tag) {
@@ -91,31 +90,15 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   __syncthreads();
 
   float* out = scores + blockIdx.z * sl_stride + (b * Hq + hk * G) * (int64_t)nc_cap;
-  const int nch = fs / FC;
-  const int step = (int)gridDim.x * 16 * NW;
+  const int nch = fs / FC;                 // 1, 2, 4 or 8; 1 with FPL < 4
   if (row0 >= n_cand) return;              // wave-uniform, no barrier follows
   float hold[G][3];                        // chunk sums (tree_add)
-  int ch = 0;
-  // one chunk of a row block; the next chunk's loads (of this block or the
-  // wave's next one) go out first where the registers hold two (up to four
-  // heads), into `nxt`
-  constexpr bool kAhead = G <= 4;
-  bool loaded = true;                      // (eight heads: the first chunk only)
-  auto chunk = [&](float (&cur)[16][FPL], float (&nxt)[16][FPL]) -> bool {
-    const int r0 = row0, c0 = ch;
-    if (++ch == nch) { ch = 0; row0 += step; }
-    const bool more = row0 < n_cand;
-    if constexpr (kAhead) {
-      if (more) load_rows(nxt, row0, ch);
-    } else {
-      if (!loaded) load_rows(cur, r0, c0);
-      loaded = false;
-    }
+  auto products = [&](const float (&x)[16][FPL], int ch) {
     float pq[G][FPL];
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-      for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * fs + c0 * FC + lane * FPL + e];
+      for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * fs + ch * FC + lane * FPL + e];
     // keep the chunk's loads together (the compiler would otherwise sink
     // each to its first use and wait on one at a time)
     __builtin_amdgcn_sched_barrier(0);
@@ -126,25 +109,38 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
       for (int r = 0; r < 16; ++r) {
         float a = 0.f;
 #pragma unroll
-        for (int e = 0; e < FPL; ++e) a = fmaf(cur[r][e], pq[g][e], a);
+        for (int e = 0; e < FPL; ++e) a = fmaf(x[r][e], pq[g][e], a);
         part[r] = a;
       }
       transpose_reduce<16>(part, lane);
       float v = part[0];
       v = xor_sum<16>(v);
       v = xor_sum<32>(v);
-      v = tree_add(v, c0, hold[g]);
-      // the block is complete
-      if (c0 == nch - 1 && lane < 16 && r0 + lane < n_cand)
-        out[g * (int64_t)nc_cap + r0 + lane] = v;
+      v = tree_add(v, ch, hold[g]);
+      if (ch == nch - 1 && lane < 16 && row0 + lane < n_cand)
+        out[g * (int64_t)nc_cap + row0 + lane] = v;
     }
-    return more;
   };
-  if constexpr (kAhead) {
+  // the next chunk's loads go out before this one's products where the
+  // registers hold two (up to four heads)
+  if constexpr (FPL < 4) {
+    products(xa, 0);
+  } else if constexpr (G <= 4) {
     float xb[16][FPL];
-    while (chunk(xa, xb) && chunk(xb, xa)) {}
+#pragma unroll 1
+    for (int ch = 0; ch < nch; ch += 2) {
+      if (ch + 1 < nch) load_rows(xb, row0, ch + 1);
+      products(xa, ch);
+      if (ch + 1 >= nch) break;
+      if (ch + 2 < nch) load_rows(xa, row0, ch + 2);
+      products(xb, ch + 1);
+    }
   } else {
-    while (chunk(xa, xa)) {}
+#pragma unroll 1
+    for (int ch = 0; ch < nch; ++ch) {
+      if (ch > 0) load_rows(xa, row0, ch);
+      products(xa, ch);
+    }
   }
 }
 
@@ -758,13 +754,7 @@ void launch_phi_score(const Shape& s, const void* q, const void* omega, const fl
   const int fs = s.n / sp.nsl, P = s.B * s.Hkv;
   // four waves per workgroup where eight would leave CUs idle
   const bool narrow = ceil_div(n_cand, 128) * P * sp.nsl < num_cu();
-  const int rows = narrow ? 64 : 128;
-  // row groups: one block of rows each up to four workgroups per CU, then
-  // equal numbers of blocks (a workgroup's phi(q) serves all its blocks)
-  const int64_t blocks = ceil_div(n_cand, rows);
-  const int64_t per = std::max<int64_t>(1, blocks * P * sp.nsl / (4 * (int64_t)num_cu()));
-  const int64_t groups = ceil_div(blocks, per);
-  const dim3 grid((unsigned)groups, (unsigned)P, (unsigned)sp.nsl);
+  const dim3 grid((unsigned)ceil_div(n_cand, narrow ? 64 : 128), (unsigned)P, (unsigned)sp.nsl);
   auto go = [&](auto fpl, auto nw) {
     constexpr int NW = decltype(nw)::value;
     launch(RADAR_K_SCORE, k_phi_score<T, D, G, decltype(fpl)::value, NW>, grid, dim3(64 * NW),

@@ -1,7 +1,8 @@
 """phi(q) and the segment scores at the edges of their tiles and slices: every
 feature count, candidate counts around the row blocks of a wave and of a
 workgroup, every group size, both head dims, few and many pairs (few take
-feature slices and narrow workgroups), on the paths whose scores run as a
+feature slices and narrow workgroups; 260 of eight heads hold all of phi(q), 64
+KB, in one slice), on the paths whose scores run as a
 kernel of their own and on the fused one. All candidates are selected (k =
 256), so every score comes back; they are held to the suite's 1e-5 of the fp64
 oracle, and a bf16 Omega has to give the bits of its fp32 copy."""
@@ -33,7 +34,7 @@ def _run(path, cfg, q, K, omega, summ, t, k):
 @pytest.mark.parametrize("n_cand,G,d,pairs", [
     (1, 1, 64, 1), (15, 2, 128, 2), (16, 4, 128, 1), (17, 8, 64, 1), (63, 4, 64, 3),
     (64, 1, 128, 40), (65, 8, 128, 2), (127, 2, 64, 1), (128, 4, 128, 2), (129, 1, 64, 2),
-    (255, 4, 128, 1), (256, 8, 128, 1), (129, 4, 64, 300)])
+    (255, 4, 128, 1), (256, 8, 128, 1), (129, 4, 64, 300), (30, 8, 128, 260)])
 def test_scores(n, n_cand, G, d, pairs):
     c, w = 3, 2
     t = n_cand * c + w
