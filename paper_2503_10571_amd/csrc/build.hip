@@ -501,44 +501,61 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
 
 // Features per workgroup (16 nf), waves per workgroup and whether they share
 // a segment, by the time the call should take: rounds of the persistent grid,
-// times 64-key blocks per wave, times a wave's time per block. The last was
-// measured at d = 128 (us, for nf = 2, 4, 8, 16, 32) with two waves per SIMD
-// and with one: below nf = 8 the keys' way through the L1 bounds it, above it
-// the products, so wide slices win where there is work for every wave (4.2 M
-// keys at n = 512: 548 us at nf = 32, 705 at 8, 1852 at 2), narrow ones or
-// split segments where there is not (36 segments of 647 keys at n = 1024: 19 us
-// at nf = 16 split eight ways, 27 at nf = 4 and 138 at nf = 32 unsplit; 340 of
-// 700 at n = 512: 52 split at nf = 16, 58 at 8 and 145 at 32 unsplit). The
-// estimate is within 15% of those; d = 64 keeps the order. A feature's sum
-// depends on none of this, so a segment close and a rebuild agree bit for bit.
+// times 64-key blocks per wave, times a wave's time per block with one wave per
+// SIMD and with two (us, for nf = 2, 4, 8, 16, 32; a last round that fills at
+// most half the chip runs at the first). At d = 128 below nf = 8 the keys' way
+// through the L1 bounds a block, above it the products, so wide slices win where
+// there is work for every wave (4.2 M keys at n = 512: 548 us at nf = 32, 705 at
+// 8, 1852 at 2), narrow ones or split segments where there is not (36 segments
+// of 647 keys at n = 1024: 19 us at nf = 16 split eight ways, 27 at nf = 4 and
+// 138 at nf = 32 unsplit). At d = 64 a block costs less, and narrow slices lose
+// less (624 segments of 426 keys at n = 2048: 112 us at nf = 8, 119 at 16 and 140
+// at 16 split eight ways; d = 128, 825 of 470 at n = 1024: 108 at 32, 117 at 16
+// and 130 at 16 split). The times are fitted to 781 shapes (8 to 20000 segments of
+// 33 to 846 keys, both d, every n) in up to 13 forms each; the choice is within 2%
+// of the fastest in the mean, one in twenty misses it by more than 5%. A feature's sum depends on
+// none of this, so a segment close and a rebuild agree bit for bit.
 struct BuildPlan {
   int nf, nw;
   bool split;
-  int64_t per_round;   // items of a full round of the grid
-  float us;            // estimate
+  uint32_t full;       // items of the grid's full rounds
+  float us, full_us;   // estimates: all items, the full rounds alone
 };
-BuildPlan build_plan(int64_t items, int n, int c) {
-  constexpr float kTwo[] = {3.4f, 3.5f, 5.2f, 8.6f, 16.1f};
-  constexpr float kOne[] = {2.0f, 2.2f, 3.2f, 5.5f, 10.0f};
-  const int64_t cus = num_cu(), nblk = ceil_div(c, 64);
-  BuildPlan best{2, 4, false, 1, INFINITY};
+// f(plan) for every form of a build of `items` segments (32-bit arithmetic: a
+// short append waits for this)
+template <typename F>
+void each_build_plan(uint32_t items, int d, int n, int c, F&& f) {
+  constexpr float kOne[2][5] = {{1.1f, 1.6f, 3.0f, 3.0f, 9.0f}, {1.9f, 2.2f, 3.2f, 5.8f, 14.0f}};
+  constexpr float kTwo[2][5] = {{1.9f, 2.6f, 3.4f, 5.6f, 9.6f}, {2.4f, 3.7f, 4.5f, 6.9f, 12.1f}};
+  const uint32_t cus = (uint32_t)num_cu(), nblk = ((uint32_t)c + 63) / 64;
+  const float* one = kOne[d == 128], *two = kTwo[d == 128];
+  // a remainder of at most 32 keys costs about half a block
+  const float blocks = (float)nblk - (nblk * 64 - (uint32_t)c >= 32 ? 0.4f : 0.f);
   for (int i = 0; i < 5 && (32 << i) <= n; ++i) {
-    const int nf = 2 << i;
-    for (int split = 0; split < 3; ++split) {  // no, over 4 waves, over 8
-      const int nw = split ? 4 * split : nf >= 16 ? 8 : 4;
+    const uint32_t nf = 2u << i, slices = (uint32_t)n / (16 * nf);
+    for (uint32_t split = 0; split < 3; ++split) {   // no, over 4 waves, over 8
+      const uint32_t nw = split ? 4 * split : nf >= 16 ? 8 : 4;
       if (split && (nf > 16 || nblk < 2 || (split == 2 && nblk <= 4))) continue;
-      const int64_t slices = n / (16 * nf);
       // (a split workgroup of nf = 16 has 96 KB of LDS or more)
-      const int64_t slots =
-          std::max<int64_t>(1, (nw == 8 || (split && nf == 16) ? 1 : 2) * cus / slices);
-      const int64_t groups = split ? items : ceil_div(items, nw);
-      const int64_t gx = std::min(groups, slots);
-      const int64_t rounds = ceil_div(groups, gx) * (split ? ceil_div(nblk, nw) : nblk);
-      const bool one = nw == 4 && (gx * slices <= cus || (split && nf == 16));
-      const float us = (float)rounds * (one ? kOne[i] : kTwo[i]) + 0.15f * (float)nf;
-      if (us < best.us) best = {nf, nw, split != 0, gx * (split ? 1 : nw), us};
+      const bool alone = nw == 8 || (split && nf == 16);
+      const uint32_t slots = std::max(1u, (alone ? 1 : 2) * cus / slices);
+      const uint32_t groups = split ? items : (items + nw - 1) / nw;
+      const uint32_t gx = std::min(groups, slots);
+      const uint32_t full = groups / gx, rest = groups - full * gx;
+      auto round = [&](uint32_t wgs) {     // of so many workgroups per slice
+        const float t = nw == 4 && (alone || wgs * slices <= cus) ? one[i] : two[i];
+        if (!split) return t * blocks;
+        return (split == 1 ? 1.08f : 0.97f) * t * (float)((nblk + nw - 1) / nw) + 0.5f;
+      };
+      const float full_us = 0.1f * (float)nf + (float)full * round(gx);
+      f(BuildPlan{(int)nf, (int)nw, split != 0, full * gx * (split ? 1 : nw),
+                  full_us + (rest ? round(rest) : 0.f), full_us});
     }
   }
+}
+BuildPlan build_plan(uint32_t items, int d, int n, int c) {
+  BuildPlan best{2, 4, false, 0, INFINITY, 0.f};
+  each_build_plan(items, d, n, c, [&](const BuildPlan& p) { if (p.us < best.us) best = p; });
   return best;
 }
 
@@ -593,21 +610,28 @@ radar_status launch_build_bf16_any(const Shape& s, const void* K, const void* om
   const int64_t items = (int64_t)s.B * s.Hkv * seg_count;
   if (items == 0) return RADAR_OK;
   if (items >= ((int64_t)1 << 31)) return RADAR_EUNSUPPORTED;   // 32-bit item ids
-  const BuildPlan p = build_plan(items, s.n, s.c);
-  // a last round that is mostly empty goes to a launch of its own with a plan
-  // for few items, where the estimates say that it pays for the launch (4256
-  // segments of 300 keys, d = 64, n = 256: 81 us, one launch 95)
-  const int64_t full = items / p.per_round * p.per_round;
-  if (full > 0 && full < items) {
-    const BuildPlan rest = build_plan(items - full, s.n, s.c);
-    const BuildPlan most = build_plan(full, s.n, s.c);
-    if (most.us + rest.us + 4.f < p.us) {
-      launch_build_plan<D>(most, s, K, omega, summ, seg_first, seg_count, 0, full, pos, st);
-      launch_build_plan<D>(rest, s, K, omega, summ, seg_first, seg_count, full, items, pos, st);
-      return launch_status();
-    }
-  }
-  launch_build_plan<D>(p, s, K, omega, summ, seg_first, seg_count, 0, items, pos, st);
+  const BuildPlan p = build_plan((uint32_t)items, s.d, s.n, s.c);
+  // A last round that is mostly empty goes to a launch of its own with the plan
+  // for few items, where the estimates say that it pays for the launch, with the
+  // plan whose full rounds and rest are the least then (2088 segments of 426
+  // keys, d = 64, n = 256: 53 us, one launch 64; 524 of 426, d = 128, n = 1024:
+  // 70 and 87). Not for closes: most of them have nothing to do.
+  BuildPlan first = p, rest{};
+  float us = 0.96f * p.us;
+  if (!pos)
+    each_build_plan((uint32_t)items, s.d, s.n, s.c, [&](const BuildPlan& f) {
+      if (f.full == 0 || f.full >= items || f.full_us + 3.3f >= us) return;
+      const BuildPlan r = build_plan((uint32_t)items - f.full, s.d, s.n, s.c);
+      if (f.full_us + 3.3f + r.us < us) {
+        us = f.full_us + 3.3f + r.us;
+        first = f;
+        rest = r;
+      }
+    });
+  const int64_t full = rest.nf ? first.full : items;
+  launch_build_plan<D>(first, s, K, omega, summ, seg_first, seg_count, 0, full, pos, st);
+  if (full < items)
+    launch_build_plan<D>(rest, s, K, omega, summ, seg_first, seg_count, full, items, pos, st);
   return launch_status();
 }
 
