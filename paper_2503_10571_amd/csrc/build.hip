@@ -241,7 +241,8 @@ __global__ __launch_bounds__(256) void k_build_f32(
 // of batch 8 x 32 heads x 128K at n = 256, 615 -> 535 us for 4.2 M keys at
 // n = 512 and 94 -> 67 us for 131 K keys at n = 2048. Fetching the next
 // block ahead (n <= 256, where the registers allow it) is worth 2%.
-template <int D, int NF, int NW, bool SPLIT>
+// HOST: the keys lie in host memory (see fetch).
+template <int D, int NF, int NW, bool SPLIT, bool HOST>
 __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
     const bf16_t* __restrict__ K, const void* __restrict__ omega, bool obf,
     float* __restrict__ summ, int n, int c, int64_t cap, int64_t s_cap,
@@ -289,7 +290,20 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
   // key blocks: lane (row col, k-slot group grp) of sub-tile st holds bytes
   // kb * 64 + grp * 16 .. + 16 of key st * 16 + col; keys past the segment
   // re-read its last one and are masked by their norm
+  uint32_t touched = 0;
   auto fetch = [&](uint4 (&A)[NS][KB], const bf16_t* base, int off) {
+    // HOST: the loads below ask for half a line each, and the
+    // host link gives 44 GB/s; a word of both halves of every line first asks
+    // for whole ones (52 GB/s: 67 MB of keys 1524 -> 1296 us)
+    if constexpr (HOST) {
+#pragma unroll
+      for (int i = 0; i < D / 32; ++i) {
+        const int half = i * 64 + lane;    // of the block's lines
+        const int row = min(off + half / (D / 32), c - 1);
+        touched ^= *reinterpret_cast<const uint32_t*>(base + (int64_t)row * D + half % (D / 32) * 32);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
       const int row = min(off + st * 16 + col, c - 1);
@@ -451,6 +465,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
       item = nitem;
       base = nbase;
     }
+    if (HOST && n < 0) summ[lane] = (float)touched;    // (never: keeps the loads)
     return;
   }
 
@@ -497,6 +512,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
   } else {
     while (item < n_items) step(keys, keys);
   }
+  if (HOST && n < 0) summ[lane] = (float)touched;      // (never: keeps the loads)
 }
 
 // Features per workgroup (16 nf), waves per workgroup and whether they share
@@ -522,9 +538,9 @@ struct BuildPlan {
   float us, full_us;   // estimates: all items, the full rounds alone
 };
 // f(plan) for every form of a build of `items` segments (32-bit arithmetic: a
-// short append waits for this)
+// short append waits for this); wide: only those that read the keys least often
 template <typename F>
-void each_build_plan(uint32_t items, int d, int n, int c, F&& f) {
+void each_build_plan(uint32_t items, int d, int n, int c, bool wide, F&& f) {
   constexpr float kOne[2][5] = {{1.1f, 1.6f, 3.0f, 3.0f, 9.0f}, {1.9f, 2.2f, 3.2f, 5.8f, 14.0f}};
   constexpr float kTwo[2][5] = {{1.9f, 2.6f, 3.4f, 5.6f, 9.6f}, {2.4f, 3.7f, 4.5f, 6.9f, 12.1f}};
   const uint32_t cus = (uint32_t)num_cu(), nblk = ((uint32_t)c + 63) / 64;
@@ -533,6 +549,7 @@ void each_build_plan(uint32_t items, int d, int n, int c, F&& f) {
   const float blocks = (float)nblk - (nblk * 64 - (uint32_t)c >= 32 ? 0.4f : 0.f);
   for (int i = 0; i < 5 && (32 << i) <= n; ++i) {
     const uint32_t nf = 2u << i, slices = (uint32_t)n / (16 * nf);
+    if (wide && i < 4 && (64 << i) <= n) continue;
     for (uint32_t split = 0; split < 3; ++split) {   // no, over 4 waves, over 8
       const uint32_t nw = split ? 4 * split : nf >= 16 ? 8 : 4;
       if (split && (nf > 16 || nblk < 2 || (split == 2 && nblk <= 4))) continue;
@@ -553,16 +570,26 @@ void each_build_plan(uint32_t items, int d, int n, int c, F&& f) {
     }
   }
 }
-BuildPlan build_plan(uint32_t items, int d, int n, int c) {
+BuildPlan build_plan(uint32_t items, int d, int n, int c, bool wide) {
   BuildPlan best{2, 4, false, 0, INFINITY, 0.f};
-  each_build_plan(items, d, n, c, [&](const BuildPlan& p) { if (p.us < best.us) best = p; });
+  each_build_plan(items, d, n, c, wide, [&](const BuildPlan& p) { if (p.us < best.us) best = p; });
   return best;
+}
+
+// (60 ns a call)
+bool on_host(const void* p) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeHost;
 }
 
 template <int D, int NF, int NW, bool SPLIT>
 void launch_build_bf16(const Shape& s, const void* K, const void* omega, float* summ,
                        int seg_first, int seg_count, int64_t item0, int64_t items,
-                       const int64_t* pos, hipStream_t st) {
+                       const int64_t* pos, bool host, hipStream_t st) {
   const int slices = s.n / (16 * NF);
   const int64_t resident = std::max<int64_t>(1, (8 / NW) * (int64_t)num_cu() / slices);
   const int64_t todo = items - item0;
@@ -570,20 +597,22 @@ void launch_build_bf16(const Shape& s, const void* K, const void* omega, float* 
   const float s1 = kLog2e / std::pow((float)s.d, 0.25f);
   const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
   const float out_scale = 1.f / ((float)s.c * std::sqrt((float)s.n));
-  launch(RADAR_K_BUILD, k_build_bf16<D, NF, NW, SPLIT>, dim3((unsigned)gx, (unsigned)slices),
-         dim3(64 * NW), 0, st, reinterpret_cast<const bf16_t*>(K), omega, s.obf, summ, s.n, s.c,
-         s.cap, s.s_cap, seg_first, seg_count, (uint32_t)item0, (uint32_t)items, s1, s2,
-         out_scale, pos, s.Hkv, s.n_sink);
+  launch(RADAR_K_BUILD,
+         host ? k_build_bf16<D, NF, NW, SPLIT, true> : k_build_bf16<D, NF, NW, SPLIT, false>,
+         dim3((unsigned)gx, (unsigned)slices), dim3(64 * NW), 0, st,
+         reinterpret_cast<const bf16_t*>(K), omega, s.obf, summ, s.n, s.c, s.cap, s.s_cap,
+         seg_first, seg_count, (uint32_t)item0, (uint32_t)items, s1, s2, out_scale, pos, s.Hkv,
+         s.n_sink);
 }
 
 // items [item0, items) of the call by plan p
 template <int D>
 void launch_build_plan(const BuildPlan& p, const Shape& s, const void* K, const void* omega,
                        float* summ, int seg_first, int seg_count, int64_t item0, int64_t items,
-                       const int64_t* pos, hipStream_t st) {
+                       const int64_t* pos, bool host, hipStream_t st) {
   auto go = [&](auto f, auto w, auto sp) {
     launch_build_bf16<D, decltype(f)::value, decltype(w)::value, decltype(sp)::value>(
-        s, K, omega, summ, seg_first, seg_count, item0, items, pos, st);
+        s, K, omega, summ, seg_first, seg_count, item0, items, pos, host, st);
   };
   auto go_f = [&](auto f) {
     constexpr int NF = decltype(f)::value;
@@ -610,7 +639,15 @@ radar_status launch_build_bf16_any(const Shape& s, const void* K, const void* om
   const int64_t items = (int64_t)s.B * s.Hkv * seg_count;
   if (items == 0) return RADAR_OK;
   if (items >= ((int64_t)1 << 31)) return RADAR_EUNSUPPORTED;   // 32-bit item ids
-  const BuildPlan p = build_plan((uint32_t)items, s.d, s.n, s.c);
+  // Keys in host memory are asked for in whole lines (see fetch; from 2 MB, below
+  // which it does not show), and once they are too many for the caches they come
+  // over the host link again for every slice: from 20 MB the forms with the
+  // fewest slices (67 MB at n = 256: 1296 us, 2070 with neither; 17 MB: 361 and
+  // 412; 15 MB at n = 512: 288 and 318, 347 in one slice without whole lines).
+  const int64_t bytes = items * s.c * D * 2;
+  const bool host = bytes > (2 << 20) && on_host(K);
+  const bool wide = host && bytes > (20 << 20);
+  const BuildPlan p = build_plan((uint32_t)items, s.d, s.n, s.c, wide);
   // A last round that is mostly empty goes to a launch of its own with the plan
   // for few items, where the estimates say that it pays for the launch, with the
   // plan whose full rounds and rest are the least then (2088 segments of 426
@@ -619,9 +656,9 @@ radar_status launch_build_bf16_any(const Shape& s, const void* K, const void* om
   BuildPlan first = p, rest{};
   float us = 0.96f * p.us;
   if (!pos)
-    each_build_plan((uint32_t)items, s.d, s.n, s.c, [&](const BuildPlan& f) {
+    each_build_plan((uint32_t)items, s.d, s.n, s.c, wide, [&](const BuildPlan& f) {
       if (f.full == 0 || f.full >= items || f.full_us + 3.3f >= us) return;
-      const BuildPlan r = build_plan((uint32_t)items - f.full, s.d, s.n, s.c);
+      const BuildPlan r = build_plan((uint32_t)items - f.full, s.d, s.n, s.c, wide);
       if (f.full_us + 3.3f + r.us < us) {
         us = f.full_us + 3.3f + r.us;
         first = f;
@@ -629,9 +666,9 @@ radar_status launch_build_bf16_any(const Shape& s, const void* K, const void* om
       }
     });
   const int64_t full = rest.nf ? first.full : items;
-  launch_build_plan<D>(first, s, K, omega, summ, seg_first, seg_count, 0, full, pos, st);
+  launch_build_plan<D>(first, s, K, omega, summ, seg_first, seg_count, 0, full, pos, host, st);
   if (full < items)
-    launch_build_plan<D>(rest, s, K, omega, summ, seg_first, seg_count, full, items, pos, st);
+    launch_build_plan<D>(rest, s, K, omega, summ, seg_first, seg_count, full, items, pos, host, st);
   return launch_status();
 }
 

@@ -115,3 +115,30 @@ def test_graph_replays_equal_eager(merged, path):
             torch.randn(1 << 20, device="cuda").sum().item()
     finally:
         radar.set_decode_path(radar.PATH_AUTO)
+
+
+@pytest.mark.parametrize("where", ["device", "host"])
+def test_captured_build(where):
+    """An index build of 43 MB of keys (which asks where the keys lie) under
+    capture, the keys changed between the replays."""
+    print(f"[case] graph capture: build of {where} keys", flush=True)
+    c, segs, pairs, d = 300, 70, 8, 128
+    t = c * segs
+    cfg = radar.Config(pairs, 1, 1, d, 256, c, c, t + 1, torch.bfloat16)
+    K = torch.randn(pairs, 1, t + 1, d, device="cuda").to(torch.bfloat16)
+    omega = torch.randn(256, d, device="cuda").to(torch.bfloat16).float()
+    keys = K.cpu().pin_memory() if where == "host" else K
+    eager, summ = (radar.new_summaries(cfg, "cuda") for _ in range(2))
+    radar.build_index(cfg, keys, omega, t, summ)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        radar.build_index(cfg, keys, omega, t, summ)
+    for rep in range(3):
+        keys.mul_(0.75)
+        radar.build_index(cfg, keys, omega, t, eager)
+        summ.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(eager, summ), rep

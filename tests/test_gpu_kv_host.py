@@ -152,3 +152,32 @@ def test_layer_with_host_cache(schedule):
         torch.cuda.synchronize()
         assert torch.equal(_bits(outs[0]), _bits(outs[1])), i
     assert torch.equal(_bits(layers[0].summaries), _bits(layers[1].summaries))
+
+
+@pytest.mark.parametrize("n,d,c,segs", [(64, 128, 100, 30), (256, 64, 33, 300), (512, 128, 70, 44),
+                                        (2048, 128, 129, 20), (256, 128, 300, 70),
+                                        (1024, 64, 200, 220)])
+def test_build_of_host_keys(n, d, c, segs):
+    """Index builds of more than 2 MB (a form of their own for host memory)
+    and 20 MB (the widest slices) of keys, and the closes of a batch, give the
+    bits of the same build from device memory."""
+    pairs, t = 8, segs * c
+    print(f"[case] host build n={n} d={d} c={c} segs={segs}", flush=True)
+    cfg = radar.Config(pairs, 1, 1, d, n, c, c, t + 5, torch.bfloat16)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + c)
+    K = torch.randn(pairs, 1, t + 5, d, generator=g, device="cuda").to(torch.bfloat16)
+    omega = torch.randn(n, d, generator=g, device="cuda").to(torch.bfloat16).float()
+    dev, host = (radar.new_summaries(cfg, "cuda") for _ in range(2))
+    radar.build_index(cfg, K, omega, t, dev)
+    Kh = _pinned(K)
+    radar.build_index(cfg, Kh, omega, t, host)
+    assert torch.equal(dev, host)
+    # closes: the last segment again, at positions of their own (one closes none)
+    pos = torch.tensor([t - 1] * (pairs - 1) + [t - 2], device="cuda")
+    rows = K[torch.arange(pairs, device="cuda"), :, pos].clone()
+    host[:-1, :, segs - 1] = 0
+    Vh = _pinned(K)
+    radar.append(cfg, Kh, Vh, rows, rows, omega, 0, host, pos=pos)
+    torch.cuda.synchronize()
+    assert torch.equal(dev, host)
