@@ -229,18 +229,16 @@ __global__ __launch_bounds__(256) void k_build_f32(
 // turn, and a segment's total adds the block sums in block order, as a wave
 // that walks the segment alone does, so both forms give the same bits.
 //
-// What bounds it is power: at two waves per SIMD the 64 MFMAs, 64 exp2, 64
-// fma and 64 adds of 64 keys x 64 features take the same time whether they
-// are interleaved by hand or left to the compiler to within 3% (the clock
-// falls from 2.2 to 1.7 GHz as the schedule gets denser), so what counts is
-// work per key and feature. For 1024 (key, feature) quads a SIMD takes 195 ns
-// with everything in registers; B fragments from LDS add 15 ns, keys from
-// HBM 50 ns at 256 features per pass and half of that at 512. Keys staged
-// through LDS and shared by four waves, with a barrier per 128 keys (the
-// layout before this one), took 334 ns: 2.71 -> 2.42 ms for the 33.5 M keys
-// of batch 8 x 32 heads x 128K at n = 256, 615 -> 535 us for 4.2 M keys at
-// n = 512 and 94 -> 67 us for 131 K keys at n = 2048. Fetching the next
-// block ahead (n <= 256, where the registers allow it) is worth 2%.
+// What bounds it is the matrix and vector work of a SIMD together. A 16x16 tile
+// of keys and features at d = 128 is 64 cycles on the matrix pipe and 96 of
+// vector issue (four elements per lane: exp2 at quarter rate 64, fma and add 16
+// each); a SIMD takes 135 per tile at 256 features (33.5 M keys in 2.38 ms at the
+// 1.86 GHz that it runs at; the matrix pipe is busy 47% of them), however the
+// two are interleaved, by hand or by the compiler, to within 3%. Keys staged
+// through LDS and shared by four waves, with a barrier per 128 keys (the layout
+// before this one), took 2.71 ms; 615 -> 535 us for 4.2 M keys at n = 512 and 94
+// -> 67 us for 131 K keys at n = 2048. Fetching the next block ahead (n <= 256,
+// where the registers allow it) is worth 2%.
 // HOST: the keys lie in host memory (see fetch).
 template <int D, int NF, int NW, bool SPLIT, bool HOST>
 __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(

@@ -17,7 +17,8 @@
 //                  segment (split and scored paths): phi(q) of a feature slice
 //                  in LDS, HBM-bound GEMV over the fp32 summaries, DPP
 //                  transpose-reduce.
-//   k_phi, k_score the same as two kernels, for large summary tables.
+//   k_phi, k_score the same as two kernels, for large summary tables and many
+//                  rows of few pairs.
 //   k_topk_union   per query head top-k (score desc, index asc) by radix
 //                  selection; per kv head sorted union of the group.
 //   k_segment_mass ln(beta_s), the exact attention mass of every candidate

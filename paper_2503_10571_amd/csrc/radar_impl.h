@@ -653,10 +653,11 @@ struct TileRef {
 // transpose-reduced so that each lane ends with one token's logit, softmax
 // runs across the wave, and p is broadcast back (DPP row broadcast) to the
 // lanes that hold the matching V chunks. At d = 128 the 64 rows of K and V take
-// 256 registers, which k_attend has for one or two heads (IT = 32: 150 us for
-// 96 pairs of 1.1 MB with two heads, 197 in halves); with more heads, and in
-// the 512-thread workgroups of the scored kernel, a tile is done in two halves
-// of 32 rows (IT = 16: 309 us instead of 610 for 40 pairs with eight heads).
+// 256 registers, which k_attend has for one or two heads (IT = 32: a step of 96
+// pairs of 8.4 MB with two heads 112 us, 129 in halves; of 1.0 MB 32 and 40;
+// with one head 137 and 154); with more heads, and in the 512-thread workgroups
+// of the scored kernel, a tile is done in two halves of 32 rows (IT = 16: 75 us
+// instead of 120 for 40 pairs of 3.3 MB with eight heads).
 template <int D, int G, int IT = 16>
 struct TileVec {
   static constexpr int kLdsBytes = 0;           // per wave

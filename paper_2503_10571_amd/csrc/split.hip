@@ -145,7 +145,7 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
 }
 
 // ---------------------------------------------------------------------------
-// k_phi, k_score: the same as two kernels, for large summary tables
+// k_phi, k_score: the same as two kernels (score_plan says when)
 // ---------------------------------------------------------------------------
 // k_phi: phi(q) of 64 features of one (b, kv head) per workgroup.
 template <typename T, int D, int G, bool BF>
@@ -689,7 +689,8 @@ void launch_score_ng(const Shape& s, const float* phiq, const float* summ,
   } else {
     constexpr int rows_per_wave = 16 * (N <= 256 ? 2 : 1);
     // waves per workgroup: 4 when that still gives two workgroups per CU,
-    // else fewer, so that the rows spread over more CUs
+    // else fewer, so that the rows spread over more CUs (n = 512, where the
+    // slices of few pairs had no room; large tables always give them)
     int wpb = 4;
     while (wpb > 1 && ceil_div(n_cand, rows_per_wave * wpb) * s.B * s.Hkv < 2 * num_cu())
       wpb >>= 1;
