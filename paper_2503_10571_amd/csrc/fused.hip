@@ -132,14 +132,13 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     // is computed (the rows do not depend on it), so the projection's
     // latency overlaps the stream of the scores.
     constexpr int RB = FPL <= 4 ? 2 : 1;   // 16-row batches per pass
-    const float* base = summ + (bh * s_cap) * N;
+    constexpr int FC = FPL < 4 ? FPL : 4;  // ... of a chunk
+    const float* base = summ + (bh * s_cap) * N + lane * FC;
     // feature e of this lane's: four consecutive ones of each chunk of 256, so
     // that a load instruction reads whole lines (eight in a row, n = 512: half of
     // each line per instruction, 24.0 us a step instead of 20.8 for 32 pairs of
     // one head and 175 rows)
-    auto at = [&](int e) {
-      return FPL > 4 ? e / 4 * 256 + lane * 4 + e % 4 : lane * FPL + e;
-    };
+    auto at = [](int e) { return e / 4 * 256 + e % 4; };   // from base
     float x[RB][16][FPL];
     auto load_rows = [&](int rb) {
 #pragma unroll
@@ -207,7 +206,6 @@ __global__ __launch_bounds__(512) void k_decode_fused(
     // ---- 2. scores ------------------------------------------------------
     // a chunk's sum of row (lane & 15) for one head (tree_add's order)
     auto dot = [&](const float* pq, auto&& row_at) -> float {
-      constexpr int FC = FPL < 4 ? FPL : 4;
       float part[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -287,7 +285,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(
 #pragma unroll
       for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * N + at(e)];
+        for (int e = 0; e < FPL; ++e) pq[g][e] = phq[g * N + lane * FC + at(e)];
       for (int rb = rb0; rb < n_cand; rb += NW * 16 * RB) {
         if (rb != rb0) load_rows(rb);
 #pragma unroll

@@ -122,20 +122,23 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
     }
   };
   // the next chunk's loads go out before this one's products where the
-  // registers hold two (up to four heads)
-  if constexpr (FPL < 4) {
+  // registers hold two (up to four heads); a single chunk, what small calls
+  // take, by itself (before a loop the compiler works out every row's address:
+  // 0.4 us of a step)
+  if (FPL < 4 || nch == 1) {
     products(xa, 0);
-  } else if constexpr (G <= 4) {
+    return;
+  }
+  if constexpr (FPL == 4 && G <= 4) {
     float xb[16][FPL];
 #pragma unroll 1
     for (int ch = 0; ch < nch; ch += 2) {
-      if (ch + 1 < nch) load_rows(xb, row0, ch + 1);
+      load_rows(xb, row0, ch + 1);
       products(xa, ch);
-      if (ch + 1 >= nch) break;
       if (ch + 2 < nch) load_rows(xa, row0, ch + 2);
       products(xb, ch + 1);
     }
-  } else {
+  } else if constexpr (FPL == 4) {
 #pragma unroll 1
     for (int ch = 0; ch < nch; ++ch) {
       if (ch > 0) load_rows(xa, row0, ch);
