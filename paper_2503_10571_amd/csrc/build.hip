@@ -290,9 +290,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_build_bf16(
   // re-read its last one and are masked by their norm
   uint32_t touched = 0;
   auto fetch = [&](uint4 (&A)[NS][KB], const bf16_t* base, int off) {
-    // HOST: the loads below ask for half a line each, and the
-    // host link gives 44 GB/s; a word of both halves of every line first asks
-    // for whole ones (52 GB/s: 67 MB of keys 1524 -> 1296 us)
+    // HOST: the loads below ask for half a line each, and the host link gives
+    // 45 to 53 GB/s; a word of both halves of every line first asks for whole
+    // ones (56 GB/s: 1.07 GB of keys 22.1 -> 19.1 ms, 268 MB 5.65 -> 4.79)
     if constexpr (HOST) {
 #pragma unroll
       for (int i = 0; i < D / 32; ++i) {
@@ -536,9 +536,10 @@ struct BuildPlan {
   float us, full_us;   // estimates: all items, the full rounds alone
 };
 // f(plan) for every form of a build of `items` segments (32-bit arithmetic: a
-// short append waits for this); wide: only those that read the keys least often
+// short append waits for this); link: only the form for keys in host memory (see
+// launch_build_bf16_any)
 template <typename F>
-void each_build_plan(uint32_t items, int d, int n, int c, bool wide, F&& f) {
+void each_build_plan(uint32_t items, int d, int n, int c, bool link, F&& f) {
   constexpr float kOne[2][5] = {{1.1f, 1.6f, 3.0f, 3.0f, 9.0f}, {1.9f, 2.2f, 3.2f, 5.8f, 14.0f}};
   constexpr float kTwo[2][5] = {{1.9f, 2.6f, 3.4f, 5.6f, 9.6f}, {2.4f, 3.7f, 4.5f, 6.9f, 12.1f}};
   const uint32_t cus = (uint32_t)num_cu(), nblk = ((uint32_t)c + 63) / 64;
@@ -547,10 +548,10 @@ void each_build_plan(uint32_t items, int d, int n, int c, bool wide, F&& f) {
   const float blocks = (float)nblk - (nblk * 64 - (uint32_t)c >= 32 ? 0.4f : 0.f);
   for (int i = 0; i < 5 && (32 << i) <= n; ++i) {
     const uint32_t nf = 2u << i, slices = (uint32_t)n / (16 * nf);
-    if (wide && i < 4 && (64 << i) <= n) continue;
+    if (link && i != 2 && (i > 2 || (64 << i) <= n)) continue;
     for (uint32_t split = 0; split < 3; ++split) {   // no, over 4 waves, over 8
       const uint32_t nw = split ? 4 * split : nf >= 16 ? 8 : 4;
-      if (split && (nf > 16 || nblk < 2 || (split == 2 && nblk <= 4))) continue;
+      if (link ? split != 2 : split && (nf > 16 || nblk < 2 || (split == 2 && nblk <= 4))) continue;
       // (a split workgroup of nf = 16 has 96 KB of LDS or more)
       const bool alone = nw == 8 || (split && nf == 16);
       const uint32_t slots = std::max(1u, (alone ? 1 : 2) * cus / slices);
@@ -568,9 +569,9 @@ void each_build_plan(uint32_t items, int d, int n, int c, bool wide, F&& f) {
     }
   }
 }
-BuildPlan build_plan(uint32_t items, int d, int n, int c, bool wide) {
+BuildPlan build_plan(uint32_t items, int d, int n, int c, bool link) {
   BuildPlan best{2, 4, false, 0, INFINITY, 0.f};
-  each_build_plan(items, d, n, c, wide, [&](const BuildPlan& p) { if (p.us < best.us) best = p; });
+  each_build_plan(items, d, n, c, link, [&](const BuildPlan& p) { if (p.us < best.us) best = p; });
   return best;
 }
 
@@ -591,7 +592,11 @@ void launch_build_bf16(const Shape& s, const void* K, const void* omega, float* 
   const int slices = s.n / (16 * NF);
   const int64_t resident = std::max<int64_t>(1, (8 / NW) * (int64_t)num_cu() / slices);
   const int64_t todo = items - item0;
-  const int64_t gx = std::min<int64_t>(SPLIT ? todo : ceil_div(todo, NW), resident);
+  int64_t gx = std::min<int64_t>(SPLIT ? todo : ceil_div(todo, NW), resident);
+  // workgroups go round the 8 XCDs in turn, so with a multiple of 8 a segment's
+  // slices read it through one L2, and it comes over the host link once (27
+  // segments of 724 keys in two slices: 101 us, 192 with 27 workgroups each)
+  if (host) gx = ceil_div(gx, 8) * 8;
   const float s1 = kLog2e / std::pow((float)s.d, 0.25f);
   const float s2 = kLog2e / (2.f * std::sqrt((float)s.d));
   const float out_scale = 1.f / ((float)s.c * std::sqrt((float)s.n));
@@ -638,14 +643,18 @@ radar_status launch_build_bf16_any(const Shape& s, const void* K, const void* om
   if (items == 0) return RADAR_OK;
   if (items >= ((int64_t)1 << 31)) return RADAR_EUNSUPPORTED;   // 32-bit item ids
   // Keys in host memory are asked for in whole lines (see fetch; from 2 MB, below
-  // which it does not show), and once they are too many for the caches they come
-  // over the host link again for every slice: from 20 MB the forms with the
-  // fewest slices (67 MB at n = 256: 1296 us, 2070 with neither; 17 MB: 361 and
-  // 412; 15 MB at n = 512: 288 and 318, 347 in one slice without whole lines).
-  const int64_t bytes = items * s.c * D * 2;
-  const bool host = bytes > (2 << 20) && on_host(K);
-  const bool wide = host && bytes > (20 << 20);
-  const BuildPlan p = build_plan((uint32_t)items, s.d, s.n, s.c, wide);
+  // which it does not show) and come over the link once only where a segment's
+  // slices read it through one L2 (see launch_build_bf16) at about the same time:
+  // eight waves that share a segment keep its slices together, in slices of up to
+  // 128 features (1.07 GB at n = 256 in segments of 256 keys: 19.1 ms, 56 GB/s;
+  // 23.7 in one slice with a segment per wave, 38.3 with four waves; of 1500 keys:
+  // 19.0, 25.5 in one split slice; 13 MB at n = 512 in segments of 64: 237 us, 275
+  // in the form of device memory). Above n = 1024 these are too many slices where
+  // segments are short, and the forms of device memory do as well or better
+  // (n = 2048, 67 MB in segments of 33: 54 and 36 GB/s; 268 MB of 362: 56 and 51).
+  const bool host = items * s.c * D * 2 > (2 << 20) && on_host(K);
+  const bool link = host && s.n <= 1024;
+  const BuildPlan p = build_plan((uint32_t)items, s.d, s.n, s.c, link);
   // A last round that is mostly empty goes to a launch of its own with the plan
   // for few items, where the estimates say that it pays for the launch, with the
   // plan whose full rounds and rest are the least then (2088 segments of 426
@@ -654,9 +663,9 @@ radar_status launch_build_bf16_any(const Shape& s, const void* K, const void* om
   BuildPlan first = p, rest{};
   float us = 0.96f * p.us;
   if (!pos)
-    each_build_plan((uint32_t)items, s.d, s.n, s.c, wide, [&](const BuildPlan& f) {
+    each_build_plan((uint32_t)items, s.d, s.n, s.c, link, [&](const BuildPlan& f) {
       if (f.full == 0 || f.full >= items || f.full_us + 3.3f >= us) return;
-      const BuildPlan r = build_plan((uint32_t)items - f.full, s.d, s.n, s.c, wide);
+      const BuildPlan r = build_plan((uint32_t)items - f.full, s.d, s.n, s.c, link);
       if (f.full_us + 3.3f + r.us < us) {
         us = f.full_us + 3.3f + r.us;
         first = f;

@@ -154,15 +154,19 @@ def test_layer_with_host_cache(schedule):
     assert torch.equal(_bits(layers[0].summaries), _bits(layers[1].summaries))
 
 
-@pytest.mark.parametrize("n,d,c,segs", [(64, 128, 100, 30), (256, 64, 33, 300), (512, 128, 70, 44),
-                                        (2048, 128, 129, 20), (256, 128, 300, 70),
-                                        (1024, 64, 200, 220)])
-def test_build_of_host_keys(n, d, c, segs):
-    """Index builds of more than 2 MB (a form of their own for host memory)
-    and 20 MB (the widest slices) of keys, and the closes of a batch, give the
-    bits of the same build from device memory."""
-    pairs, t = 8, segs * c
-    print(f"[case] host build n={n} d={d} c={c} segs={segs}", flush=True)
+@pytest.mark.parametrize("n,d,c,segs,pairs", [
+    (64, 128, 100, 30, 8), (256, 64, 33, 300, 8), (512, 128, 70, 44, 8), (2048, 128, 129, 20, 8),
+    (256, 128, 300, 70, 8), (1024, 64, 200, 220, 8),
+    # segments shorter than the eight waves' share, one block and less of it
+    (64, 64, 30, 1500, 8), (128, 128, 65, 200, 8), (2048, 128, 33, 400, 8),
+    # grids that are rounded up over the segments
+    (256, 128, 724, 27, 1), (2048, 128, 300, 11, 5), (64, 64, 700, 13, 3)])
+def test_build_of_host_keys(n, d, c, segs, pairs):
+    """Index builds of more than 2 MB of keys (forms and grids of their own for
+    host memory), and the closes of a batch, give the bits of the same build
+    from device memory."""
+    t = segs * c
+    print(f"[case] host build n={n} d={d} c={c} segs={segs} pairs={pairs}", flush=True)
     cfg = radar.Config(pairs, 1, 1, d, n, c, c, t + 5, torch.bfloat16)
     g = torch.Generator(device="cuda")
     g.manual_seed(n + c)
@@ -174,7 +178,7 @@ def test_build_of_host_keys(n, d, c, segs):
     radar.build_index(cfg, Kh, omega, t, host)
     assert torch.equal(dev, host)
     # closes: the last segment again, at positions of their own (one closes none)
-    pos = torch.tensor([t - 1] * (pairs - 1) + [t - 2], device="cuda")
+    pos = torch.tensor(([t - 1] * (pairs - 1) + [t - 2])[-pairs:], device="cuda")
     rows = K[torch.arange(pairs, device="cuda"), :, pos].clone()
     host[:-1, :, segs - 1] = 0
     Vh = _pinned(K)
