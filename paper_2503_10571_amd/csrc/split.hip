@@ -41,10 +41,15 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   const float* base = summ + bh * s_cap * n + f0 + lane * FPL;
 
   float xa[16][FPL];
+  // (an opaque row length: the sixteen addresses are worked out again for each
+  // chunk; kept across chunks they took all registers and spilled, 45.8 us for
+  // a step with four sequences of 1995 candidates at n = 512, 39.6 without)
   auto load_rows = [&](float (&x)[16][FPL], int row0, int ch) {
+    int len = n;
+    asm volatile("" : "+s"(len));
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float* src = base + (int64_t)min(row0 + r, n_cand - 1) * n + ch * FC;
+      const float* src = base + (int64_t)min(row0 + r, n_cand - 1) * len + ch * FC;
       if constexpr (FPL == 4) {
         const float4 v = ld_stream_f4(src);
         x[r][0] = v.x; x[r][1] = v.y; x[r][2] = v.z; x[r][3] = v.w;
