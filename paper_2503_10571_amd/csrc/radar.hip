@@ -318,10 +318,12 @@ int fused_ways(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
 //    pairs, R = 1, of 3 MB, 337 MB: 78.3 and 101.6 us; 216 of 3 MB, 120 MB: 108.4
 //    and 115.9; 56 pairs, R = 4, of 10 MB, 80 MB: 98.6 and 108.7; 40 pairs, R = 6,
 //    of 10 MB, 27 MB: 76.4 and 81.2; 80 pairs, R = 3, of 4.4 MB, 24 MB: 84.7 and
-//    71.4), the others, whose attention is slower in the split kernel, from 256
-//    MB (144 pairs of 5.4 MB, 608 MB: 113.0 and 127.0; 104 of 11 MB, 269 MB: 160.7
-//    and 164.8; 144 of 1.7 MB, 191 MB, and 160 of 1 MB, 102 MB: equal to 1%).
-//    Over 170 fp32 calls the rule is within 0.5% of the faster one in the mean.
+//    71.4), the others, whose attention is slower in the split kernel, from 80
+//    MB (96 pairs of 3 MB, 92 MB: 69.8 and 83.4; 192 of 2.9 MB, 177 MB: 101.9 and
+//    110.0; 144 of 5.4 MB, 608 MB: 113.0 and 127.0; below, 72 pairs of 5.7 MB, 72
+//    MB: 84.7 and 78.4, and 96 of 1.6 MB, 50 MB: 47.9 and 52.1; above it 216 pairs
+//    of 3.6 MB, 137 MB, are the other way: 151.0 and 141.8).
+//    Over 180 fp32 calls the rule is within 1% of the faster one in the mean.
 int choose_path(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
   const int n_cand = make_span(sa.t_max, sa).n_cand;
   const bool f32_d128 = s.dt == RADAR_F32 && s.d == 128;
@@ -348,7 +350,7 @@ int choose_path(const Shape& s, const WsLayout& L, const SeqArgs& sa) {
       P * pair > (64 << 20) ? P * pair / busy * std::max<int64_t>(0, num_cu() - busy) : 0;
   const bool light = s.G == 1 && pair <= (3 << 20) && s.n * s.d * 4 <= (256 << 10) &&
                      (int64_t)n_cand * s.n * 4 <= (96 << 10);
-  if (select && (light || idle_bytes > (s.G == 1 ? 24 << 20 : 256 << 20)))
+  if (select && (light || idle_bytes > (s.G == 1 ? 24 << 20 : 80 << 20)))
     return RADAR_PATH_SELECT;
   return !select && idle_bytes > (256 << 20) ? RADAR_PATH_SPLIT : RADAR_PATH_SCORED;
 }
