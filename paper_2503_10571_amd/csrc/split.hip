@@ -43,10 +43,11 @@ __global__ __launch_bounds__(64 * NW) void k_phi_score(
   float xa[16][FPL];
   // (an opaque row length: the sixteen addresses are worked out again for each
   // chunk; kept across chunks they took all registers and spilled, 45.8 us for
-  // a step with four sequences of 1995 candidates at n = 512, 39.6 without)
+  // a step with four sequences of 1995 candidates at n = 512, 39.6 without. Not
+  // for the first chunk, 0.2 us of a small call, nor where eight heads hold one)
   auto load_rows = [&](float (&x)[16][FPL], int row0, int ch) {
     int len = n;
-    asm volatile("" : "+s"(len));
+    if (G <= 4 && ch > 0) asm volatile("" : "+s"(len));
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float* src = base + (int64_t)min(row0 + r, n_cand - 1) * len + ch * FC;
